@@ -414,6 +414,39 @@ int build_grid(const thor_grid_params &p, Grid &G) {
     add_grad(c, -lsum);
     if (cnt > kRing2) return THOR_EINVAL;
   }
+
+  // Tangent bases and the coefficients in them: horizontal momentum has two
+  // components, so the step's kernels gather two rows and weights, not three.
+  G.frame.resize((size_t)n * 9);
+  for (int64_t c = 0; c < n; ++c) {
+    const Vec3 p = G.pos[c];
+    // e1 along z x p, or x x p near the poles; e2 = p x e1
+    Vec3 a = std::fabs(p.z) < 0.9 ? Vec3{-p.y, p.x, 0.0} : Vec3{0.0, -p.z, p.y};
+    const double l = std::sqrt(a.x * a.x + a.y * a.y + a.z * a.z);
+    a = Vec3{a.x / l, a.y / l, a.z / l};
+    const Vec3 b{p.y * a.z - p.z * a.y, p.z * a.x - p.x * a.z, p.x * a.y - p.y * a.x};
+    const double f[9] = {a.x, a.y, a.z, b.x, b.y, b.z, p.x, p.y, p.z};
+    std::copy(f, f + 9, &G.frame[(size_t)c * 9]);
+  }
+  G.div_t.resize((size_t)n * 14);
+  G.grad_t.resize((size_t)n * 12);
+  G.dd_t.resize((size_t)n * kRing2 * 2);
+  // the two tangent components (basis of column y) of a coefficient vector
+  auto tangent = [&](const double *v, int64_t y, double *out) {
+    const double *f = &G.frame[(size_t)y * 9];
+    out[0] = v[0] * f[0] + v[1] * f[1] + v[2] * f[2];
+    out[1] = v[0] * f[3] + v[1] * f[4] + v[2] * f[5];
+  };
+  for (int64_t c = 0; c < n; ++c) {
+    for (int j = 0; j < 7; ++j) {
+      const double *cj = &G.div_coef[(size_t)c * 21 + 3 * j];
+      const int32_t m = j ? G.nbr[(size_t)c * 6 + j - 1] : (int32_t)c;
+      tangent(cj, m < 0 ? c : m, &G.div_t[(size_t)c * 14 + 2 * j]);
+      if (j) tangent(cj, c, &G.grad_t[(size_t)c * 12 + 2 * (j - 1)]);
+    }
+    for (int m = 0; m < kRing2; ++m)
+      tangent(&G.dd_w[((size_t)c * kRing2 + m) * 3], c, &G.dd_t[((size_t)c * kRing2 + m) * 2]);
+  }
   return THOR_OK;
 }
 

@@ -31,6 +31,14 @@ struct Grid {
   std::vector<double> lap_coef;  // [n][6]
   std::vector<int32_t> dd_idx;   // [n][18] two-ring columns, -1 pad
   std::vector<double> dd_w;      // [n][18][3] lap(grad .) weights
+  // tangent basis of every column (e1, e2, then the cell point) and the
+  // coefficients contracted with it: the divergence with the basis of the
+  // column the vector sits in, gradient and damping with that of the column
+  // they act on
+  std::vector<double> frame;     // [n][9]
+  std::vector<double> div_t;     // [n][7][2]
+  std::vector<double> grad_t;    // [n][6][2]
+  std::vector<double> dd_t;      // [n][18][2]
 };
 
 int build_grid(const thor_grid_params &p, Grid &G);

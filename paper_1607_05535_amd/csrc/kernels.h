@@ -26,24 +26,32 @@ struct Fields {
   const H *dc;            // [N][21] divergence/gradient coefficient vectors
   const H *lc;            // [N][6]  Laplacian neighbour weights
   const H *rhat;          // [N][3]
+  const H *frame;         // [N][9]  tangent basis e1, e2 and rhat of the column
+  const H *dv;            // [N][14] divergence coefficients of (Ma, Mb): c_j . (e1, e2) of column j
+  const H *gt;            // [N][12] gradient coefficients in the column's own basis
   const int32_t *ddi;     // [N][18] two-ring columns (-1 pad)
-  const H *ddw;           // [N][18][3] lap(grad .) weights
+  const H *ddw;           // [N][18][2] lap(grad .) weights in the column's own basis
   const double *area;     // [N]
   const double *teq;      // [N] Newtonian T_eq; cos(lon - lon_ss) cos(lat) (hot Jupiter); sin(lat) (Held-Suarez)
 
-  // current small-step state
+  // current small-step state.  Inside a stage rho holds the deviation from
+  // rho[t] (the stage's last substep leaves the density itself) and the
+  // horizontal momentum its two tangent components (Ma, Mb); the last
+  // substep of a large step also leaves it as the Cartesian (Mx, My, Mz) that
+  // every other reader of the state uses
   double *rho, *rth, *W;  // [N][L]
   H *Mx, *My, *Mz;        // [N][L]
+  H *Ma, *Mb;             // [N][L]
   H *ps;                  // p* = p - p[t]
   // large-step copies Phi[t]
   double *rho_t, *rth_t, *W_t, *p_t;
   H *Mx_t, *My_t, *Mz_t;
   // large-step forcing (frozen over the step)
-  H *FMx, *FMy, *FMz;     // proj_h(-grad p[t]) + hyperdiffusion of momentum
+  H *FMa, *FMb;           // -grad p[t] + hyperdiffusion of momentum, tangent components
   double *FW;             // [t] vertical imbalance + hyperdiffusion of W
   H *Hrho, *Hrth;         // hyperdiffusion of rho and rho theta (horizontal stencils)
   // stage forcing
-  H *SMx, *SMy, *SMz;
+  H *SMa, *SMb;
   double *SW;
   H *thL, *Gam;           // linearisation theta and gamma p / rho theta
   // divergence damping
@@ -117,14 +125,17 @@ inline int n_blocks_h(const Consts &c, int wpb) { return n_blocks_for(c.N, c.hcp
 // after which the host swaps the two buffer sets.
 // Acoustic substeps take dtau = dt / div (div = 3 in stage 1, n otherwise);
 // first = first substep of an RK stage (restart from Phi[t], p* = 0);
-// last = final substep of the large step (the physics is applied there).
+// stage_end = its last one (phase V leaves the density, not its deviation);
+// last = final substep of the large step (phase M then also leaves the
+// Cartesian momentum; phase V applies the physics, unless the energy fixer
+// does it afterwards).
 // ev0 / ev1 (timing, may be null): events recorded by the dispatch itself
 // when the family's first kernel starts and its last kernel ends.
 template <typename H>
-void launch_hmom(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, hipStream_t s,
+void launch_hmom(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, bool last, hipStream_t s,
                  hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 template <typename H>
-void launch_vert(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, bool last,
+void launch_vert(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, bool stage_end, bool physics,
                  hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 template <typename H>
 void launch_slow(const Fields<H> &f, const Consts &c, int wpb, bool from_t, hipStream_t s,
@@ -162,7 +173,7 @@ struct Planet {
 enum class BatchOp { Large, Slow, Hmom, Vert, VertLast };
 
 // Every member of an ensemble in one launch per phase.  arg0/arg1: Slow:
-// from_t; Hmom/Vert: div, first.
+// from_t; Hmom: div, first | last << 1; Vert: div, first | stage_end << 1.
 template <typename H>
 void launch_batch(const Planet<H> *P, const int2 *tiles, int n_tiles, int wpb, int parity, BatchOp op,
                   int arg0, int arg1, hipStream_t s);

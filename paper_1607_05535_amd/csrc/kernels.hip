@@ -34,19 +34,17 @@
 
 // Wavefronts per SIMD that the phase-M kernel is compiled for, as both the
 // minimum and the maximum (register budget 512 / n): scheduled for that
-// budget the two-ring gathers keep many loads in flight per wavefront
-// (FP64: 33 us at 2 against 36 us at 3 and 43 us when the compiler is left
-// to aim for 4, at g6 L32).
+// budget the two-ring gathers keep many loads in flight per wavefront.
+#ifndef HMOM_OCC_D
 #define HMOM_OCC_D 2
+#endif
 #ifndef HMOM_OCC_F
 #define HMOM_OCC_F 4
 #endif
-// Two-ring rows of D that k_hmom loads together, FP64 and mixed.
-#ifndef HMOM_DU_D
-#define HMOM_DU_D 6
-#endif
-#ifndef HMOM_DU_F
-#define HMOM_DU_F 18
+// Two-ring rows of D that k_hmom loads together (all 18: 24.8 us against
+// 25.7 with 6 and 25.4 with 3, FP64 g6 L32).
+#ifndef HMOM_DU
+#define HMOM_DU 18
 #endif
 #ifndef HMOM_PU
 #define HMOM_PU 6
@@ -270,18 +268,23 @@ __device__ __forceinline__ void st4(float *p, int nv, const float v[kHq]) {
 // Phase M of one lane's kHq levels.  FIRST (the first substep: p* = 0, D
 // of the [t] state) and DD (divergence damping) are compile-time (0 or 1)
 // in the single-state kernel, so each form is straight-line code whose
-// gathers are unrolled (the six p* rows; the 18 two-ring D rows six at a
-// time in FP64, all together in the mixed form): the scheduler can put
-// the rows of both gathers and of M, S_M in flight together (FP64
-// unchanged, mixed 17.4 -> 15.9 us at g6 L32).  The
+// gathers are unrolled (the six p* rows, the 18 two-ring D rows): the
+// scheduler can put the rows of both gathers and of M, S_M in flight
+// together.
+// Bound by the memory system (rows from the last-level cache, and the
+// stencil weights every lane of a column reads), so the momentum and its
+// forcing are two tangent components and every weight a pair instead of a
+// Cartesian vector: 64 + 15 bytes per cell against 88 + 22.5 and 90 load
+// instructions per lane against 108; g6 L32 FP64 33.6 -> 24.8 us, mixed
+// 16.3 -> 12.6, 9 planets together 143 -> 111.  The
 // ensemble kernel passes -1 for both (runtime flags, partly unrolled
 // gathers): there the four forms measured slower (1.31 -> 1.38-1.45 ms per
 // launch over 64 planets).  Every form adds its terms in the same order (j,
 // m ascending), so all give the same bits.
 template <typename H, bool VEC, int FIRST_, int DD_>
 __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, const HLane &ln, double dtau,
-                                           int first_rt) {
-  const bool FIRST = FIRST_ < 0 ? first_rt != 0 : FIRST_ != 0;
+                                           int flags) {
+  const bool FIRST = FIRST_ < 0 ? (flags & 1) != 0 : FIRST_ != 0, last = (flags & 2) != 0;
   const bool DD = DD_ < 0 ? c.div_damp != 0 : DD_ != 0;
   const int col = ln.col, nv = ln.nv;
   const size_t idx = (size_t)col * c.S + ln.lev0;
@@ -296,109 +299,120 @@ __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, 
       ring[m] = v < 0 ? col : v;
     }
   }
-  const H *dc = f.dc + (size_t)col * 21;
   H ir[kHq];
 #pragma unroll
   for (int q = 0; q < kHq; ++q) ir[q] = (H)1 / (H)radius_c(c, ln.lev0 + q);
-  H gx[kHq], gy[kHq], gz[kHq];
+  H ga[kHq], gb[kHq];
 #pragma unroll
-  for (int q = 0; q < kHq; ++q) gx[q] = gy[q] = gz[q] = 0;
+  for (int q = 0; q < kHq; ++q) ga[q] = gb[q] = 0;
   if (!FIRST) {
     // (1/r) sum_j c_j (p*_j - p*_0)
+    const H *gt = f.gt + (size_t)col * 12;
     H s0[kHq];
     ld4<VEC>(f.ps + idx, nv, s0);
 #pragma unroll(FIRST_ < 0 ? 2 : HMOM_PU)
     for (int j = 0; j < 6; ++j) {
       H sj[kHq];
       ld4<VEC>(f.ps + (size_t)nb[j] * c.S + ln.lev0, nv, sj);
-      const H cx = dc[3 * (j + 1)], cy = dc[3 * (j + 1) + 1], cz = dc[3 * (j + 1) + 2];
+      const H ca = gt[2 * j], cb = gt[2 * j + 1];
 #pragma unroll
       for (int q = 0; q < kHq; ++q) {
         const H d = sj[q] - s0[q];
-        gx[q] += cx * d;
-        gy[q] += cy * d;
-        gz[q] += cz * d;
+        ga[q] += ca * d;
+        gb[q] += cb * d;
       }
     }
 #pragma unroll
     for (int q = 0; q < kHq; ++q) {
-      gx[q] *= ir[q];
-      gy[q] *= ir[q];
-      gz[q] *= ir[q];
+      ga[q] *= ir[q];
+      gb[q] *= ir[q];
     }
   }
-  H ddx[kHq], ddy[kHq], ddz[kHq];
+  H dda[kHq], ddb[kHq];
 #pragma unroll
-  for (int q = 0; q < kHq; ++q) ddx[q] = ddy[q] = ddz[q] = 0;
+  for (int q = 0; q < kHq; ++q) dda[q] = ddb[q] = 0;
   if (DD) {
     // -Kd lap(grad D) over the two-ring, D of the current small-step state
     const H *D = FIRST ? f.Dt : f.D;
-    const H *dw = f.ddw + (size_t)col * kRing2 * 3;
+    const H *dw = f.ddw + (size_t)col * kRing2 * 2;
     H d0[kHq];
     ld4<VEC>(D + idx, nv, d0);
-#pragma unroll(DD_ < 0 ? 6 : sizeof(H) == 8 ? HMOM_DU_D : HMOM_DU_F)
+#pragma unroll(DD_ < 0 ? 6 : HMOM_DU)
     for (int m = 0; m < kRing2; ++m) {
       H dm[kHq];
       ld4<VEC>(D + (size_t)ring[m] * c.S + ln.lev0, nv, dm);
-      const H wx = dw[3 * m], wy = dw[3 * m + 1], wz = dw[3 * m + 2];
+      const H wa = dw[2 * m], wb = dw[2 * m + 1];
 #pragma unroll
       for (int q = 0; q < kHq; ++q) {
         const H dd = dm[q] - d0[q];
-        ddx[q] += wx * dd;
-        ddy[q] += wy * dd;
-        ddz[q] += wz * dd;
+        dda[q] += wa * dd;
+        ddb[q] += wb * dd;
       }
     }
 #pragma unroll
     for (int q = 0; q < kHq; ++q) {
       const H s = (H)(-c.Kd) * ir[q] * ir[q] * ir[q];
-      ddx[q] *= s;
-      ddy[q] *= s;
-      ddz[q] *= s;
+      dda[q] *= s;
+      ddb[q] *= s;
     }
   }
-  const H *rh = f.rhat + (size_t)col * 3;
-  const H rx = rh[0], ry = rh[1], rz = rh[2];
+  const H *fr = f.frame + (size_t)col * 9;
   const H dt = (H)dtau;
-  H mx[kHq], my[kHq], mz[kHq], sx[kHq], sy[kHq], sz[kHq];
-  ld4<VEC>((FIRST ? f.Mx_t : f.Mx) + idx, nv, mx);
-  ld4<VEC>((FIRST ? f.My_t : f.My) + idx, nv, my);
-  ld4<VEC>((FIRST ? f.Mz_t : f.Mz) + idx, nv, mz);
-  ld4<VEC>(f.SMx + idx, nv, sx);
-  ld4<VEC>(f.SMy + idx, nv, sy);
-  ld4<VEC>(f.SMz + idx, nv, sz);
+  H ma[kHq], mb[kHq], sa[kHq], sb[kHq];
+  if (FIRST) {
+    H mx[kHq], my[kHq], mz[kHq];
+    ld4<VEC>(f.Mx_t + idx, nv, mx);
+    ld4<VEC>(f.My_t + idx, nv, my);
+    ld4<VEC>(f.Mz_t + idx, nv, mz);
+#pragma unroll
+    for (int q = 0; q < kHq; ++q) {
+      ma[q] = mx[q] * fr[0] + my[q] * fr[1] + mz[q] * fr[2];
+      mb[q] = mx[q] * fr[3] + my[q] * fr[4] + mz[q] * fr[5];
+    }
+  } else {
+    ld4<VEC>(f.Ma + idx, nv, ma);
+    ld4<VEC>(f.Mb + idx, nv, mb);
+  }
+  ld4<VEC>(f.SMa + idx, nv, sa);
+  ld4<VEC>(f.SMb + idx, nv, sb);
 #pragma unroll
   for (int q = 0; q < kHq; ++q) {
-    const H ax = mx[q] + dt * (-gx[q] + sx[q] + ddx[q]);
-    const H ay = my[q] + dt * (-gy[q] + sy[q] + ddy[q]);
-    const H az = mz[q] + dt * (-gz[q] + sz[q] + ddz[q]);
-    const H mr = ax * rx + ay * ry + az * rz;
-    mx[q] = ax - mr * rx;
-    my[q] = ay - mr * ry;
-    mz[q] = az - mr * rz;
+    ma[q] += dt * (-ga[q] + sa[q] + dda[q]);
+    mb[q] += dt * (-gb[q] + sb[q] + ddb[q]);
   }
-  st4<VEC>(f.Mx + idx, nv, mx);
-  st4<VEC>(f.My + idx, nv, my);
-  st4<VEC>(f.Mz + idx, nv, mz);
+  st4<VEC>(f.Ma + idx, nv, ma);
+  st4<VEC>(f.Mb + idx, nv, mb);
+  if (last) {
+    H mx[kHq], my[kHq], mz[kHq];
+#pragma unroll
+    for (int q = 0; q < kHq; ++q) {
+      mx[q] = ma[q] * fr[0] + mb[q] * fr[3];
+      my[q] = ma[q] * fr[1] + mb[q] * fr[4];
+      mz[q] = ma[q] * fr[2] + mb[q] * fr[5];
+    }
+    st4<VEC>(f.Mx + idx, nv, mx);
+    st4<VEC>(f.My + idx, nv, my);
+    st4<VEC>(f.Mz + idx, nv, mz);
+  }
 }
 
 template <typename H, bool FORMS>
 __device__ __forceinline__ void b_hmom(const Fields<H> &f, const Consts &c, const HLane &ln, double dtau,
-                                       int first) {
+                                       int flags) {
   if (!ln.store) return;
   // rows of stride S: whole groups of kHq
   if (!FORMS) {
-    hmom_cells<H, true, -1, -1>(f, c, ln, dtau, first);
-  } else if (first) {
+    hmom_cells<H, true, -1, -1>(f, c, ln, dtau, flags);
+  } else if (flags & 1) {
     if (c.div_damp)
-      hmom_cells<H, true, 1, 1>(f, c, ln, dtau, first);
+      hmom_cells<H, true, 1, 1>(f, c, ln, dtau, flags);
     else
-      hmom_cells<H, true, 1, 0>(f, c, ln, dtau, first);
+      hmom_cells<H, true, 1, 0>(f, c, ln, dtau, flags);
   } else {
     if (c.div_damp)
-      hmom_cells<H, true, 0, 1>(f, c, ln, dtau, first);
+      hmom_cells<H, true, 0, 1>(f, c, ln, dtau, flags);
     else
-      hmom_cells<H, true, 0, 0>(f, c, ln, dtau, first);
+      hmom_cells<H, true, 0, 0>(f, c, ln, dtau, flags);
   }
 }
 
@@ -460,24 +474,24 @@ __device__ __forceinline__ double physics_p(const Consts &c, const double *teq, 
 // W; pressure from the nonlinear equation of state (Eq. theta_to_p).
 // ---------------------------------------------------------------------------
 template <typename H, bool LAST, int ORD = 1>
-__device__ __forceinline__ void b_vert(const Fields<H> &f, const Consts &c, const Lane &ln, double dtau, int first) {
+__device__ __forceinline__ void b_vert(const Fields<H> &f, const Consts &c, const Lane &ln, double dtau, int flags) {
+  const bool first = (flags & 1) != 0, end = (flags & 2) != 0;
   const int L = c.L, lev = ln.lev, col = ln.col;
   const size_t idx = (size_t)col * c.S + lev;
   int nb[6];
   load_nbr(f.nbr, col, nb);
-  const H *dc = f.dc + (size_t)col * 21;
+  const H *dv = f.dv + (size_t)col * 14;
 
   // horizontal divergences of M and theta_L M
   H drho, dth;
   {
-    H mx = f.Mx[idx], my = f.My[idx], mz = f.Mz[idx];
-    H t = dc[0] * mx + dc[1] * my + dc[2] * mz;
+    H t = dv[0] * f.Ma[idx] + dv[1] * f.Mb[idx];
     drho = t;
     dth = f.thL[idx] * t;
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
       size_t nj = (size_t)nb[j] * c.S + lev;
-      H u = dc[3 * (j + 1)] * f.Mx[nj] + dc[3 * (j + 1) + 1] * f.My[nj] + dc[3 * (j + 1) + 2] * f.Mz[nj];
+      H u = dv[2 * (j + 1)] * f.Ma[nj] + dv[2 * (j + 1) + 1] * f.Mb[nj];
       drho += u;
       dth += f.thL[nj] * u;
     }
@@ -486,10 +500,10 @@ __device__ __forceinline__ void b_vert(const Fields<H> &f, const Consts &c, cons
     dth *= ir;
   }
 
-  const double *rho_in = first ? f.rho_t : f.rho;
   const double *rth_in = first ? f.rth_t : f.rth;
   const double *W_in = first ? f.W_t : f.W;
-  const double rho0 = rho_in[idx];
+  const double rho0 = first ? 0.0 : f.rho[idx];   // deviation from rho[t]
+  const double rt = end || c.hydrostatic ? f.rho_t[idx] : 0.0;
   const double rth0 = rth_in[idx];
   const double Wj = lev == 0 ? 0.0 : W_in[idx];
   const double ps_in = first ? 0.0 : (double)f.ps[idx];
@@ -498,10 +512,9 @@ __device__ __forceinline__ void b_vert(const Fields<H> &f, const Consts &c, cons
   const double thC = (double)f.thL[idx];
   const double Drho = (double)drho, Dth = (double)dth;
   const double Hrth = (double)f.Hrth[idx];
-  const double rho_hat = rho0 + dtau * (-Drho + (double)f.Hrho[idx]);
+  const double rhs = rho0 + dtau * (-Drho + (double)f.Hrho[idx]);   // rho-hat minus rho[t]
   const double rth_hat = rth0 + dtau * (-Dth + Hrth);
   const double phs = ps_in + dtau * gam * (-Dth + Hrth);   // p-hat minus p[t]
-  const double rhs = rho_hat - f.rho_t[idx];              // rho-hat minus rho[t]
 
   const int lm = ln.lane > 0 ? ln.lane - 1 : 0;
   const int lp = ln.lane < 63 ? ln.lane + 1 : 63;
@@ -541,7 +554,6 @@ __device__ __forceinline__ void b_vert(const Fields<H> &f, const Consts &c, cons
   // interface lev
   double d0;
   if (c.hydrostatic) {
-    const double rt = f.rho_t[idx];
     const double pt_m = shfl(pt, lm), rt_m = shfl(rt, lm);
     d0 = dtau * (-(pt - pt_m) / dz - 0.5 * c.grav * (rt_m + rt));
   } else {
@@ -577,7 +589,8 @@ __device__ __forceinline__ void b_vert(const Fields<H> &f, const Consts &c, cons
   double Wp = shfl(Wn, lp);
   if (lev == L - 1) Wp = 0.0;
 
-  const double rho_new = rho_hat - ap * Wp + am * Wn;
+  double rho_new = rhs - ap * Wp + am * Wn;
+  if (end) rho_new += rt;
   double rth_new = rth_hat - ap * thI_p * Wp + am * thI * Wn;
   double p = c.p_ref * powd(c.Rd * rth_new / c.p_ref, c.gamma);
   double hs_sigma = 0.0;
@@ -631,14 +644,14 @@ __device__ __forceinline__ Lane2 map_lane2(const Consts &c, int lb) {
 
 template <typename H, bool LAST>
 __device__ __forceinline__ void b_vert2(const Fields<H> &f, const Consts &c, const Lane2 &ln, double dtau,
-                                        int first) {
+                                        int flags) {
+  const bool first = (flags & 1) != 0, end = (flags & 2) != 0;
   const int L = c.L, col = ln.col, lev0 = ln.lev0;
   const int lm = ln.lane > 0 ? ln.lane - 1 : 0;
   const int lp = ln.lane < 63 ? ln.lane + 1 : 63;
   int nb[6];
   load_nbr(f.nbr, col, nb);
-  const H *dc = f.dc + (size_t)col * 21;
-  const double *rho_in = first ? f.rho_t : f.rho;
+  const H *dv = f.dv + (size_t)col * 14;
   const double *rth_in = first ? f.rth_t : f.rth;
   const double *W_in = first ? f.W_t : f.W;
   const double dz = c.dz;
@@ -646,7 +659,7 @@ __device__ __forceinline__ void b_vert2(const Fields<H> &f, const Consts &c, con
 
   // per level of the lane (q = 0, 1); a level past the column's top is
   // loaded from the top level and never stored
-  double Drho[2], rho_hat[2], rth_hat[2], phs[2], rhs[2], gam[2], thC[2], pt[2], rt[2], d0[2];
+  double Drho[2], rth_hat[2], phs[2], rhs[2], gam[2], thC[2], pt[2], rt[2], d0[2];
   // radial factors of cell k: g+ = r_I(k+1)^2 / (r_C^2 dz), g- = r_I(k)^2 / (r_C^2 dz)
   auto gpm = [&](int k, double &gpk, double &gmk) {
     const double rI = radius_i(c, k), rI1 = rI + c.rdz;
@@ -661,14 +674,13 @@ __device__ __forceinline__ void b_vert2(const Fields<H> &f, const Consts &c, con
     const size_t idx = (size_t)col * c.S + lev;
     H drho, dth;
     {
-      H mx = f.Mx[idx], my = f.My[idx], mz = f.Mz[idx];
-      H t = dc[0] * mx + dc[1] * my + dc[2] * mz;
+      H t = dv[0] * f.Ma[idx] + dv[1] * f.Mb[idx];
       drho = t;
       dth = f.thL[idx] * t;
 #pragma unroll
       for (int j = 0; j < 6; ++j) {
         size_t nj = (size_t)nb[j] * c.S + lev;
-        H u = dc[3 * (j + 1)] * f.Mx[nj] + dc[3 * (j + 1) + 1] * f.My[nj] + dc[3 * (j + 1) + 2] * f.Mz[nj];
+        H u = dv[2 * (j + 1)] * f.Ma[nj] + dv[2 * (j + 1) + 1] * f.Mb[nj];
         drho += u;
         dth += f.thL[nj] * u;
       }
@@ -676,7 +688,7 @@ __device__ __forceinline__ void b_vert2(const Fields<H> &f, const Consts &c, con
       drho *= ir;
       dth *= ir;
     }
-    const double rho0 = rho_in[idx];
+    const double rho0 = first ? 0.0 : f.rho[idx];   // deviation from rho[t]
     const double rth0 = rth_in[idx];
     const double Wj = lev == 0 ? 0.0 : W_in[idx];
     const double ps_in = first ? 0.0 : (double)f.ps[idx];
@@ -686,11 +698,10 @@ __device__ __forceinline__ void b_vert2(const Fields<H> &f, const Consts &c, con
     Drho[q] = (double)drho;
     const double Dth = (double)dth;
     const double Hrth = (double)f.Hrth[idx];
-    rho_hat[q] = rho0 + dtau * (-Drho[q] + (double)f.Hrho[idx]);
+    rhs[q] = rho0 + dtau * (-Drho[q] + (double)f.Hrho[idx]);
     rth_hat[q] = rth0 + dtau * (-Dth + Hrth);
     phs[q] = ps_in + dtau * gam[q] * (-Dth + Hrth);
-    rt[q] = f.rho_t[idx];
-    rhs[q] = rho_hat[q] - rt[q];
+    rt[q] = end || c.hydrostatic ? f.rho_t[idx] : 0.0;
     d0[q] = c.hydrostatic ? 0.0 : Wj + dtau * f.SW[idx];
   }
   // values of level lev0 - 1 (the lane below's second level)
@@ -775,7 +786,8 @@ __device__ __forceinline__ void b_vert2(const Fields<H> &f, const Consts &c, con
     double gpq, gmq;
     gpm(min(lev0 + q, L - 1), gpq, gmq);
     const double ap = dtau * gpq, am = dtau * gmq;
-    rho_new[q] = rho_hat[q] - ap * Wp[q] + am * Wn[q];
+    rho_new[q] = rhs[q] - ap * Wp[q] + am * Wn[q];
+    if (end) rho_new[q] += rt[q];
     rth_new[q] = rth_hat[q] - ap * thIp * Wp[q] + am * thI[q] * Wn[q];
     p[q] = c.p_ref * powd(c.Rd * rth_new[q] / c.p_ref, c.gamma);
   }
@@ -845,20 +857,30 @@ __device__ __forceinline__ VLane map_vlane(const Consts &c, int lb) {
   return r;
 }
 
+//
+// Bound by the memory system: per cell 16 words in and 5 out from the
+// last-level cache, and 21 gathered rows.  The momentum is gathered as two
+// tangent components (3 rows per neighbour with theta_L, not 4; 136 bytes of
+// stencil per column, not 192), and the density is carried as its deviation
+// from rho[t] inside a stage, so that only the stage's last substep reads
+// rho[t]: g6 L32 FP64 43.3 -> 37.4 us, mixed 29.2 -> 27.6, g5 L37 FP64 16.4
+// -> 15.2.
+//
 // ANEL (the anelastic switch): the density update takes the divergence of
 // the reference-density mass flux, fC M horizontally and fI W vertically,
 // and the buoyancy terms of the tridiagonal the matching fI W; the
 // divergence-damping D keeps the plain momentum divergence.
 template <typename H, bool LAST, bool ANEL = false>
 __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, const VLane &ln, double dtau,
-                                        int first) {
+                                        int flags) {
+  const bool first = (flags & 1) != 0, end = (flags & 2) != 0;
   const int L = c.L, col = ln.col, lev0 = ln.lev0;
   const size_t idx = (size_t)col * c.S + lev0;
   const int lm = ln.lane > 0 ? ln.lane - 1 : 0;
   const int lp = ln.lane < 63 ? ln.lane + 1 : 63;
   int nb[6];
   load_nbr(f.nbr, col, nb);
-  const H *dc = f.dc + (size_t)col * 21;
+  const H *dv = f.dv + (size_t)col * 14;
 
   // radial factors g+ = r_I(k+1)^2 / (r_C^2 dz), g- = r_I(k)^2 / (r_C^2 dz)
   // and 1 / r_C of cells lev0 - 1 .. lev0 + 3 (index k - lev0 + 1)
@@ -877,16 +899,15 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
   // horizontal divergences of M and theta_L M (ANEL: and of fC M)
   H drho[kHq], dth[kHq], thl[kHq], dmass[kHq];
   {
-    H mx[kHq], my[kHq], mz[kHq], fc[kHq];
-    ld4<true>(f.Mx + idx, kHq, mx);
-    ld4<true>(f.My + idx, kHq, my);
-    ld4<true>(f.Mz + idx, kHq, mz);
+    H ma[kHq], mb[kHq], fc[kHq];
+    ld4<true>(f.Ma + idx, kHq, ma);
+    ld4<true>(f.Mb + idx, kHq, mb);
     ld4<true>(f.thL + idx, kHq, thl);
     if (ANEL) ld4<true>(f.fC + idx, kHq, fc);
-    const H c0x = dc[0], c0y = dc[1], c0z = dc[2];
+    const H c0a = dv[0], c0b = dv[1];
 #pragma unroll
     for (int q = 0; q < kHq; ++q) {
-      const H t = c0x * mx[q] + c0y * my[q] + c0z * mz[q];
+      const H t = c0a * ma[q] + c0b * mb[q];
       drho[q] = t;
       dth[q] = thl[q] * t;
       if (ANEL) dmass[q] = fc[q] * t;
@@ -894,16 +915,15 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
 #pragma unroll VERT4_UNROLL
     for (int j = 0; j < 6; ++j) {
       const size_t nj = (size_t)nb[j] * c.S + lev0;
-      H nx[kHq], ny[kHq], nz[kHq], nt[kHq], nf[kHq];
-      ld4<true>(f.Mx + nj, kHq, nx);
-      ld4<true>(f.My + nj, kHq, ny);
-      ld4<true>(f.Mz + nj, kHq, nz);
+      H na[kHq], nb_[kHq], nt[kHq], nf[kHq];
+      ld4<true>(f.Ma + nj, kHq, na);
+      ld4<true>(f.Mb + nj, kHq, nb_);
       ld4<true>(f.thL + nj, kHq, nt);
       if (ANEL) ld4<true>(f.fC + nj, kHq, nf);
-      const H cx = dc[3 * (j + 1)], cy = dc[3 * (j + 1) + 1], cz = dc[3 * (j + 1) + 2];
+      const H ca = dv[2 * (j + 1)], cb = dv[2 * (j + 1) + 1];
 #pragma unroll
       for (int q = 0; q < kHq; ++q) {
-        const H u = cx * nx[q] + cy * ny[q] + cz * nz[q];
+        const H u = ca * na[q] + cb * nb_[q];
         drho[q] += u;
         dth[q] += nt[q] * u;
         if (ANEL) dmass[q] += nf[q] * u;
@@ -919,21 +939,30 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
   }
 
   // explicit parts of density, rho theta and the deviation pressure
-  double rho_hat[kHq], rth_hat[kHq], phs[kHq], rhs[kHq], gam[kHq], thC[kHq], pt[kHq], d0[kHq];
+  // (the density as its deviation from rho[t], rhs)
+  double rth_hat[kHq], phs[kHq], rhs[kHq], gam[kHq], thC[kHq], pt[kHq], rt[kHq], d0[kHq];
   {
-    double rho0[kHq], rth0[kHq], rt[kHq];
+    double rho0[kHq], rth0[kHq];
     H gh[kHq], hrho[kHq], hrth[kHq], psh[kHq];
-    ld4<true>((first ? f.rho_t : f.rho) + idx, kHq, rho0);
     ld4<true>((first ? f.rth_t : f.rth) + idx, kHq, rth0);
     ld4<true>(f.p_t + idx, kHq, pt);
-    ld4<true>(f.rho_t + idx, kHq, rt);
+    if (end || c.hydrostatic) {
+      ld4<true>(f.rho_t + idx, kHq, rt);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kHq; ++q) rt[q] = 0.0;
+    }
     ld4<true>(f.Gam + idx, kHq, gh);
     ld4<true>(f.Hrho + idx, kHq, hrho);
     ld4<true>(f.Hrth + idx, kHq, hrth);
     if (first) {
 #pragma unroll
-      for (int q = 0; q < kHq; ++q) psh[q] = (H)0;
+      for (int q = 0; q < kHq; ++q) {
+        psh[q] = (H)0;
+        rho0[q] = 0.0;
+      }
     } else {
+      ld4<true>(f.rho + idx, kHq, rho0);
       ld4<true>(f.ps + idx, kHq, psh);
     }
     if (c.hydrostatic) {
@@ -957,10 +986,9 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
       gam[q] = (double)gh[q];
       thC[q] = (double)thl[q];
       const double Dr = (double)(ANEL ? dmass[q] : drho[q]), Dt = (double)dth[q], Hr = (double)hrth[q];
-      rho_hat[q] = rho0[q] + dtau * (-Dr + (double)hrho[q]);
+      rhs[q] = rho0[q] + dtau * (-Dr + (double)hrho[q]);
       rth_hat[q] = rth0[q] + dtau * (-Dt + Hr);
       phs[q] = (double)psh[q] + dtau * gam[q] * (-Dt + Hr);
-      rhs[q] = rho_hat[q] - rt[q];
     }
   }
 
@@ -1086,10 +1114,11 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
     const double ap = dtau * gp[q + 1], am = dtau * gm[q + 1];
     if (ANEL) {
       const double fIp = q < kHq - 1 ? fI[q + 1] : fI_up;
-      rho_new[q] = rho_hat[q] - ap * fIp * Wp[q] + am * fI[q] * Wn[q];
+      rho_new[q] = rhs[q] - ap * fIp * Wp[q] + am * fI[q] * Wn[q];
     } else {
-      rho_new[q] = rho_hat[q] - ap * Wp[q] + am * Wn[q];
+      rho_new[q] = rhs[q] - ap * Wp[q] + am * Wn[q];
     }
+    if (end) rho_new[q] += rt[q];
     rth_new[q] = rth_hat[q] - ap * thIp * Wp[q] + am * thI[q] * Wn[q];
     p[q] = c.p_ref * powd(c.Rd * rth_new[q] / c.p_ref, c.gamma);
   }
@@ -1165,24 +1194,23 @@ __device__ __forceinline__ void b_friction(const Fields<H> &f, const Consts &c, 
 // full Cartesian momentum, Coriolis, projections (Eqs. mom, proj_h, proj_r),
 // and the linearisation coefficients theta_L and gamma p / (rho theta).
 // ---------------------------------------------------------------------------
-template <typename H, bool VEC, bool SHALLOW, int ORD>
-__device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, const HLane &ln, int from_t) {
+// FROM_T: the stage state is Phi[t], whose momentum is Cartesian; else it is
+// the previous stage's, in tangent components.
+template <typename H, bool VEC, bool SHALLOW, int ORD, bool FROM_T>
+__device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, const HLane &ln) {
   const int L = c.L, col = ln.col, nv = ln.nv, lev0 = ln.lev0;
   const int lane = threadIdx.x & 63;
   const int lm = lane > 0 ? lane - 1 : 0;
   const int lp = lane < 63 ? lane + 1 : 63;
   const size_t idx = (size_t)col * c.S + lev0;
-  const double *rho = from_t ? f.rho_t : f.rho;
-  const double *rth = from_t ? f.rth_t : f.rth;
-  const double *W = from_t ? f.W_t : f.W;
-  const H *Mx = from_t ? f.Mx_t : f.Mx;
-  const H *My = from_t ? f.My_t : f.My;
-  const H *Mz = from_t ? f.Mz_t : f.Mz;
+  const double *rho = FROM_T ? f.rho_t : f.rho;
+  const double *rth = FROM_T ? f.rth_t : f.rth;
+  const double *W = FROM_T ? f.W_t : f.W;
   int nb[6];
   load_nbr(f.nbr, col, nb);
-  const H *dc = f.dc + (size_t)col * 21;
-  const H *rh = f.rhat + (size_t)col * 3;
-  const H rx = rh[0], ry = rh[1], rz = rh[2];
+  const H *dc = FROM_T ? f.dc + (size_t)col * 21 : f.dv + (size_t)col * 14;
+  const H *fr = f.frame + (size_t)col * 9;
+  const H rx = fr[6], ry = fr[7], rz = fr[8];
 
   // own column: full momentum m = M + Wbar rhat and velocity m / rho (in the
   // shallow form the horizontal momentum M and velocity M / rho, with the
@@ -1198,11 +1226,25 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
     double Wwin[10];
     if (ORD == 3) level_window(Wk, lev0, L, lm, lp, Wwin);
     ld4<VEC>(rho + idx, nv, rho0);
-    H mx0[kHq], my0[kHq], mz0[kHq];
-    ld4<VEC>(Mx + idx, nv, mx0);
-    ld4<VEC>(My + idx, nv, my0);
-    ld4<VEC>(Mz + idx, nv, mz0);
-    const H d0x = dc[0], d0y = dc[1], d0z = dc[2];
+    H mx0[kHq], my0[kHq], mz0[kHq], t0[kHq];   // t0: own-column term of the horizontal divergence of M
+    if (FROM_T) {
+      ld4<VEC>(f.Mx_t + idx, nv, mx0);
+      ld4<VEC>(f.My_t + idx, nv, my0);
+      ld4<VEC>(f.Mz_t + idx, nv, mz0);
+#pragma unroll
+      for (int q = 0; q < kHq; ++q) t0[q] = dc[0] * mx0[q] + dc[1] * my0[q] + dc[2] * mz0[q];
+    } else {
+      H ma[kHq], mb[kHq];
+      ld4<VEC>(f.Ma + idx, nv, ma);
+      ld4<VEC>(f.Mb + idx, nv, mb);
+#pragma unroll
+      for (int q = 0; q < kHq; ++q) {
+        mx0[q] = ma[q] * fr[0] + mb[q] * fr[3];
+        my0[q] = ma[q] * fr[1] + mb[q] * fr[4];
+        mz0[q] = ma[q] * fr[2] + mb[q] * fr[5];
+        t0[q] = dc[0] * ma[q] + dc[1] * mb[q];
+      }
+    }
 #pragma unroll
     for (int q = 0; q < kHq; ++q) {
       const double up = lev0 + q == L - 1 ? 0.0 : (q + 1 < kHq ? Wk[q + 1] : Wn);
@@ -1221,7 +1263,7 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
       vy0[q] = fy[q] * irho0;
       vz0[q] = fz[q] * irho0;
       // horizontal flux divergence of v_q M: own-column term
-      const H t = d0x * mx0[q] + d0y * my0[q] + d0z * mz0[q];
+      const H t = t0[q];
       Ax[q] = vx0[q] * t;
       Ay[q] = vy0[q] * t;
       Az[q] = vz0[q] * t;
@@ -1242,17 +1284,35 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
     double wwin[10];
     if (ORD == 3) level_window(wn, lev0, L, lm, lp, wwin);
     ld4<VEC>(rho + nj, nv, rj);
-    ld4<VEC>(Mx + nj, nv, mxj);
-    ld4<VEC>(My + nj, nv, myj);
-    ld4<VEC>(Mz + nj, nv, mzj);
-    const H *rn = f.rhat + (size_t)nb[j] * 3;
-    const H rnx = rn[0], rny = rn[1], rnz = rn[2];
-    const H cx = dc[3 * (j + 1)], cy = dc[3 * (j + 1) + 1], cz = dc[3 * (j + 1) + 2];
+    const H *fn = f.frame + (size_t)nb[j] * 9;
+    const H rnx = fn[6], rny = fn[7], rnz = fn[8];
+    H tj[kHq];
+    if (FROM_T) {
+      ld4<VEC>(f.Mx_t + nj, nv, mxj);
+      ld4<VEC>(f.My_t + nj, nv, myj);
+      ld4<VEC>(f.Mz_t + nj, nv, mzj);
+      const H cx = dc[3 * (j + 1)], cy = dc[3 * (j + 1) + 1], cz = dc[3 * (j + 1) + 2];
+#pragma unroll
+      for (int q = 0; q < kHq; ++q) tj[q] = cx * mxj[q] + cy * myj[q] + cz * mzj[q];
+    } else {
+      H ma[kHq], mb[kHq];
+      ld4<VEC>(f.Ma + nj, nv, ma);
+      ld4<VEC>(f.Mb + nj, nv, mb);
+      const H ca = dc[2 * (j + 1)], cb = dc[2 * (j + 1) + 1];
+      const H ax = fn[0], ay = fn[1], az = fn[2], bx = fn[3], by = fn[4], bz = fn[5];
+#pragma unroll
+      for (int q = 0; q < kHq; ++q) {
+        mxj[q] = ma[q] * ax + mb[q] * bx;
+        myj[q] = ma[q] * ay + mb[q] * by;
+        mzj[q] = ma[q] * az + mb[q] * bz;
+        tj[q] = ca * ma[q] + cb * mb[q];
+      }
+    }
 #pragma unroll
     for (int q = 0; q < kHq; ++q) {
       const double up = lev0 + q == L - 1 ? 0.0 : (q + 1 < kHq ? wn[q + 1] : wnn);
       const H wb = ORD == 3 ? (H)cubic_i2c(wwin + q + 1, lev0 + q, L) : (H)(0.5 * (wn[q] + up));
-      const H t = (cx * mxj[q] + cy * myj[q] + cz * mzj[q]) / (H)rj[q];
+      const H t = tj[q] / (H)rj[q];
       if (SHALLOW) {
         Ax[q] += mxj[q] * t;
         Ay[q] += myj[q] * t;
@@ -1321,16 +1381,12 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
       Az[q] += (Fz1 - Fz[q]) * s;
       if (SHALLOW) {
         // traditional approximation: 2 Omega sin(lat) rhat x M, horizontal;
-        // the horizontal equations take the projection of A here and the
+        // the horizontal equations take the tangent components of A and the
         // vertical one the scalar advection of w
         const H fc = om2 * rz;
         Ax[q] += fc * (ry * fz[q] - rz * fy[q]);
         Ay[q] += fc * (rz * fx[q] - rx * fz[q]);
         Az[q] += fc * (rx * fy[q] - ry * fx[q]);
-        const H ah = Ax[q] * rx + Ay[q] * ry + Az[q] * rz;
-        Ax[q] -= ah * rx;
-        Ay[q] -= ah * ry;
-        Az[q] -= ah * rz;
         H Fr1 = q + 1 < kHq ? Fr[q + 1] : nr;
         if (lev == L - 1) Fr1 = 0;
         acr[q] = Ar[q] * irc + (Fr1 - Fr[q]) * s;
@@ -1346,48 +1402,39 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
   H aw[10];
   if (ORD == 3) level_window(acr, lev0, L, lm, lp, aw);
   if (!ln.store) return;
-  H smx[kHq], smy[kHq], smz[kHq], thl[kHq], gam[kHq];
+  H sma[kHq], smb[kHq], thl[kHq], gam[kHq];
   double sw[kHq], fw[kHq], rth0[kHq], pt[kHq];
   H ps[kHq];
-  ld4<VEC>(f.FMx + idx, nv, smx);
-  ld4<VEC>(f.FMy + idx, nv, smy);
-  ld4<VEC>(f.FMz + idx, nv, smz);
+  ld4<VEC>(f.FMa + idx, nv, sma);
+  ld4<VEC>(f.FMb + idx, nv, smb);
   ld4<VEC>(f.FW + idx, nv, fw);
   ld4<VEC>(rth + idx, nv, rth0);
   ld4<VEC>(f.p_t + idx, nv, pt);
-  if (!from_t) ld4<VEC>(f.ps + idx, nv, ps);
+  if (!FROM_T) ld4<VEC>(f.ps + idx, nv, ps);
 #pragma unroll
   for (int q = 0; q < kHq; ++q) {
-    if (SHALLOW) {   // A is horizontal already
-      smx[q] -= Ax[q];
-      smy[q] -= Ay[q];
-      smz[q] -= Az[q];
-    } else {
-      smx[q] -= Ax[q] - acr[q] * rx;
-      smy[q] -= Ay[q] - acr[q] * ry;
-      smz[q] -= Az[q] - acr[q] * rz;
-    }
+    sma[q] -= Ax[q] * fr[0] + Ay[q] * fr[1] + Az[q] * fr[2];
+    smb[q] -= Ax[q] * fr[3] + Ay[q] * fr[4] + Az[q] * fr[5];
     const H am = q ? acr[q - 1] : acr_m;
     if (ORD == 3)
       sw[q] = lev0 + q == 0 ? 0.0 : fw[q] - (double)cubic_c2i(aw + q, lev0 + q, L);
     else
       sw[q] = lev0 + q == 0 ? 0.0 : fw[q] - 0.5 * ((double)am + (double)acr[q]);
     // linearisation coefficients
-    const double p0 = pt[q] + (from_t ? 0.0 : (double)ps[q]);
+    const double p0 = pt[q] + (FROM_T ? 0.0 : (double)ps[q]);
     thl[q] = (H)(rth0[q] / rho0[q]);
     gam[q] = (H)(c.gamma * p0 / rth0[q]);
   }
-  st4<VEC>(f.SMx + idx, nv, smx);
-  st4<VEC>(f.SMy + idx, nv, smy);
-  st4<VEC>(f.SMz + idx, nv, smz);
+  st4<VEC>(f.SMa + idx, nv, sma);
+  st4<VEC>(f.SMb + idx, nv, smb);
   st4<VEC>(f.SW + idx, nv, sw);
   st4<VEC>(f.thL + idx, nv, thl);
   st4<VEC>(f.Gam + idx, nv, gam);
 }
 
-template <typename H, bool SHALLOW = false, int ORD = 1>
-__device__ __forceinline__ void b_slow(const Fields<H> &f, const Consts &c, const HLane &ln, int from_t) {
-  slow_cells<H, true, SHALLOW, ORD>(f, c, ln, from_t);   // rows of stride S: whole groups of kHq
+template <typename H, bool FROM_T, bool SHALLOW = false, int ORD = 1>
+__device__ __forceinline__ void b_slow(const Fields<H> &f, const Consts &c, const HLane &ln) {
+  slow_cells<H, true, SHALLOW, ORD, FROM_T>(f, c, ln);   // rows of stride S: whole groups of kHq
 }
 
 // ---------------------------------------------------------------------------
@@ -1645,40 +1692,36 @@ __device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c
     st4<VEC>(f.Hrho + idx, nv, h);
   }
   {
-    const H *rh = f.rhat + (size_t)col * 3;
-    const double rx = rh[0], ry = rh[1], rz = rh[2];
-    // -grad p[t] (in double: full pressure), projected, in the horizontal
-    // precision; the momentum hyperdiffusion is added to it below
-    H fx[kHq], fy[kHq], fz[kHq];
+    // -grad p[t] (in double: full pressure) in the column's tangent basis,
+    // in the horizontal precision; the momentum hyperdiffusion is added to
+    // it below
+    H fa[kHq], fb[kHq];
     {
-      const H *dch = f.dc + (size_t)col * 21;
-      double p[kHq], gx[kHq], gy[kHq], gz[kHq];
+      const H *gt = f.gt + (size_t)col * 12;
+      double p[kHq], ga[kHq], gb[kHq];
       ld4<VEC>(f.p_t + idx, nv, p);
 #pragma unroll
-      for (int q = 0; q < kHq; ++q) gx[q] = gy[q] = gz[q] = 0;
+      for (int q = 0; q < kHq; ++q) ga[q] = gb[q] = 0;
 #pragma unroll 2
       for (int j = 0; j < 6; ++j) {
         double pj[kHq];
         ld4<VEC>(f.p_t + (size_t)nb[j] * c.S + lev0, nv, pj);
-        const double cx = dch[3 * (j + 1)], cy = dch[3 * (j + 1) + 1], cz = dch[3 * (j + 1) + 2];
+        const double ca = gt[2 * j], cb = gt[2 * j + 1];
 #pragma unroll
         for (int q = 0; q < kHq; ++q) {
           const double dp = pj[q] - p[q];
-          gx[q] += cx * dp;
-          gy[q] += cy * dp;
-          gz[q] += cz * dp;
+          ga[q] += ca * dp;
+          gb[q] += cb * dp;
         }
       }
 #pragma unroll
       for (int q = 0; q < kHq; ++q) {
         const double irc = 1.0 / radius_c(c, lev0 + q);
-        const double x = gx[q] * irc, y = gy[q] * irc, z = gz[q] * irc;
-        const double gr = x * rx + y * ry + z * rz;
-        fx[q] = (H)(-(x - gr * rx));
-        fy[q] = (H)(-(y - gr * ry));
-        fz[q] = (H)(-(z - gr * rz));
+        fa[q] = (H)(-(ga[q] * irc));
+        fb[q] = (H)(-(gb[q] * irc));
       }
     }
+    const H *fr = f.frame + (size_t)col * 9;
     double hx[kHq], hy[kHq], hz[kHq];
     lap4<VEC>(f.Xvx, nb, lch, c.S, lev0, nv, idx, hx);
     lap4<VEC>(f.Xvy, nb, lch, c.S, lev0, nv, idx, hy);
@@ -1686,14 +1729,11 @@ __device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c
 #pragma unroll
     for (int q = 0; q < kHq; ++q) {
       const double x = -irc2[q] * hx[q], y = -irc2[q] * hy[q], z = -irc2[q] * hz[q];
-      const double hr = x * rx + y * ry + z * rz;
-      fx[q] = (H)((double)fx[q] + (x - hr * rx));
-      fy[q] = (H)((double)fy[q] + (y - hr * ry));
-      fz[q] = (H)((double)fz[q] + (z - hr * rz));
+      fa[q] = (H)((double)fa[q] + (x * fr[0] + y * fr[1] + z * fr[2]));
+      fb[q] = (H)((double)fb[q] + (x * fr[3] + y * fr[4] + z * fr[5]));
     }
-    st4<VEC>(f.FMx + idx, nv, fx);
-    st4<VEC>(f.FMy + idx, nv, fy);
-    st4<VEC>(f.FMz + idx, nv, fz);
+    st4<VEC>(f.FMa + idx, nv, fa);
+    st4<VEC>(f.FMb + idx, nv, fb);
   }
   {
     // the [t] vertical imbalance at interface lev plus the hyperdiffusion
@@ -1949,7 +1989,6 @@ __device__ __forceinline__ void b_import(const Fields<H> &f, const Consts &c, co
     b_##NAME(f, c, MAP(c, t.y) ARGS);                                                \
   }
 #define COMMA ,
-THOR_KERNEL(slow, sizeof(H) == 8 ? 2 : 4, map_hlane, COMMA int from_t, COMMA from_t)
 THOR_KERNEL(large0, 4, map_hlane, , )
 THOR_KERNEL(anel, 8, map_hlane, , )
 THOR_KERNEL(large1, sizeof(H) == 8 ? LARGE1_OCC_D : LARGE1_OCC_F, map_hlane, , )
@@ -1960,58 +1999,72 @@ THOR_KERNEL(friction, 8, map_hlane, , )
 template <typename H>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F, sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F)))
-void k_hmom(Fields<H> f, Consts c, int div, int first) {
-  b_hmom<H, true>(f, c, map_hlane(c, xcd_block()), c.dt / div, first);
+void k_hmom(Fields<H> f, Consts c, int div, int flags) {
+  b_hmom<H, true>(f, c, map_hlane(c, xcd_block()), c.dt / div, flags);
 }
 template <typename H>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F, sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F)))
-void kb_hmom(const Planet<H> *P, const int2 *tiles, int parity, int div, int first) {
+void kb_hmom(const Planet<H> *P, const int2 *tiles, int parity, int div, int flags) {
   const int2 t = tiles[xcd_block()];
   if (t.x < 0) return;
   const Fields<H> &f = P[t.x].f[parity];
   const Consts &c = P[t.x].c;
-  b_hmom<H, false>(f, c, map_hlane(c, t.y), c.dt / div, first);
+  b_hmom<H, false>(f, c, map_hlane(c, t.y), c.dt / div, flags);
+}
+template <typename H, bool FROM_T>
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? 2 : 4)))
+void k_slow(Fields<H> f, Consts c) {
+  b_slow<H, FROM_T>(f, c, map_hlane(c, xcd_block()));
+}
+template <typename H, bool FROM_T>
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? 2 : 4)))
+void kb_slow(const Planet<H> *P, const int2 *tiles, int parity) {
+  const int2 t = tiles[xcd_block()];
+  if (t.x < 0) return;
+  const Fields<H> &f = P[t.x].f[parity];
+  const Consts &c = P[t.x].c;
+  b_slow<H, FROM_T>(f, c, map_hlane(c, t.y));
 }
 // slow terms of the shallow-atmosphere form and of the cubic vertical
 // interpolation (single states only)
-template <typename H, bool SHALLOW, int ORD>
+template <typename H, bool FROM_T, bool SHALLOW, int ORD>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? (SHALLOW && ORD == 3 ? 1 : 2) : (SHALLOW && ORD == 3 ? 2 : 3))))
-void k_slow_var(Fields<H> f, Consts c, int from_t) {
-  b_slow<H, SHALLOW, ORD>(f, c, map_hlane(c, xcd_block()), from_t);
+void k_slow_var(Fields<H> f, Consts c) {
+  b_slow<H, FROM_T, SHALLOW, ORD>(f, c, map_hlane(c, xcd_block()));
 }
 template <typename H, bool LAST>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? 4 : (LAST ? 5 : 6))))
-void k_vert(Fields<H> f, Consts c, int div, int first) {
-  b_vert<H, LAST>(f, c, map_lane(c, xcd_block()), c.dt / div, first);
+void k_vert(Fields<H> f, Consts c, int div, int flags) {
+  b_vert<H, LAST>(f, c, map_lane(c, xcd_block()), c.dt / div, flags);
 }
 // phase V with two levels per lane (single states, 32 < L <= 64)
 template <typename H, bool LAST>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? 2 : 3)))
-void k_vert2(Fields<H> f, Consts c, int div, int first) {
-  b_vert2<H, LAST>(f, c, map_lane2(c, xcd_block()), c.dt / div, first);
+void k_vert2(Fields<H> f, Consts c, int div, int flags) {
+  b_vert2<H, LAST>(f, c, map_lane2(c, xcd_block()), c.dt / div, flags);
 }
 // phase V on the gather mapping (kHq levels per lane)
 template <typename H, bool LAST, bool ANEL = false>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(VERT4_OCC)))
-void k_vert4(Fields<H> f, Consts c, int div, int first) {
-  b_vert4<H, LAST, ANEL>(f, c, map_vlane(c, xcd_block()), c.dt / div, first);
+void k_vert4(Fields<H> f, Consts c, int div, int flags) {
+  b_vert4<H, LAST, ANEL>(f, c, map_vlane(c, xcd_block()), c.dt / div, flags);
 }
 // phase V with the cubic interface theta (single states only)
 template <typename H, bool LAST>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? 3 : 4)))
-void k_vert3(Fields<H> f, Consts c, int div, int first) {
-  b_vert<H, LAST, 3>(f, c, map_lane(c, xcd_block()), c.dt / div, first);
+void k_vert3(Fields<H> f, Consts c, int div, int flags) {
+  b_vert<H, LAST, 3>(f, c, map_lane(c, xcd_block()), c.dt / div, flags);
 }
 template <typename H, bool LAST>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(VERT4_OCC)))
-void kb_vert(const Planet<H> *P, const int2 *tiles, int parity, int div, int first) {
+void kb_vert(const Planet<H> *P, const int2 *tiles, int parity, int div, int flags) {
   const int2 t = tiles[xcd_block()];
   if (t.x < 0) return;
   const Fields<H> &f = P[t.x].f[parity];
   const Consts &c = P[t.x].c;
-  b_vert4<H, LAST>(f, c, map_vlane(c, t.y), c.dt / div, first);
+  b_vert4<H, LAST>(f, c, map_vlane(c, t.y), c.dt / div, flags);
 }
 #undef COMMA
 #undef THOR_KERNEL
@@ -2029,54 +2082,60 @@ void dispatch(K kernel, dim3 g, dim3 b, hipStream_t s, hipEvent_t e0, hipEvent_t
 }
 
 template <typename H>
-void launch_hmom(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, hipStream_t s, hipEvent_t ev0,
-                 hipEvent_t ev1) {
-  dispatch(k_hmom<H>, dim3(n_blocks_h(c, wpb)), dim3(64 * wpb), s, ev0, ev1, f, c, div, (int)first);
+void launch_hmom(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, bool last, hipStream_t s,
+                 hipEvent_t ev0, hipEvent_t ev1) {
+  dispatch(k_hmom<H>, dim3(n_blocks_h(c, wpb)), dim3(64 * wpb), s, ev0, ev1, f, c, div, (int)first | (int)last << 1);
 }
 template <typename H>
-void launch_vert(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, bool last, hipStream_t s,
-                 hipEvent_t ev0, hipEvent_t ev1) {
+void launch_vert(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, bool stage_end, bool physics,
+                 hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  const int flags = (int)first | (int)stage_end << 1;
   const dim3 g(c.vnl == 4 ? n_blocks_h(c, wpb) : c.vnl == 2 ? n_blocks_for(c.N, c.vcpw, wpb) : n_blocks(c, wpb)),
       b(64 * wpb);
-  const bool fr = last && c.forcing == THOR_FORCING_HELD_SUAREZ;
+  const bool fr = physics && c.forcing == THOR_FORCING_HELD_SUAREZ;
   hipEvent_t e1 = fr ? nullptr : ev1;   // with the friction kernel, the family ends with it
-  if (last) {
+  if (physics) {
     if (c.anelastic)
-      dispatch(k_vert4<H, true, true>, g, b, s, ev0, e1, f, c, div, (int)first);
+      dispatch(k_vert4<H, true, true>, g, b, s, ev0, e1, f, c, div, flags);
     else if (c.vnl == 4)
-      dispatch(k_vert4<H, true>, g, b, s, ev0, e1, f, c, div, (int)first);
+      dispatch(k_vert4<H, true>, g, b, s, ev0, e1, f, c, div, flags);
     else if (c.vnl == 2)
-      dispatch(k_vert2<H, true>, g, b, s, ev0, e1, f, c, div, (int)first);
+      dispatch(k_vert2<H, true>, g, b, s, ev0, e1, f, c, div, flags);
     else if (c.vorder == 3)
-      dispatch(k_vert3<H, true>, g, b, s, ev0, e1, f, c, div, (int)first);
+      dispatch(k_vert3<H, true>, g, b, s, ev0, e1, f, c, div, flags);
     else
-      dispatch(k_vert<H, true>, g, b, s, ev0, e1, f, c, div, (int)first);
+      dispatch(k_vert<H, true>, g, b, s, ev0, e1, f, c, div, flags);
     if (fr) dispatch(k_friction<H>, dim3(n_blocks_h(c, 4)), dim3(256), s, nullptr, ev1, f, c);
   } else {
     if (c.anelastic)
-      dispatch(k_vert4<H, false, true>, g, b, s, ev0, ev1, f, c, div, (int)first);
+      dispatch(k_vert4<H, false, true>, g, b, s, ev0, ev1, f, c, div, flags);
     else if (c.vnl == 4)
-      dispatch(k_vert4<H, false>, g, b, s, ev0, ev1, f, c, div, (int)first);
+      dispatch(k_vert4<H, false>, g, b, s, ev0, ev1, f, c, div, flags);
     else if (c.vnl == 2)
-      dispatch(k_vert2<H, false>, g, b, s, ev0, ev1, f, c, div, (int)first);
+      dispatch(k_vert2<H, false>, g, b, s, ev0, ev1, f, c, div, flags);
     else if (c.vorder == 3)
-      dispatch(k_vert3<H, false>, g, b, s, ev0, ev1, f, c, div, (int)first);
+      dispatch(k_vert3<H, false>, g, b, s, ev0, ev1, f, c, div, flags);
     else
-      dispatch(k_vert<H, false>, g, b, s, ev0, ev1, f, c, div, (int)first);
+      dispatch(k_vert<H, false>, g, b, s, ev0, ev1, f, c, div, flags);
   }
+}
+template <typename H, bool FROM_T>
+void dispatch_slow(const Fields<H> &f, const Consts &c, dim3 g, dim3 b, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  if (c.vorder == 3 && c.shallow)
+    dispatch(k_slow_var<H, FROM_T, true, 3>, g, b, s, ev0, ev1, f, c);
+  else if (c.vorder == 3)
+    dispatch(k_slow_var<H, FROM_T, false, 3>, g, b, s, ev0, ev1, f, c);
+  else if (c.shallow)
+    dispatch(k_slow_var<H, FROM_T, true, 1>, g, b, s, ev0, ev1, f, c);
+  else
+    dispatch(k_slow<H, FROM_T>, g, b, s, ev0, ev1, f, c);
 }
 template <typename H>
 void launch_slow(const Fields<H> &f, const Consts &c, int wpb, bool from_t, hipStream_t s, hipEvent_t ev0,
                  hipEvent_t ev1) {
   const dim3 g(n_blocks_h(c, wpb)), b(64 * wpb);
-  if (c.vorder == 3 && c.shallow)
-    dispatch(k_slow_var<H, true, 3>, g, b, s, ev0, ev1, f, c, (int)from_t);
-  else if (c.vorder == 3)
-    dispatch(k_slow_var<H, false, 3>, g, b, s, ev0, ev1, f, c, (int)from_t);
-  else if (c.shallow)
-    dispatch(k_slow_var<H, true, 1>, g, b, s, ev0, ev1, f, c, (int)from_t);
-  else
-    dispatch(k_slow<H>, g, b, s, ev0, ev1, f, c, (int)from_t);
+  if (from_t) dispatch_slow<H, true>(f, c, g, b, s, ev0, ev1);
+  else dispatch_slow<H, false>(f, c, g, b, s, ev0, ev1);
 }
 template <typename H>
 void launch_large(const Fields<H> &f, const Consts &c, int wpb, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
@@ -2128,7 +2187,8 @@ void launch_batch(const Planet<H> *P, const int2 *tiles, int n_tiles, int wpb, i
       hipLaunchKernelGGL(kb_large2<H>, g, b, 0, s, P, tiles, parity);
       break;
     case BatchOp::Slow:
-      hipLaunchKernelGGL(kb_slow<H>, g, b, 0, s, P, tiles, parity, arg0);
+      if (arg0) hipLaunchKernelGGL((kb_slow<H, true>), g, b, 0, s, P, tiles, parity);
+      else hipLaunchKernelGGL((kb_slow<H, false>), g, b, 0, s, P, tiles, parity);
       break;
     case BatchOp::Hmom:
       hipLaunchKernelGGL(kb_hmom<H>, g, b, 0, s, P, tiles, parity, arg0, arg1);
@@ -2145,9 +2205,9 @@ void launch_batch(const Planet<H> *P, const int2 *tiles, int n_tiles, int wpb, i
 }
 
 #define THOR_INSTANTIATE(H)                                                                          \
-  template void launch_hmom<H>(const Fields<H> &, const Consts &, int, int, bool, hipStream_t, hipEvent_t,   \
+  template void launch_hmom<H>(const Fields<H> &, const Consts &, int, int, bool, bool, hipStream_t, hipEvent_t, \
                                hipEvent_t);                                                          \
-  template void launch_vert<H>(const Fields<H> &, const Consts &, int, int, bool, bool, hipStream_t,        \
+  template void launch_vert<H>(const Fields<H> &, const Consts &, int, int, bool, bool, bool, hipStream_t,  \
                                hipEvent_t, hipEvent_t);                                              \
   template void launch_slow<H>(const Fields<H> &, const Consts &, int, bool, hipStream_t, hipEvent_t,       \
                                hipEvent_t);                                                          \

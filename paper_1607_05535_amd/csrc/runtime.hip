@@ -60,8 +60,11 @@ void carve(Carver &cv, Fields<H> &f, size_t N, size_t L, bool anelastic) {
   f.dc = cv.take<H>(N * 21);
   f.lc = cv.take<H>(N * 6);
   f.rhat = cv.take<H>(N * 3);
+  f.frame = cv.take<H>(N * 9);
+  f.dv = cv.take<H>(N * 14);
+  f.gt = cv.take<H>(N * 12);
   f.ddi = cv.take<int32_t>(N * kRing2);
-  f.ddw = cv.take<H>(N * kRing2 * 3);
+  f.ddw = cv.take<H>(N * kRing2 * 2);
   f.area = cv.take<double>(N);
   f.teq = cv.take<double>(N);
   f.rho = cv.take<double>(NL);
@@ -70,6 +73,8 @@ void carve(Carver &cv, Fields<H> &f, size_t N, size_t L, bool anelastic) {
   f.Mx = cv.take<H>(NL);
   f.My = cv.take<H>(NL);
   f.Mz = cv.take<H>(NL);
+  f.Ma = cv.take<H>(NL);
+  f.Mb = cv.take<H>(NL);
   f.ps = cv.take<H>(NL);
   f.rho_t = cv.take<double>(NL);
   f.rth_t = cv.take<double>(NL);
@@ -78,15 +83,13 @@ void carve(Carver &cv, Fields<H> &f, size_t N, size_t L, bool anelastic) {
   f.Mx_t = cv.take<H>(NL);
   f.My_t = cv.take<H>(NL);
   f.Mz_t = cv.take<H>(NL);
-  f.FMx = cv.take<H>(NL);
-  f.FMy = cv.take<H>(NL);
-  f.FMz = cv.take<H>(NL);
+  f.FMa = cv.take<H>(NL);
+  f.FMb = cv.take<H>(NL);
   f.FW = cv.take<double>(NL);
   f.Hrho = cv.take<H>(NL);
   f.Hrth = cv.take<H>(NL);
-  f.SMx = cv.take<H>(NL);
-  f.SMy = cv.take<H>(NL);
-  f.SMz = cv.take<H>(NL);
+  f.SMa = cv.take<H>(NL);
+  f.SMb = cv.take<H>(NL);
   f.SW = cv.take<double>(NL);
   f.thL = cv.take<H>(NL);
   f.Gam = cv.take<H>(NL);
@@ -206,6 +209,25 @@ size_t bytes_for(int precision, size_t N, size_t L, bool anelastic) {
   return cv.off;
 }
 
+// A host array in the horizontal precision: the array itself in FP64, a
+// converted copy in the mixed form.
+template <typename H>
+struct HostArray {
+  std::vector<H> own;
+  const H *ptr;
+  size_t n;
+  explicit HostArray(const std::vector<double> &v) : n(v.size()) {
+    if constexpr (sizeof(H) == sizeof(double)) {
+      ptr = v.data();
+    } else {
+      own.assign(v.begin(), v.end());
+      ptr = own.data();
+    }
+  }
+  const H *data() const { return ptr; }
+  size_t size() const { return n; }
+};
+
 template <typename H>
 int upload(thor_state *s, const Grid &G, const thor_planet *pl, const thor_vertical *v,
            const thor_forcing *fo, const thor_init *in, char *base, Fields<H> *fp) {
@@ -218,10 +240,8 @@ int upload(thor_state *s, const Grid &G, const thor_planet *pl, const thor_verti
   const Fields<H> &f = fp[0];
   const Consts &c = s->c;
   // geometry
-  std::vector<H> dc(G.div_coef.begin(), G.div_coef.end());
-  std::vector<H> lc(G.lap_coef.begin(), G.lap_coef.end());
+  const HostArray<H> dc(G.div_coef), lc(G.lap_coef), frame(G.frame), dv(G.div_t), gt(G.grad_t), ddw(G.dd_t);
   std::vector<H> rh(N * 3);
-  std::vector<H> ddw(G.dd_w.begin(), G.dd_w.end());
   std::vector<double> teq(N);
   for (size_t i = 0; i < N; ++i) {
     const Vec3 p = G.pos[i];
@@ -246,8 +266,8 @@ int upload(thor_state *s, const Grid &G, const thor_planet *pl, const thor_verti
   // anelastic reference column: the same isothermal column, padded to S
   std::vector<double> rref(S);
   for (size_t k = 0; k < S; ++k) rref[k] = rcol[k < L ? k : L - 1];
-  std::vector<double> rho(NL), rth(NL), zero(NL, 0.0);
-  std::vector<H> zeroH(NL, (H)0);
+  // (at rest: the momenta and p* stay the zeros of the cleared buffer)
+  std::vector<double> rho(NL), rth(NL);
   const uint64_t pbase = (uint64_t)in->planet_index << 40;
   for (size_t i = 0; i < N; ++i)
     for (size_t k = 0; k < L; ++k) {
@@ -269,17 +289,15 @@ int upload(thor_state *s, const Grid &G, const thor_planet *pl, const thor_verti
             hip_ok(hipMemcpyAsync((void *)f.dc, dc.data(), dc.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy dc") &&
             hip_ok(hipMemcpyAsync((void *)f.lc, lc.data(), lc.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy lc") &&
             hip_ok(hipMemcpyAsync((void *)f.rhat, rh.data(), rh.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy rhat") &&
+            hip_ok(hipMemcpyAsync((void *)f.frame, frame.data(), frame.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy frame") &&
+            hip_ok(hipMemcpyAsync((void *)f.dv, dv.data(), dv.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy dv") &&
+            hip_ok(hipMemcpyAsync((void *)f.gt, gt.data(), gt.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy gt") &&
             hip_ok(hipMemcpyAsync((void *)f.ddi, G.dd_idx.data(), G.dd_idx.size() * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy ddi") &&
             hip_ok(hipMemcpyAsync((void *)f.ddw, ddw.data(), ddw.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy ddw") &&
             hip_ok(hipMemcpyAsync((void *)f.area, G.area.data(), N * sizeof(double), hipMemcpyHostToDevice, st), "copy area") &&
             hip_ok(hipMemcpyAsync((void *)f.teq, teq.data(), N * sizeof(double), hipMemcpyHostToDevice, st), "copy teq") &&
             hip_ok(hipMemcpyAsync(f.rho_t, rho.data(), NL * sizeof(double), hipMemcpyHostToDevice, st), "copy rho") &&
             hip_ok(hipMemcpyAsync(f.rth_t, rth.data(), NL * sizeof(double), hipMemcpyHostToDevice, st), "copy rth") &&
-            hip_ok(hipMemcpyAsync(f.W_t, zero.data(), NL * sizeof(double), hipMemcpyHostToDevice, st), "copy W") &&
-            hip_ok(hipMemcpyAsync(f.Mx_t, zeroH.data(), NL * sizeof(H), hipMemcpyHostToDevice, st), "copy Mx") &&
-            hip_ok(hipMemcpyAsync(f.My_t, zeroH.data(), NL * sizeof(H), hipMemcpyHostToDevice, st), "copy My") &&
-            hip_ok(hipMemcpyAsync(f.Mz_t, zeroH.data(), NL * sizeof(H), hipMemcpyHostToDevice, st), "copy Mz") &&
-            hip_ok(hipMemcpyAsync(f.ps, zeroH.data(), NL * sizeof(H), hipMemcpyHostToDevice, st), "copy ps") &&
             (!f.rref || hip_ok(hipMemcpyAsync((void *)f.rref, rref.data(), S * sizeof(double),
                                               hipMemcpyHostToDevice, st), "copy rref")) &&
             hip_ok(hipStreamSynchronize(st), "init synchronize");
@@ -323,11 +341,11 @@ void enqueue_large_step(thor_state *s, const Fields<H> &f, int n, hipStream_t st
   for (int stage = 0; stage < 3; ++stage) {
     timed(s, st, "slow", [&](hipEvent_t a, hipEvent_t b) { launch_slow(f, c, it[FAM_SLOW], stage == 0, st, a, b); });
     for (int i = 0; i < ns[stage]; ++i) {
-      const bool first = i == 0, last = stage == 2 && i + 1 == ns[stage];
+      const bool first = i == 0, end = i + 1 == ns[stage], last = stage == 2 && end;
       timed(s, st, "hmom",
-            [&](hipEvent_t a, hipEvent_t b) { launch_hmom(f, c, it[FAM_HMOM], div[stage], first, st, a, b); });
+            [&](hipEvent_t a, hipEvent_t b) { launch_hmom(f, c, it[FAM_HMOM], div[stage], first, last, st, a, b); });
       timed(s, st, "vert", [&](hipEvent_t a, hipEvent_t b) {
-        launch_vert(f, c, it[FAM_VERT], div[stage], first, last && !c.energy_fixer, st, a, b);
+        launch_vert(f, c, it[FAM_VERT], div[stage], first, end, last && !c.energy_fixer, st, a, b);
       });
     }
   }
@@ -831,9 +849,9 @@ void enqueue_batch_step(thor_batch *b, int n, int parity, hipStream_t st) {
   for (int stage = 0; stage < 3; ++stage) {
     L(FAM_SLOW, BatchOp::Slow, stage == 0, 0);
     for (int i = 0; i < ns[stage]; ++i) {
-      const bool first = i == 0, last = stage == 2 && i + 1 == ns[stage];
-      L(FAM_HMOM, BatchOp::Hmom, div[stage], first);
-      L(FAM_VERT, last ? BatchOp::VertLast : BatchOp::Vert, div[stage], first);
+      const bool first = i == 0, end = i + 1 == ns[stage], last = stage == 2 && end;
+      L(FAM_HMOM, BatchOp::Hmom, div[stage], first | last << 1);
+      L(FAM_VERT, last ? BatchOp::VertLast : BatchOp::Vert, div[stage], first | end << 1);
     }
   }
 }
