@@ -54,41 +54,67 @@ inline unsigned cblocks(int N, int L) {
   return (unsigned)((waves + 3) / 4);
 }
 
-__device__ __forceinline__ void east_north(double x, double y, double z, double e[3], double n[3]) {
-  const double lam = sqrt(x * x + y * y) < 1e-12 ? 0.0 : atan2(y, x);
-  const double phi = asin(fmin(1.0, fmax(-1.0, z)));
-  e[0] = -sin(lam);
-  e[1] = cos(lam);
-  e[2] = 0.0;
-  n[0] = -sin(phi) * cos(lam);
-  n[1] = -sin(phi) * sin(lam);
-  n[2] = cos(phi);
+// kHq consecutive values of a padded state row.
+__device__ __forceinline__ void row4(const double *p, double v[kHq]) {
+  const double2 a = *reinterpret_cast<const double2 *>(p), b = *reinterpret_cast<const double2 *>(p + 2);
+  v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+}
+__device__ __forceinline__ void row4(const float *p, float v[kHq]) {
+  const float4 a = *reinterpret_cast<const float4 *>(p);
+  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
 }
 
-// (T, u, v, w, p) of every cell of the state (FP32, [f][col][lev]).
-template <typename H>
+// (T, u, v, w, p) of every cell of the state (FP32, [f][col][lev]).  A thread
+// takes kHq consecutive levels of a padded state row, so every lane works at
+// any level count and the state moves in 16-byte loads; VEC: so do the
+// outputs (n_lev a multiple of kHq, out 16-byte aligned).  Bound by memory
+// (48 bytes in and 20 out per cell): g6 L32 36 -> 17 us, g5 L37 19 -> 9 with
+// one cell per lane and the angles of every cell before.
+template <typename H, bool VEC>
 __global__ __launch_bounds__(256) void k_fields(Fields<H> f, Consts c, float *out) {
-  const CLane ln = clane(c.N, c.L);
-  const int L = c.L;
-  const size_t idx = (size_t)ln.col * c.S + ln.lev;   // state (row stride S)
-  const size_t oi = (size_t)ln.col * L + ln.lev;      // output, [f][col][lev]
-  const int lp = ln.lane < 63 ? ln.lane + 1 : 63;
-  const double W = ln.lev == 0 ? 0.0 : f.W_t[idx];
-  double W1 = __shfl(W, lp, 64);
-  if (ln.lev == L - 1) W1 = 0.0;
-  if (!ln.store) return;
-  const double rho = f.rho_t[idx];
-  const double p = c.p_ref * powd(c.Rd * f.rth_t[idx] / c.p_ref, c.gamma);
-  const H *rh = f.rhat + (size_t)ln.col * 3;
-  double e[3], n[3];
-  east_north(rh[0], rh[1], rh[2], e, n);
-  const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
+  const int L = c.L, per = c.S / kHq;
+  const int g = blockIdx.x * 256 + threadIdx.x;
+  const int col = g / per;
+  if (col >= c.N) return;
+  const int lev0 = (g - col * per) * kHq;
+  const size_t idx = (size_t)col * c.S + lev0;   // state (row stride S)
+  const size_t oi = (size_t)col * L + lev0;      // output, [f][col][lev]
+  double rho[kHq], rth[kHq], W[kHq + 1];
+  H mx[kHq], my[kHq], mz[kHq];
+  row4(f.rho_t + idx, rho);
+  row4(f.rth_t + idx, rth);
+  row4(f.W_t + idx, W);
+  row4(f.Mx_t + idx, mx);
+  row4(f.My_t + idx, my);
+  row4(f.Mz_t + idx, mz);
+  W[kHq] = lev0 + kHq < L ? f.W_t[idx + kHq] : 0.0;
+  if (lev0 == 0) W[0] = 0.0;
+  const H *fr = f.frame + (size_t)col * 9;
+  const double e[3] = {fr[0], fr[1], fr[2]}, n[3] = {fr[3], fr[4], fr[5]};
+  float o[kF][kHq];
+#pragma unroll
+  for (int q = 0; q < kHq; ++q) {
+    const double p = c.p_ref * powd(c.Rd * rth[q] / c.p_ref, c.gamma);
+    const double vx = (double)mx[q] / rho[q], vy = (double)my[q] / rho[q], vz = (double)mz[q] / rho[q];
+    const double W1 = lev0 + q == L - 1 ? 0.0 : W[q + 1];
+    o[0][q] = (float)(p / (rho[q] * c.Rd));
+    o[1][q] = (float)(e[0] * vx + e[1] * vy);
+    o[2][q] = (float)(n[0] * vx + n[1] * vy + n[2] * vz);
+    o[3][q] = (float)(0.5 * (W[q] + W1) / rho[q]);
+    o[4][q] = (float)p;
+  }
   const size_t NL = (size_t)c.N * L;
-  out[oi] = (float)(p / (rho * c.Rd));
-  out[NL + oi] = (float)(e[0] * vx + e[1] * vy + e[2] * vz);
-  out[2 * NL + oi] = (float)(n[0] * vx + n[1] * vy + n[2] * vz);
-  out[3 * NL + oi] = (float)(0.5 * (W + W1) / rho);
-  out[4 * NL + oi] = (float)p;
+#pragma unroll
+  for (int k = 0; k < kF; ++k) {
+    float *d = out + k * NL + oi;
+    if (VEC) {
+      *reinterpret_cast<float4 *>(d) = make_float4(o[k][0], o[k][1], o[k][2], o[k][3]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kHq; ++q)
+        if (lev0 + q < L) d[q] = o[k][q];
+    }
+  }
 }
 
 // Coarse state from a fine one: area-weighted T and p, mass-weighted
@@ -234,9 +260,8 @@ __global__ __launch_bounds__(256) void k_apply(Fields<H> f, Consts c, const floa
   if (!ln.store) return;
   if (k == 0 && applied) applied[ln.col] = ok ? 1 : 0;
   if (!ok) return;
-  const H *rh = f.rhat + (size_t)ln.col * 3;
-  double e[3], n[3];
-  east_north(rh[0], rh[1], rh[2], e, n);
+  const H *fr = f.frame + (size_t)ln.col * 9;
+  const double e[3] = {fr[0], fr[1], fr[2]}, n[3] = {fr[3], fr[4], fr[5]};
   const double r = rho1 / rho;
   f.Mx_t[idx] = (H)(r * (double)f.Mx_t[idx] + rho1 * (du * e[0] + dv * n[0]));
   f.My_t[idx] = (H)(r * (double)f.My_t[idx] + rho1 * (du * e[1] + dv * n[1]));
@@ -363,6 +388,17 @@ struct thor_corrector {
   int *applied = nullptr;    // device [N]
 };
 
+namespace {
+template <typename H>
+void launch_fields(thor_state *s, const Fields<H> &f, float *out) {
+  const dim3 g((unsigned)(((size_t)s->c.N * (s->c.S / kHq) + 255) / 256));
+  if (s->c.L % kHq == 0 && ((uintptr_t)out & 15) == 0)
+    hipLaunchKernelGGL((k_fields<H, true>), g, dim3(256), 0, s->stream, f, s->c, out);
+  else
+    hipLaunchKernelGGL((k_fields<H, false>), g, dim3(256), 0, s->stream, f, s->c, out);
+}
+}  // namespace
+
 extern "C" {
 
 int thor_restriction_bytes(const thor_grid *fine, const thor_grid *coarse, size_t *bytes) {
@@ -483,11 +519,8 @@ int thor_restrict(thor_state *fine, thor_state *coarse, const thor_restriction *
 int thor_state_fields32(thor_state *s, float *dev_out) {
   clear_error();
   if (!s || !dev_out) { set_error("thor_state_fields32: NULL argument"); return THOR_EINVAL; }
-  const unsigned nbk = cblocks(s->c.N, s->c.L);
-  if (s->precision == THOR_MIXED)
-    hipLaunchKernelGGL(k_fields<float>, dim3(nbk), dim3(256), 0, s->stream, s->f32[s->parity], s->c, dev_out);
-  else
-    hipLaunchKernelGGL(k_fields<double>, dim3(nbk), dim3(256), 0, s->stream, s->f64[s->parity], s->c, dev_out);
+  if (s->precision == THOR_MIXED) launch_fields(s, s->f32[s->parity], dev_out);
+  else launch_fields(s, s->f64[s->parity], dev_out);
   return ok_hip(hipGetLastError(), "fields launch") ? THOR_OK : THOR_EHIP;
 }
 

@@ -420,12 +420,11 @@ int build_grid(const thor_grid_params &p, Grid &G) {
   G.frame.resize((size_t)n * 9);
   for (int64_t c = 0; c < n; ++c) {
     const Vec3 p = G.pos[c];
-    // e1 along z x p, or x x p near the poles; e2 = p x e1
-    Vec3 a = std::fabs(p.z) < 0.9 ? Vec3{-p.y, p.x, 0.0} : Vec3{0.0, -p.z, p.y};
-    const double l = std::sqrt(a.x * a.x + a.y * a.y + a.z * a.z);
-    a = Vec3{a.x / l, a.y / l, a.z / l};
-    const Vec3 b{p.y * a.z - p.z * a.y, p.z * a.x - p.x * a.z, p.x * a.y - p.y * a.x};
-    const double f[9] = {a.x, a.y, a.z, b.x, b.y, b.z, p.x, p.y, p.z};
+    // local east and north (at a pole the longitude counts as 0)
+    const double h = std::sqrt(p.x * p.x + p.y * p.y);
+    const bool pole = h < 1e-12;
+    const double cl = pole ? 1.0 : p.x / h, sl = pole ? 0.0 : p.y / h;
+    const double f[9] = {-sl, cl, 0.0, -p.z * cl, -p.z * sl, pole ? 0.0 : h, p.x, p.y, p.z};
     std::copy(f, f + 9, &G.frame[(size_t)c * 9]);
   }
   G.div_t.resize((size_t)n * 14);

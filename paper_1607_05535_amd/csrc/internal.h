@@ -31,7 +31,7 @@ struct Grid {
   std::vector<double> lap_coef;  // [n][6]
   std::vector<int32_t> dd_idx;   // [n][18] two-ring columns, -1 pad
   std::vector<double> dd_w;      // [n][18][3] lap(grad .) weights
-  // tangent basis of every column (e1, e2, then the cell point) and the
+  // frame of every column (local east, north, then the cell point) and the
   // coefficients contracted with it: the divergence with the basis of the
   // column the vector sits in, gradient and damping with that of the column
   // they act on

@@ -26,8 +26,8 @@ struct Fields {
   const H *dc;            // [N][21] divergence/gradient coefficient vectors
   const H *lc;            // [N][6]  Laplacian neighbour weights
   const H *rhat;          // [N][3]
-  const H *frame;         // [N][9]  tangent basis e1, e2 and rhat of the column
-  const H *dv;            // [N][14] divergence coefficients of (Ma, Mb): c_j . (e1, e2) of column j
+  const H *frame;         // [N][9]  local east e, north n and rhat of the column
+  const H *dv;            // [N][14] divergence coefficients of (Ma, Mb): c_j . (e, n) of column j
   const H *gt;            // [N][12] gradient coefficients in the column's own basis
   const int32_t *ddi;     // [N][18] two-ring columns (-1 pad)
   const H *ddw;           // [N][18][2] lap(grad .) weights in the column's own basis
@@ -36,7 +36,7 @@ struct Fields {
 
   // current small-step state.  Inside a stage rho holds the deviation from
   // rho[t] (the stage's last substep leaves the density itself) and the
-  // horizontal momentum its two tangent components (Ma, Mb); the last
+  // horizontal momentum its east and north components (Ma, Mb); the last
   // substep of a large step also leaves it as the Cartesian (Mx, My, Mz) that
   // every other reader of the state uses
   double *rho, *rth, *W;  // [N][L]

@@ -1787,17 +1787,13 @@ __device__ __forceinline__ void b_diag(const Fields<H> &f, const Consts &c, cons
   if (!ln.store) return;
   const double rho = f.rho_t[idx];
   double out = 0.0;
-  const H *rh = f.rhat + (size_t)col * 3;
-  const double x = rh[0], y = rh[1], z = rh[2];
   if (field == THOR_F_T || field == THOR_F_P) {
     const double p = c.p_ref * powd(c.Rd * f.rth_t[idx] / c.p_ref, c.gamma);
     out = field == THOR_F_P ? p : p / (rho * c.Rd);
   } else if (field == THOR_F_U || field == THOR_F_V) {
-    const double lam = (sqrt(x * x + y * y) < 1e-12) ? 0.0 : atan2(y, x);
-    const double phi = asin(fmin(1.0, fmax(-1.0, z)));
+    const H *e = f.frame + (size_t)col * 9 + (field == THOR_F_U ? 0 : 3);
     const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
-    if (field == THOR_F_U) out = -sin(lam) * vx + cos(lam) * vy;
-    else out = -sin(phi) * cos(lam) * vx - sin(phi) * sin(lam) * vy + cos(phi) * vz;
+    out = (double)e[0] * vx + (double)e[1] * vy + (double)e[2] * vz;
   } else if (field == THOR_F_W) {
     out = 0.5 * (W + W1) / rho;
   } else if (field == THOR_F_RHO) {
