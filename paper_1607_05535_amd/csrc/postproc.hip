@@ -34,7 +34,9 @@ namespace {
 
 constexpr int kZq = 4;          // interpolated quantities: u, v, T, theta
 constexpr int kZslot = kZq + 1; // + valid flag
-constexpr int kZthreads = 256;  // threads of a band's reduction
+constexpr int kZthreads = 256;  // threads of a workgroup
+constexpr int kZcols = 16;      // columns per workgroup of the interpolation
+constexpr int kZpitch = kZcols + 1;   // LDS row of one level over those columns, padded
 
 bool zok(hipError_t e, const char *what) {
   if (e == hipSuccess) return true;
@@ -42,151 +44,150 @@ bool zok(hipError_t e, const char *what) {
   return false;
 }
 
-// Per column (lanes = levels, floor(64 / L) columns per wavefront): p, T,
-// u, v, theta of every level, then for each pressure level the interval of
-// the lowest-index level pair whose pressures bracket it; the column's
-// values there go to Z[col][j][0..3] and Z[col][j][4] = 1 (0 if none).
-// Zw[col] = w at the centre of the first layer (half the momentum of the
-// first interior interface over rho; the ground interface carries none).
+// Columns pos0 .. pos0 + kZcols - 1 of the band-sorted list `cols` per
+// workgroup: p, u, v, T, theta of every level into LDS ([quantity][level]
+// [column], dynamic), then one thread per (pressure level, column) looks for
+// the lowest-index level pair whose pressures bracket the level; the values
+// there go to Z[j][0..3][pos] and Z[j][4][pos] = 1 (0 if none).  Positions
+// along the lanes: 128-byte rows out, and the reduction reads a band's
+// columns contiguously.  Zw[pos] = w at the centre of the first layer (half
+// the momentum of the first interior interface over rho; the ground
+// interface carries none).
+// Bound by reading the state (40 bytes per cell); g6 L32, 20 levels:
+// 81 -> 29 us (one wavefront per column before, all its lanes
+// once through every pressure level, and the angles of every cell).
 template <typename H>
-__global__ __launch_bounds__(256) void k_zinterp(Fields<H> f, Consts c, const double *plev, int np, double *Z,
-                                                 double *Zw) {
-  const int lane = threadIdx.x & 63;
-  const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  const int L = c.L, cpw = 64 / L;
-  const int cw = lane / L, lev = lane - cw * L;
-  const bool real = cw < cpw;
-  int col = wave * cpw + cw;
-  const bool store = real && col < c.N;
-  if (col >= c.N) col = c.N - 1;
-  const size_t idx = (size_t)col * c.S + lev;   // state row stride
-  const double rho = f.rho_t[idx], rth = f.rth_t[idx];
-  const double p = c.p_ref * powd(c.Rd * rth / c.p_ref, c.gamma);
-  const H *rh = f.rhat + (size_t)col * 3;
-  const double x = rh[0], y = rh[1], z = rh[2];
-  const double lam = sqrt(x * x + y * y) < 1e-12 ? 0.0 : atan2(y, x);
-  const double phi = asin(fmin(1.0, fmax(-1.0, z)));
-  const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
-  double q[kZq];
-  q[0] = -sin(lam) * vx + cos(lam) * vy;
-  q[1] = -sin(phi) * cos(lam) * vx - sin(phi) * sin(lam) * vy + cos(phi) * vz;
-  q[2] = p / (rho * c.Rd);
-  q[3] = rth / rho;
-  const int lp = lane < 63 ? lane + 1 : 63;
-  const double p_up = __shfl(p, lp, 64);
-  const double Wl = lev == 0 ? 0.0 : (double)f.W_t[idx];
-  const double W_up = __shfl(Wl, lp, 64);
-  if (store && lev == 0) Zw[col] = L > 1 ? 0.5 * W_up / rho : 0.0;
-  double q_up[kZq];
-#pragma unroll
-  for (int k = 0; k < kZq; ++k) q_up[k] = __shfl(q[k], lp, 64);
-  const int first = cw * L;   // first lane of the column (in range for every lane)
-  const unsigned long long colmask = (L == 64 ? ~0ull : ((1ull << L) - 1)) << (real ? first : 0);
-  for (int j = 0; j < np; ++j) {
+__global__ __launch_bounds__(kZthreads) void k_zinterp(Fields<H> f, Consts c, const int32_t *cols, const double *plev,
+                                                       int np, double *Z, double *Zw) {
+  extern __shared__ double zs[];
+  const int L = c.L, N = c.N, pos0 = blockIdx.x * kZcols, nc = min(kZcols, N - pos0);
+  const int plane = L * kZpitch;   // one quantity
+  for (int i = threadIdx.x; i < nc * L; i += kZthreads) {
+    const int cb = i / L, lev = i - cb * L, col = cols[pos0 + cb];
+    const size_t idx = (size_t)col * c.S + lev;   // state row stride
+    const double rho = f.rho_t[idx], rth = f.rth_t[idx];
+    const double p = c.p_ref * powd(c.Rd * rth / c.p_ref, c.gamma);
+    const H *fr = f.frame + (size_t)col * 9;
+    const double e[2] = {fr[0], fr[1]}, n[3] = {fr[3], fr[4], fr[5]};
+    const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
+    double *o = zs + lev * kZpitch + cb;
+    o[0] = p;
+    o[plane] = e[0] * vx + e[1] * vy;
+    o[2 * plane] = n[0] * vx + n[1] * vy + n[2] * vz;
+    o[3 * plane] = p / (rho * c.Rd);
+    o[4 * plane] = rth / rho;
+    if (lev == 0) Zw[pos0 + cb] = L > 1 ? 0.5 * f.W_t[idx + 1] / rho : 0.0;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < np * kZcols; i += kZthreads) {
+    const int j = i / kZcols, cb = i - j * kZcols;
+    if (cb >= nc) continue;
     const double pj = plev[j];
-    // interval (lev, lev + 1): lo = p_up < hi = p
-    const bool hit = real && lev + 1 < L && p_up <= pj && pj <= p;
-    const unsigned long long m = __ballot(hit) & colmask;
-    const int src = m ? __builtin_ctzll(m) : lane;
-    const double w = (pj - p_up) / (p - p_up);
-    double v[kZq];
+    const double *col = zs + cb;
+    // interval (k, k + 1): p of k + 1 <= p_j <= p of k; four levels read at
+    // a time (past the top the last level again, which brackets nothing new)
+    int k = -1;
+    double hi = col[0];
+    for (int l = 0; l + 1 < L && k < 0; l += 4) {
+      double v[4];
 #pragma unroll
-    for (int k = 0; k < kZq; ++k) v[k] = q_up[k] + w * (q[k] - q_up[k]);
-    double o[kZq];
+      for (int u = 0; u < 4; ++u) v[u] = col[min(l + 1 + u, L - 1) * kZpitch];
 #pragma unroll
-    for (int k = 0; k < kZq; ++k) o[k] = __shfl(v[k], src, 64);
-    if (store && lev == 0) {
-      double *out = Z + ((size_t)col * np + j) * kZslot;
-#pragma unroll
-      for (int k = 0; k < kZq; ++k) out[k] = m ? o[k] : 0.0;
-      out[kZq] = m ? 1.0 : 0.0;
+      for (int u = 3; u >= 0; --u)
+        if (l + 1 + u < L && v[u] <= pj && pj <= (u ? v[u - 1] : hi)) k = l + u;
+      hi = v[3];
     }
+    double *out = Z + (size_t)j * kZslot * N + pos0 + cb;
+    const double p0 = col[max(k, 0) * kZpitch], p1 = col[min(max(k, 0) + 1, L - 1) * kZpitch];
+    const double w = (pj - p1) / (p0 - p1);
+    const double *q0 = col + max(k, 0) * kZpitch, *q1 = q0 + (k < 0 ? 0 : kZpitch);
+#pragma unroll
+    for (int q = 1; q <= kZq; ++q) {
+      const double up = q1[q * plane];
+      out[(size_t)(q - 1) * N] = k < 0 ? 0.0 : up + w * (q0[q * plane] - up);
+    }
+    out[(size_t)kZq * N] = k < 0 ? 0.0 : 1.0;
   }
 }
 
-// Fixed-order sum of one value per thread over the workgroup.
-__device__ __forceinline__ double block_sum(double v, double *sm) {
-  sm[threadIdx.x] = v;
+// Sums of NV values per thread over the workgroup, in a fixed order (across
+// the wavefront's lanes, then the wavefronts), to every thread.
+template <int NV>
+__device__ __forceinline__ void block_sums(double v[NV], double (*sm)[NV]) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] += __shfl_xor(v[k], o, 64);
+  __syncthreads();   // the previous sums have been read
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < NV; ++k) sm[threadIdx.x >> 6][k] = v[k];
   __syncthreads();
-  for (int s = kZthreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sm[threadIdx.x] += sm[threadIdx.x + s];
-    __syncthreads();
-  }
-  const double r = sm[0];
-  __syncthreads();
-  return r;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] = ((sm[0][k] + sm[1][k]) + sm[2][k]) + sm[3][k];
 }
 
-// Band b, pressure level j (one workgroup each): area-weighted means of the
-// band's columns that have a value (thread t takes columns t, t + 256, ... of
+// Band b, pressure level j < np (one workgroup each): area-weighted means of the
+// band's columns that have a value (thread t takes positions t, t + 256, ... of
 // the band's list), then the eddy products; added to the time sums
 // S[b][j][0..6] = u, v, T, theta, [u'v'], [v'T'], valid fraction and to the
-// snapshot count S[b][j][7].
-__global__ __launch_bounds__(kZthreads) void k_zreduce(const double *Z, int np, const int32_t *off,
-                                                       const int32_t *cols, const double *area, double *S) {
-  __shared__ double sm[kZthreads];
+// snapshot count S[b][j][7].  j = np: the area-weighted mean of the
+// first-layer w over all of the band's columns, then each column's deviation
+// from it added to the time sum Wsum[column].
+// Bound by latency: two passes over a band of ~1000 columns (the second from
+// L2); g6 L32, 20 levels and 36 bands: 42 -> 14 us (the
+// with one barrier tree per sum over 800-byte strides, and the map in a kernel of its own).
+__global__ __launch_bounds__(kZthreads) void k_zreduce(const double *Z, const double *Zw, int np, int N,
+                                                       const int32_t *off, const int32_t *cols, const double *area,
+                                                       double *S, double *Wsum) {
+  __shared__ double sm[kZthreads / 64][6];
   const int b = blockIdx.x, j = blockIdx.y;
   const int a0 = off[b], a1 = off[b + 1];
-  double Aband = 0.0, sA = 0, su = 0, sv = 0, sT = 0, sth = 0;
-  for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) {
-    const int col = cols[i];
-    const double *z = Z + ((size_t)col * np + j) * kZslot;
-    const double A0 = area[col], A = A0 * z[kZq];
-    Aband += A0;
-    sA += A;
-    su += A * z[0];
-    sv += A * z[1];
-    sT += A * z[2];
-    sth += A * z[3];
+  if (j == np) {
+    double s[6] = {0, 0, 0, 0, 0, 0};
+    for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) {
+      s[0] += area[i];
+      s[1] += area[i] * Zw[i];
+    }
+    block_sums<6>(s, sm);
+    if (s[0] == 0.0) return;   // empty band, uniform across the workgroup
+    const double mw = s[1] / s[0];
+    for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) Wsum[cols[i]] += Zw[i] - mw;
+    return;
   }
-  sA = block_sum(sA, sm);
+  const double *z = Z + (size_t)j * kZslot * N;
+  double s[6] = {0, 0, 0, 0, 0, 0};   // A, band area, u, v, T, theta
+  for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) {
+    const double A0 = area[i], A = A0 * z[(size_t)kZq * N + i];
+    s[0] += A;
+    s[1] += A0;
+    s[2] += A * z[i];
+    s[3] += A * z[(size_t)N + i];
+    s[4] += A * z[(size_t)2 * N + i];
+    s[5] += A * z[(size_t)3 * N + i];
+  }
+  block_sums<6>(s, sm);
+  const double sA = s[0];
   if (sA == 0.0) return;   // uniform across the workgroup
-  Aband = block_sum(Aband, sm);
-  const double mu = block_sum(su, sm) / sA, mv = block_sum(sv, sm) / sA;
-  const double mT = block_sum(sT, sm) / sA, mth = block_sum(sth, sm) / sA;
-  double euv = 0, evT = 0;
+  const double mu = s[2] / sA, mv = s[3] / sA, mT = s[4] / sA, mth = s[5] / sA, frac = sA / s[1];
+  double e[6] = {0, 0, 0, 0, 0, 0};
   for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) {
-    const int col = cols[i];
-    const double *z = Z + ((size_t)col * np + j) * kZslot;
-    const double A = area[col] * z[kZq];
-    euv += A * (z[0] - mu) * (z[1] - mv);
-    evT += A * (z[1] - mv) * (z[2] - mT);
+    const double A = area[i] * z[(size_t)kZq * N + i];
+    const double dv = z[(size_t)N + i] - mv;
+    e[0] += A * (z[i] - mu) * dv;
+    e[1] += A * dv * (z[(size_t)2 * N + i] - mT);
   }
-  euv = block_sum(euv, sm) / sA;
-  evT = block_sum(evT, sm) / sA;
+  block_sums<6>(e, sm);
   if (threadIdx.x == 0) {
     double *o = S + ((size_t)b * np + j) * 8;
     o[0] += mu;
     o[1] += mv;
     o[2] += mT;
     o[3] += mth;
-    o[4] += euv;
-    o[5] += evT;
-    o[6] += sA / Aband;
+    o[4] += e[0] / sA;
+    o[5] += e[1] / sA;
+    o[6] += frac;
     o[7] += 1.0;
-  }
-}
-
-// Band b (one workgroup): area-weighted mean of the first-layer w over all
-// of the band's columns, then each column's deviation from it added to the
-// time sum Wsum[col].
-__global__ __launch_bounds__(kZthreads) void k_zimprint(const double *Zw, const int32_t *off, const int32_t *cols,
-                                                        const double *area, double *Wsum) {
-  __shared__ double sm[kZthreads];
-  const int b = blockIdx.x;
-  const int a0 = off[b], a1 = off[b + 1];
-  double sA = 0, sw = 0;
-  for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) {
-    const int col = cols[i];
-    sA += area[col];
-    sw += area[col] * Zw[col];
-  }
-  sA = block_sum(sA, sm);
-  if (sA == 0.0) return;   // empty band, uniform across the workgroup
-  const double mw = block_sum(sw, sm) / sA;
-  for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) {
-    const int col = cols[i];
-    Wsum[col] += Zw[col] - mw;
   }
 }
 
@@ -338,10 +339,12 @@ int thor_zonal_init(thor_state *s, const thor_grid *g, double radius, double gra
   for (int b = 0; b < n_bands; ++b) off[b + 1] += off[b];
   std::vector<int32_t> fill(off.begin(), off.end() - 1);
   for (size_t i = 0; i < N; ++i) cols[fill[band[i]]++] = (int32_t)i;
+  std::vector<double> area(N);   // in band order, as Z and Zw
+  for (size_t i = 0; i < N; ++i) area[i] = g->g.area[cols[i]];
   hipStream_t st = s->stream;
   const size_t ns = (size_t)n_bands * n_plev * 8;
   bool ok = zok(hipMemcpyAsync(z->plev, plev, n_plev * sizeof(double), hipMemcpyHostToDevice, st), "copy plev") &&
-            zok(hipMemcpyAsync(z->area, g->g.area.data(), N * sizeof(double), hipMemcpyHostToDevice, st), "copy area") &&
+            zok(hipMemcpyAsync(z->area, area.data(), N * sizeof(double), hipMemcpyHostToDevice, st), "copy area") &&
             zok(hipMemcpyAsync(z->off, off.data(), off.size() * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy off") &&
             zok(hipMemcpyAsync(z->cols, cols.data(), N * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy cols");
   if (ok) {
@@ -358,17 +361,16 @@ int thor_zonal_accumulate(thor_zonal *z) {
   clear_error();
   if (!z) { set_error("thor_zonal_accumulate: NULL argument"); return THOR_EINVAL; }
   thor_state *s = z->s;
-  const int L = s->c.L, cpw = 64 / L;
-  const long waves = (s->c.N + cpw - 1) / cpw;
-  const unsigned nbk = (unsigned)((waves + 3) / 4);
+  const dim3 g((unsigned)((s->c.N + kZcols - 1) / kZcols)), t(kZthreads);
+  const unsigned lds = (unsigned)(kZslot * s->c.L * kZpitch * sizeof(double));   // 43520 bytes at 64 levels
   if (s->precision == THOR_MIXED)
-    hipLaunchKernelGGL(k_zinterp<float>, dim3(nbk), dim3(256), 0, s->stream, s->f32[s->parity], s->c, z->plev, z->np, z->Z,
+    hipLaunchKernelGGL(k_zinterp<float>, g, t, lds, s->stream, s->f32[s->parity], s->c, z->cols, z->plev, z->np, z->Z,
                        z->Zw);
   else
-    hipLaunchKernelGGL(k_zinterp<double>, dim3(nbk), dim3(256), 0, s->stream, s->f64[s->parity], s->c, z->plev, z->np, z->Z,
+    hipLaunchKernelGGL(k_zinterp<double>, g, t, lds, s->stream, s->f64[s->parity], s->c, z->cols, z->plev, z->np, z->Z,
                        z->Zw);
-  hipLaunchKernelGGL(k_zreduce, dim3(z->nb, z->np), dim3(kZthreads), 0, s->stream, z->Z, z->np, z->off, z->cols, z->area, z->S);
-  hipLaunchKernelGGL(k_zimprint, dim3(z->nb), dim3(kZthreads), 0, s->stream, z->Zw, z->off, z->cols, z->area, z->Wsum);
+  hipLaunchKernelGGL(k_zreduce, dim3(z->nb, z->np + 1), t, 0, s->stream, z->Z, z->Zw, z->np, s->c.N, z->off, z->cols,
+                     z->area, z->S, z->Wsum);
   if (!zok(hipGetLastError(), "zonal accumulate")) return THOR_EHIP;
   z->snapshots += 1;
   return THOR_OK;

@@ -69,3 +69,34 @@ def test_zonal_means_match_the_oracle():
     assert n == 0 and np.all(got["snapshots"] == 0) and np.all(got["u"] == 0)
     imp, n_imp = z.imprint()
     assert n_imp == 0 and np.all(imp == 0)
+
+
+@pytest.mark.parametrize("n_lev,n_plev,n_bands", [(1, 2, 3), (2, 1, 1), (13, 33, 41), (33, 5, 7), (64, 17, 201)])
+def test_zonal_means_at_the_edges_of_the_work_split(n_lev, n_plev, n_bands):
+    """Level counts from one to 64, more bands than latitudes (empty bands; an
+    odd number of bands, so that no column sits on a band edge)
+    and a column count that is no multiple of a workgroup's columns."""
+    from paper_1607_05535_amd import thor
+    w = workloads.small_gas_giant(glevel=2, n_lev=n_lev)
+    w.z_top *= min(1.0, n_lev / 12)   # layers thin enough for a hydrostatic column
+    w.noise_amp = 2.0
+    G = oracle_grid(w.glevel)
+    model, ost = odyn.model_from_workload(w, G)
+    ost = odyn.run(model, ost, 1, w.n_acoustic)
+    p0 = odyn.fields(model, ost)["p"]
+    plev = np.geomspace(0.5 * p0[:, -1].min(), 1.05 * p0[:, 0].max(), n_plev + 2)[1:-1]
+    grid = thor.Grid(w.glevel)
+    st = thor.State(grid, *thor.structs_from_workload(w))
+    st.step(1, w.n_acoustic)
+    z = thor.Zonal(st, grid, w.radius, w.gravity, n_bands, plev)
+    z.accumulate()
+    got, n = z.result()
+    ref, cnt = opp.time_mean([opp.snapshot(model, ost, plev, n_bands)])
+    assert n == 1 and np.array_equal(got["snapshots"], cnt)
+    speed = max(np.abs(ref["u"]).max(), np.abs(ref["v"]).max(), 1e-300)
+    for k, scale in (("u", speed), ("v", speed), ("T", 1300.0), ("theta", max(np.abs(ref["theta"]).max(), 1.0)),
+                     ("upvp", speed ** 2), ("vpTp", speed * 10.0), ("weight", 1.0)):
+        assert np.abs(got[k] - ref[k]).max() <= 1e-9 * scale, k
+    imp, _ = z.imprint()
+    imp_ref = opp.imprint_map([opp.imprint_snapshot(model, ost, n_bands)])
+    assert np.abs(imp - imp_ref).max() <= 1e-9 * max(np.abs(opp.first_layer_w(model, ost)).max(), 1e-300)
