@@ -118,6 +118,7 @@ inline int n_blocks(const Consts &c, int wpb) { return n_blocks_for(c.N, c.cpw, 
 // or, across a lane boundary, one shuffle.
 constexpr int kHq = 4;
 inline int n_blocks_h(const Consts &c, int wpb) { return n_blocks_for(c.N, c.hcpw, wpb); }
+inline long n_waves_h(const Consts &c) { return (c.N + c.hcpw - 1) / c.hcpw; }
 
 // Launchers.  `wpb` = wavefronts per workgroup (tuned per kernel family).
 // The prognostic state between large steps lives in the *_t buffers; a large

@@ -135,8 +135,8 @@ __device__ __forceinline__ void block_sums(double v[NV], double (*sm)[NV]) {
 // first-layer w over all of the band's columns, then each column's deviation
 // from it added to the time sum Wsum[column].
 // Bound by latency: two passes over a band of ~1000 columns (the second from
-// L2); g6 L32, 20 levels and 36 bands: 42 -> 14 us (the
-// with one barrier tree per sum over 800-byte strides, and the map in a kernel of its own).
+// L2); g6 L32, 20 levels and 36 bands: 42 -> 14 us (before,
+// one barrier tree per sum over 800-byte strides, and the map in a kernel of its own).
 __global__ __launch_bounds__(kZthreads) void k_zreduce(const double *Z, const double *Zw, int np, int N,
                                                        const int32_t *off, const int32_t *cols, const double *area,
                                                        double *S, double *Wsum) {

@@ -542,6 +542,7 @@ int thor_state_init(const thor_grid *g, const thor_planet *pl, const thor_vertic
   c.cpw = 64 / v->n_lev;
   c.hlpc = (v->n_lev + kHq - 1) / kHq;
   c.hcpw = 64 / c.hlpc;
+  default_wpb(n_waves_h(c), s->precision == THOR_MIXED, false, s->wpb);
   c.radius = pl->radius;
   c.omega = pl->omega;
   c.grav = pl->gravity;
@@ -784,7 +785,7 @@ struct thor_batch {
   void *tables = nullptr;          // device: Planet<H>[n], then FAM_COUNT tile tables
   size_t tile_cap = 0;             // entries reserved per tile table
   int n_tiles[FAM_COUNT] = {0, 0, 0, 0};
-  int wpb[FAM_COUNT] = {4, 4, 4, 4};
+  int wpb[FAM_COUNT] = {1, 1, 1, 1};   // set by default_wpb
   int parity = 0;
   hipStream_t stream = nullptr;
   hipStream_t cap_stream = nullptr;
@@ -933,6 +934,9 @@ int thor_batch_init(int n, const thor_grid *const *grids, const thor_planet *pl,
     b->members.push_back(m);
     off += align256(bytes);
   }
+  long waves = 0;
+  for (auto m : b->members) waves += n_waves_h(m->c);
+  default_wpb(waves, b->precision == THOR_MIXED, true, b->wpb);
   b->tables = base + off;
   b->tile_cap = batch_tile_cap(n, grids, v);
   size_t pb;
