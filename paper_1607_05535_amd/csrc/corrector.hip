@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void k_fields(Fields<H> f, Consts c, float *ou
   row4(f.Mz_t + idx, mz);
   W[kHq] = lev0 + kHq < L ? f.W_t[idx + kHq] : 0.0;
   if (lev0 == 0) W[0] = 0.0;
-  const H *fr = f.frame + (size_t)col * 9;
+  const H *fr = f.frame + (size_t)col * kFr;
   const double e[3] = {fr[0], fr[1], fr[2]}, n[3] = {fr[3], fr[4], fr[5]};
   float o[kF][kHq];
 #pragma unroll
@@ -169,9 +169,7 @@ __global__ __launch_bounds__(256) void k_restrict(Fields<H> ff, Consts cf, Field
 }
 
 __device__ __forceinline__ int slot_col(const int32_t *nbr, int col, int s) {
-  if (s == 0) return col;
-  const int v = nbr[(size_t)col * 6 + s - 1];
-  return v < 0 ? col : v;
+  return s == 0 ? col : nbr[(size_t)col * 6 + s - 1];
 }
 
 // Network inputs of every column from a fields array [f][col][lev].
@@ -260,7 +258,7 @@ __global__ __launch_bounds__(256) void k_apply(Fields<H> f, Consts c, const floa
   if (!ln.store) return;
   if (k == 0 && applied) applied[ln.col] = ok ? 1 : 0;
   if (!ok) return;
-  const H *fr = f.frame + (size_t)ln.col * 9;
+  const H *fr = f.frame + (size_t)ln.col * kFr;
   const double e[3] = {fr[0], fr[1], fr[2]}, n[3] = {fr[3], fr[4], fr[5]};
   const double r = rho1 / rho;
   f.Mx_t[idx] = (H)(r * (double)f.Mx_t[idx] + rho1 * (du * e[0] + dv * n[0]));

@@ -417,7 +417,7 @@ int build_grid(const thor_grid_params &p, Grid &G) {
 
   // Tangent bases and the coefficients in them: horizontal momentum has two
   // components, so the step's kernels gather two rows and weights, not three.
-  G.frame.resize((size_t)n * 9);
+  G.frame.assign((size_t)n * 12, 0.0);
   for (int64_t c = 0; c < n; ++c) {
     const Vec3 p = G.pos[c];
     // local east and north (at a pole the longitude counts as 0)
@@ -425,14 +425,14 @@ int build_grid(const thor_grid_params &p, Grid &G) {
     const bool pole = h < 1e-12;
     const double cl = pole ? 1.0 : p.x / h, sl = pole ? 0.0 : p.y / h;
     const double f[9] = {-sl, cl, 0.0, -p.z * cl, -p.z * sl, pole ? 0.0 : h, p.x, p.y, p.z};
-    std::copy(f, f + 9, &G.frame[(size_t)c * 9]);
+    std::copy(f, f + 9, &G.frame[(size_t)c * 12]);
   }
-  G.div_t.resize((size_t)n * 14);
+  G.div_t.assign((size_t)n * 16, 0.0);
   G.grad_t.resize((size_t)n * 12);
   G.dd_t.resize((size_t)n * kRing2 * 2);
   // the two tangent components (basis of column y) of a coefficient vector
   auto tangent = [&](const double *v, int64_t y, double *out) {
-    const double *f = &G.frame[(size_t)y * 9];
+    const double *f = &G.frame[(size_t)y * 12];
     out[0] = v[0] * f[0] + v[1] * f[1] + v[2] * f[2];
     out[1] = v[0] * f[3] + v[1] * f[4] + v[2] * f[5];
   };
@@ -440,11 +440,19 @@ int build_grid(const thor_grid_params &p, Grid &G) {
     for (int j = 0; j < 7; ++j) {
       const double *cj = &G.div_coef[(size_t)c * 21 + 3 * j];
       const int32_t m = j ? G.nbr[(size_t)c * 6 + j - 1] : (int32_t)c;
-      tangent(cj, m < 0 ? c : m, &G.div_t[(size_t)c * 14 + 2 * j]);
+      tangent(cj, m < 0 ? c : m, &G.div_t[(size_t)c * 16 + 2 * j]);
       if (j) tangent(cj, c, &G.grad_t[(size_t)c * 12 + 2 * (j - 1)]);
     }
     for (int m = 0; m < kRing2; ++m)
       tangent(&G.dd_w[((size_t)c * kRing2 + m) * 3], c, &G.dd_t[((size_t)c * kRing2 + m) * 2]);
+  }
+  G.nbr_own = G.nbr;
+  G.dd_own = G.dd_idx;
+  for (int64_t c = 0; c < n; ++c) {
+    for (int j = 0; j < 6; ++j)
+      if (G.nbr_own[(size_t)c * 6 + j] < 0) G.nbr_own[(size_t)c * 6 + j] = (int32_t)c;
+    for (int m = 0; m < kRing2; ++m)
+      if (G.dd_own[(size_t)c * kRing2 + m] < 0) G.dd_own[(size_t)c * kRing2 + m] = (int32_t)c;
   }
   return THOR_OK;
 }

@@ -35,10 +35,12 @@ struct Grid {
   // coefficients contracted with it: the divergence with the basis of the
   // column the vector sits in, gradient and damping with that of the column
   // they act on
-  std::vector<double> frame;     // [n][9]
-  std::vector<double> div_t;     // [n][7][2]
+  std::vector<double> frame;     // [n][12], the last 3 zero
+  std::vector<double> div_t;     // [n][16], 7 x 2 and 2 zeros
   std::vector<double> grad_t;    // [n][6][2]
   std::vector<double> dd_t;      // [n][18][2]
+  std::vector<int32_t> nbr_own;  // nbr and dd_idx with the column itself in place of -1
+  std::vector<int32_t> dd_own;
 };
 
 int build_grid(const thor_grid_params &p, Grid &G);

@@ -13,24 +13,30 @@
 #include <cstdint>
 
 #include "../../include/thor.h"
+#include "internal.h"
 
 namespace thor {
 
 // Horizontal-field storage/arithmetic type: double (FP64 path) or float
 // (mixed-precision form).  Vertical solve, reference state and prognostic
 // density / rho-theta / W stay double in both.
+// Values per column of the stencil records, padded so that a record is a
+// multiple of 16 bytes in either precision (they are copied in 16-byte pieces).
+constexpr int kDc = 24, kLc = 8, kFr = 12, kDv = 16, kGt = 12, kDw = 2 * kRing2;
+
 template <typename H>
 struct Fields {
-  // geometry (per column)
-  const int32_t *nbr;     // [N][6], -1 pad
-  const H *dc;            // [N][21] divergence/gradient coefficient vectors
-  const H *lc;            // [N][6]  Laplacian neighbour weights
+  // geometry (per column; a pentagon's missing neighbour, and a missing
+  // two-ring column, is the column itself with zero weight)
+  const int32_t *nbr;     // [N][6]
+  const H *dc;            // [N][kDc] divergence/gradient coefficient vectors (7 x 3)
+  const H *lc;            // [N][kLc] Laplacian neighbour weights (6)
   const H *rhat;          // [N][3]
-  const H *frame;         // [N][9]  local east e, north n and rhat of the column
-  const H *dv;            // [N][14] divergence coefficients of (Ma, Mb): c_j . (e, n) of column j
-  const H *gt;            // [N][12] gradient coefficients in the column's own basis
-  const int32_t *ddi;     // [N][18] two-ring columns (-1 pad)
-  const H *ddw;           // [N][18][2] lap(grad .) weights in the column's own basis
+  const H *frame;         // [N][kFr] local east e, north n and rhat of the column (9)
+  const H *dv;            // [N][kDv] divergence coefficients of (Ma, Mb): c_j . (e, n) of column j (14)
+  const H *gt;            // [N][kGt] gradient coefficients in the column's own basis (6 x 2)
+  const int32_t *ddi;     // [N][18] two-ring columns
+  const H *ddw;           // [N][kDw] lap(grad .) weights in the column's own basis (18 x 2)
   const double *area;     // [N]
   const double *teq;      // [N] Newtonian T_eq; cos(lon - lon_ss) cos(lat) (hot Jupiter); sin(lat) (Held-Suarez)
 
@@ -120,6 +126,42 @@ constexpr int kHq = 4;
 inline int n_blocks_h(const Consts &c, int wpb) { return n_blocks_for(c.N, c.hcpw, wpb); }
 inline long n_waves_h(const Consts &c) { return (c.N + c.hcpw - 1) / c.hcpw; }
 
+// Wavefronts of at most kLdsCols columns stage stencil weights in LDS, in
+// slices of whole KiB (one copy instruction of the wavefront each).
+constexpr int kLdsCols = 16;
+__host__ __device__ inline int wave_bytes(int bytes) { return (bytes + 1023) / 1024 * 1024; }
+// Per wavefront of `cols` columns in phase M (damping and gradient weights);
+// 0: not staged.
+template <typename H>
+inline int hmom_lds(int cols) {
+  return cols <= kLdsCols ? wave_bytes(cols * kDw * (int)sizeof(H)) + wave_bytes(cols * kGt * (int)sizeof(H)) : 0;
+}
+
+// In the slow terms (divergence coefficients, frame) and the large-step
+// kernels (coefficients and Laplacian weights; weights, gradient, frame): g6
+// L32 FP64 slow terms 40.7 -> 39.6 us, large step 112 -> 105, g7 L48 246 ->
+// 238 and 641 -> 620, mixed slow terms 27.6 -> 26.6.  k_large1 stages in FP64
+// only: in the mixed form, where its fields are double and its weights half
+// as long, 89.1 us per large step without and 90.8 with.  Phase V's 14
+// coefficients are not staged: 35.3 -> 34.8 us at g6 L32, but mixed 25.7 ->
+// 26.2, g7 L48 231 -> 233.5, g4 L20 6.0 -> 6.7.
+template <typename H>
+constexpr bool kStageLarge1 = sizeof(H) == sizeof(double);
+template <typename H>
+inline int slow_lds(int cols) {
+  return cols <= kLdsCols ? wave_bytes(cols * kDc * (int)sizeof(H)) + wave_bytes(cols * kFr * (int)sizeof(H)) : 0;
+}
+template <typename H>
+inline int large1_lds(int cols) {
+  return kStageLarge1<H> && cols <= kLdsCols ? wave_bytes(cols * kDc * (int)sizeof(H)) + wave_bytes(cols * kLc * (int)sizeof(H)) : 0;
+}
+template <typename H>
+inline int large2_lds(int cols) {
+  return cols <= kLdsCols ? wave_bytes(cols * kLc * (int)sizeof(H)) + wave_bytes(cols * kGt * (int)sizeof(H)) +
+                                wave_bytes(cols * kFr * (int)sizeof(H))
+                          : 0;
+}
+
 // Launchers.  `wpb` = wavefronts per workgroup (tuned per kernel family).
 // The prognostic state between large steps lives in the *_t buffers; a large
 // step reads them as Phi[t] and leaves its result in the unsuffixed buffers,
@@ -175,8 +217,10 @@ enum class BatchOp { Large, Slow, Hmom, Vert, VertLast };
 
 // Every member of an ensemble in one launch per phase.  arg0/arg1: Slow:
 // from_t; Hmom: div, first | last << 1; Vert: div, first | stage_end << 1.
+// max_cols: the most columns per wavefront of a member, of those that stage
+// their stencil weights in LDS (at most kLdsCols).
 template <typename H>
 void launch_batch(const Planet<H> *P, const int2 *tiles, int n_tiles, int wpb, int parity, BatchOp op,
-                  int arg0, int arg1, hipStream_t s);
+                  int arg0, int arg1, int max_cols, hipStream_t s);
 
 }  // namespace thor

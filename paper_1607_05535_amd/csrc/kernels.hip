@@ -41,14 +41,6 @@
 #ifndef HMOM_OCC_F
 #define HMOM_OCC_F 4
 #endif
-// Two-ring rows of D that k_hmom loads together (all 18: 24.8 us against
-// 25.7 with 6 and 25.4 with 3, FP64 g6 L32).
-#ifndef HMOM_DU
-#define HMOM_DU 18
-#endif
-#ifndef HMOM_PU
-#define HMOM_PU 6
-#endif
 // Neighbours whose rows the slow-terms kernel loads together (1; 2 and 3
 // measured no faster in FP64 and slower in the mixed form at g6 L32).
 #ifndef SLOW_NU
@@ -130,10 +122,39 @@ __device__ __forceinline__ double rcpd(double x) {
 __device__ __forceinline__ void load_nbr(const int32_t *nbr, int col, int nb[6]) {
   const int32_t *p = nbr + (size_t)col * 6;
 #pragma unroll
-  for (int j = 0; j < 6; ++j) {
-    int v = p[j];
-    nb[j] = v < 0 ? col : v;
-  }
+  for (int j = 0; j < 6; ++j) nb[j] = p[j];
+}
+
+// Stencil weights of a wavefront's columns through LDS.  Every lane of a
+// column needs the same weights; read from memory by each lane they were a
+// third of phase M's load instructions and of the bytes its L1 returned.  The
+// columns of a gather-mapping wavefront are consecutive, so the wavefront
+// copies their records (PER values each) straight into its own slice of LDS,
+// 1 KiB per instruction, and reads them back as broadcasts; no barrier, and no
+// wait of its own: the copies are issued before the neighbour ids, which the
+// first gather waits for anyway.  Columns from N up read the array's end.
+// Phase M, weights per lane -> through LDS: g6 L32 FP64 23.4 -> 20.8 us, mixed
+// 11.9 -> 11.0, g7 L48 FP64 167 -> 146, g5 L37 8.4 -> 7.5.
+template <int PER, typename H>
+__device__ __forceinline__ void wave_copy(const H *base, const Consts &c, int first, char *lds) {
+  constexpr int kRec = PER * (int)sizeof(H);
+  static_assert(kRec % 16 == 0, "16-byte pieces");
+  const char *src = reinterpret_cast<const char *>(base) + (size_t)first * kRec;
+  const int bytes = c.hcpw * kRec, last = min(bytes, (c.N - first) * kRec) - 16;
+  const int lane16 = (threadIdx.x & 63) * 16;
+  for (int i = 0; i < bytes; i += 1024)
+    __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void *)(src + min(i + lane16, last)),
+                                     (__attribute__((address_space(3))) void *)(lds + i), 16, 0, 0);
+}
+// The copies (and every load issued so far) have landed.
+__device__ __forceinline__ void wave_copy_wait() {
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+// This wavefront's slice of the workgroup's LDS.
+__device__ __forceinline__ char *wave_lds(char *lds, int per_wave) {
+  return lds + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6) * per_wave);
 }
 
 // ---------------------------------------------------------------------------
@@ -145,16 +166,19 @@ __device__ __forceinline__ void load_nbr(const int32_t *nbr, int col, int nb[6])
 // one column.
 struct HLane {
   int col, lev0, nv;
+  int first, cw;   // the wavefront's first column; this lane's among its hcpw
   bool store;
 };
 
 __device__ __forceinline__ HLane map_hlane(const Consts &c, int lb) {
   HLane r;
   const int lane = threadIdx.x & 63;
-  const int wave = lb * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(lb * (blockDim.x >> 6) + (threadIdx.x >> 6));
   const int cw = lane / c.hlpc;
   const int sub = lane - cw * c.hlpc;
   const int col = wave * c.hcpw + cw;
+  r.first = min(wave * c.hcpw, c.N - 1);
+  r.cw = min(cw, c.hcpw - 1);
   r.lev0 = sub * kHq;
   r.nv = min(kHq, c.L - r.lev0);
   r.store = cw < c.hcpw && col < c.N && r.nv > 0;
@@ -266,39 +290,37 @@ __device__ __forceinline__ void st4(float *p, int nv, const float v[kHq]) {
 }
 
 // Phase M of one lane's kHq levels.  FIRST (the first substep: p* = 0, D
-// of the [t] state) and DD (divergence damping) are compile-time (0 or 1)
-// in the single-state kernel, so each form is straight-line code whose
-// gathers are unrolled (the six p* rows, the 18 two-ring D rows): the
-// scheduler can put the rows of both gathers and of M, S_M in flight
-// together.
+// of the [t] state) and DD (divergence damping) are compile-time, so each
+// form is straight-line code whose gathers are unrolled (the six p* rows,
+// the 18 two-ring D rows: 24.8 us with all 18 together, 25.7 with 6 and 25.4
+// with 3): the scheduler can put the rows of both gathers and of M, S_M in
+// flight together.
 // Bound by the memory system (rows from the last-level cache, and the
-// stencil weights every lane of a column reads), so the momentum and its
+// stencil weights every lane of a column needs), so the momentum and its
 // forcing are two tangent components and every weight a pair instead of a
 // Cartesian vector: 64 + 15 bytes per cell against 88 + 22.5 and 90 load
 // instructions per lane against 108; g6 L32 FP64 33.6 -> 24.8 us, mixed
-// 16.3 -> 12.6, 9 planets together 143 -> 111.  The
-// ensemble kernel passes -1 for both (runtime flags, partly unrolled
-// gathers): there the four forms measured slower (1.31 -> 1.38-1.45 ms per
-// launch over 64 planets).  Every form adds its terms in the same order (j,
-// m ascending), so all give the same bits.
-template <typename H, bool VEC, int FIRST_, int DD_>
+// 16.3 -> 12.6; the weights through LDS (wave_copy) take it to 20.8 and 11.0.
+template <typename H, bool VEC, bool FIRST, bool DD, bool LDSW>
 __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, const HLane &ln, double dtau,
-                                           int flags) {
-  const bool FIRST = FIRST_ < 0 ? (flags & 1) != 0 : FIRST_ != 0, last = (flags & 2) != 0;
-  const bool DD = DD_ < 0 ? c.div_damp != 0 : DD_ != 0;
+                                           int flags, char *lds) {
+  const bool last = (flags & 2) != 0;
   const int col = ln.col, nv = ln.nv;
   const size_t idx = (size_t)col * c.S + ln.lev0;
+  char *const lds_gt = lds + wave_bytes(c.hcpw * kDw * (int)sizeof(H));
+  if (LDSW) {
+    if (DD) wave_copy<kDw>(f.ddw, c, ln.first, lds);
+    if (!FIRST) wave_copy<kGt>(f.gt, c, ln.first, lds_gt);
+  }
   int nb[6];
   if (!FIRST) load_nbr(f.nbr, col, nb);
   int ring[kRing2];
   if (DD) {
     const int32_t *di = f.ddi + (size_t)col * kRing2;
 #pragma unroll
-    for (int m = 0; m < kRing2; ++m) {
-      const int v = di[m];
-      ring[m] = v < 0 ? col : v;
-    }
+    for (int m = 0; m < kRing2; ++m) ring[m] = di[m];
   }
+  if (LDSW) wave_copy_wait();
   H ir[kHq];
 #pragma unroll
   for (int q = 0; q < kHq; ++q) ir[q] = (H)1 / (H)radius_c(c, ln.lev0 + q);
@@ -307,10 +329,10 @@ __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, 
   for (int q = 0; q < kHq; ++q) ga[q] = gb[q] = 0;
   if (!FIRST) {
     // (1/r) sum_j c_j (p*_j - p*_0)
-    const H *gt = f.gt + (size_t)col * 12;
+    const H *gt = LDSW ? reinterpret_cast<const H *>(lds_gt) + ln.cw * kGt : f.gt + (size_t)col * kGt;
     H s0[kHq];
     ld4<VEC>(f.ps + idx, nv, s0);
-#pragma unroll(FIRST_ < 0 ? 2 : HMOM_PU)
+#pragma unroll
     for (int j = 0; j < 6; ++j) {
       H sj[kHq];
       ld4<VEC>(f.ps + (size_t)nb[j] * c.S + ln.lev0, nv, sj);
@@ -334,10 +356,10 @@ __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, 
   if (DD) {
     // -Kd lap(grad D) over the two-ring, D of the current small-step state
     const H *D = FIRST ? f.Dt : f.D;
-    const H *dw = f.ddw + (size_t)col * kRing2 * 2;
+    const H *dw = LDSW ? reinterpret_cast<const H *>(lds) + ln.cw * kDw : f.ddw + (size_t)col * kDw;
     H d0[kHq];
     ld4<VEC>(D + idx, nv, d0);
-#pragma unroll(DD_ < 0 ? 6 : HMOM_DU)
+#pragma unroll
     for (int m = 0; m < kRing2; ++m) {
       H dm[kHq];
       ld4<VEC>(D + (size_t)ring[m] * c.S + ln.lev0, nv, dm);
@@ -356,7 +378,7 @@ __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, 
       ddb[q] *= s;
     }
   }
-  const H *fr = f.frame + (size_t)col * 9;
+  const H *fr = f.frame + (size_t)col * kFr;
   const H dt = (H)dtau;
   H ma[kHq], mb[kHq], sa[kHq], sb[kHq];
   if (FIRST) {
@@ -380,6 +402,7 @@ __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, 
     ma[q] += dt * (-ga[q] + sa[q] + dda[q]);
     mb[q] += dt * (-gb[q] + sb[q] + ddb[q]);
   }
+  if (!ln.store) return;
   st4<VEC>(f.Ma + idx, nv, ma);
   st4<VEC>(f.Mb + idx, nv, mb);
   if (last) {
@@ -396,23 +419,20 @@ __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, 
   }
 }
 
-template <typename H, bool FORMS>
+template <typename H, bool LDSW>
 __device__ __forceinline__ void b_hmom(const Fields<H> &f, const Consts &c, const HLane &ln, double dtau,
-                                       int flags) {
-  if (!ln.store) return;
+                                       int flags, char *lds) {
   // rows of stride S: whole groups of kHq
-  if (!FORMS) {
-    hmom_cells<H, true, -1, -1>(f, c, ln, dtau, flags);
-  } else if (flags & 1) {
+  if (flags & 1) {
     if (c.div_damp)
-      hmom_cells<H, true, 1, 1>(f, c, ln, dtau, flags);
+      hmom_cells<H, true, true, true, LDSW>(f, c, ln, dtau, flags, lds);
     else
-      hmom_cells<H, true, 1, 0>(f, c, ln, dtau, flags);
+      hmom_cells<H, true, true, false, LDSW>(f, c, ln, dtau, flags, lds);
   } else {
     if (c.div_damp)
-      hmom_cells<H, true, 0, 1>(f, c, ln, dtau, flags);
+      hmom_cells<H, true, false, true, LDSW>(f, c, ln, dtau, flags, lds);
     else
-      hmom_cells<H, true, 0, 0>(f, c, ln, dtau, flags);
+      hmom_cells<H, true, false, false, LDSW>(f, c, ln, dtau, flags, lds);
   }
 }
 
@@ -480,7 +500,7 @@ __device__ __forceinline__ void b_vert(const Fields<H> &f, const Consts &c, cons
   const size_t idx = (size_t)col * c.S + lev;
   int nb[6];
   load_nbr(f.nbr, col, nb);
-  const H *dv = f.dv + (size_t)col * 14;
+  const H *dv = f.dv + (size_t)col * kDv;
 
   // horizontal divergences of M and theta_L M
   H drho, dth;
@@ -651,7 +671,7 @@ __device__ __forceinline__ void b_vert2(const Fields<H> &f, const Consts &c, con
   const int lp = ln.lane < 63 ? ln.lane + 1 : 63;
   int nb[6];
   load_nbr(f.nbr, col, nb);
-  const H *dv = f.dv + (size_t)col * 14;
+  const H *dv = f.dv + (size_t)col * kDv;
   const double *rth_in = first ? f.rth_t : f.rth;
   const double *W_in = first ? f.W_t : f.W;
   const double dz = c.dz;
@@ -880,7 +900,7 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
   const int lp = ln.lane < 63 ? ln.lane + 1 : 63;
   int nb[6];
   load_nbr(f.nbr, col, nb);
-  const H *dv = f.dv + (size_t)col * 14;
+  const H *dv = f.dv + (size_t)col * kDv;
 
   // radial factors g+ = r_I(k+1)^2 / (r_C^2 dz), g- = r_I(k)^2 / (r_C^2 dz)
   // and 1 / r_C of cells lev0 - 1 .. lev0 + 3 (index k - lev0 + 1)
@@ -1196,8 +1216,8 @@ __device__ __forceinline__ void b_friction(const Fields<H> &f, const Consts &c, 
 // ---------------------------------------------------------------------------
 // FROM_T: the stage state is Phi[t], whose momentum is Cartesian; else it is
 // the previous stage's, in tangent components.
-template <typename H, bool VEC, bool SHALLOW, int ORD, bool FROM_T>
-__device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, const HLane &ln) {
+template <typename H, bool VEC, bool SHALLOW, int ORD, bool FROM_T, bool LDSW>
+__device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, const HLane &ln, char *lds) {
   const int L = c.L, col = ln.col, nv = ln.nv, lev0 = ln.lev0;
   const int lane = threadIdx.x & 63;
   const int lm = lane > 0 ? lane - 1 : 0;
@@ -1206,10 +1226,17 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
   const double *rho = FROM_T ? f.rho_t : f.rho;
   const double *rth = FROM_T ? f.rth_t : f.rth;
   const double *W = FROM_T ? f.W_t : f.W;
+  constexpr int kC = FROM_T ? kDc : kDv;   // divergence coefficients of the Cartesian or tangent momentum
+  char *const lds_fr = lds + wave_bytes(c.hcpw * kC * (int)sizeof(H));
+  if (LDSW) {
+    wave_copy<kC>(FROM_T ? f.dc : f.dv, c, ln.first, lds);
+    wave_copy<kFr>(f.frame, c, ln.first, lds_fr);
+  }
   int nb[6];
   load_nbr(f.nbr, col, nb);
-  const H *dc = FROM_T ? f.dc + (size_t)col * 21 : f.dv + (size_t)col * 14;
-  const H *fr = f.frame + (size_t)col * 9;
+  if (LDSW) wave_copy_wait();
+  const H *dc = LDSW ? reinterpret_cast<const H *>(lds) + ln.cw * kC : (FROM_T ? f.dc : f.dv) + (size_t)col * kC;
+  const H *fr = LDSW ? reinterpret_cast<const H *>(lds_fr) + ln.cw * kFr : f.frame + (size_t)col * kFr;
   const H rx = fr[6], ry = fr[7], rz = fr[8];
 
   // own column: full momentum m = M + Wbar rhat and velocity m / rho (in the
@@ -1284,7 +1311,7 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
     double wwin[10];
     if (ORD == 3) level_window(wn, lev0, L, lm, lp, wwin);
     ld4<VEC>(rho + nj, nv, rj);
-    const H *fn = f.frame + (size_t)nb[j] * 9;
+    const H *fn = f.frame + (size_t)nb[j] * kFr;
     const H rnx = fn[6], rny = fn[7], rnz = fn[8];
     H tj[kHq];
     if (FROM_T) {
@@ -1432,9 +1459,9 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
   st4<VEC>(f.Gam + idx, nv, gam);
 }
 
-template <typename H, bool FROM_T, bool SHALLOW = false, int ORD = 1>
-__device__ __forceinline__ void b_slow(const Fields<H> &f, const Consts &c, const HLane &ln) {
-  slow_cells<H, true, SHALLOW, ORD, FROM_T>(f, c, ln);   // rows of stride S: whole groups of kHq
+template <typename H, bool FROM_T, bool SHALLOW, int ORD, bool LDSW>
+__device__ __forceinline__ void b_slow(const Fields<H> &f, const Consts &c, const HLane &ln, char *lds) {
+  slow_cells<H, true, SHALLOW, ORD, FROM_T, LDSW>(f, c, ln, lds);   // rows of stride S: whole groups of kHq
 }
 
 // ---------------------------------------------------------------------------
@@ -1558,8 +1585,13 @@ __device__ __forceinline__ void lap4(const T *s, const int nb[6], const H *lc, i
 // from them (rather than reading fields the previous kernel stored); every
 // sum takes its j-th term, so each adds its terms in the same order as a
 // field-by-field pass.
-template <typename H, bool VEC>
-__device__ __forceinline__ void large1_cells(const Fields<H> &f, const Consts &c, const HLane &ln) {
+template <typename H, bool VEC, bool LDSW>
+__device__ __forceinline__ void large1_cells(const Fields<H> &f, const Consts &c, const HLane &ln, char *lds) {
+  char *const lds1 = lds + wave_bytes(c.hcpw * kDc * (int)sizeof(H));
+  if (LDSW) {
+    wave_copy<kDc>(f.dc, c, ln.first, lds);
+    wave_copy<kLc>(f.lc, c, ln.first, lds1);
+  }
   const int L = c.L, lev0 = ln.lev0, nv = ln.nv, col = ln.col;
   const size_t idx = (size_t)col * c.S + lev0;
   const int lane = threadIdx.x & 63;
@@ -1575,8 +1607,9 @@ __device__ __forceinline__ void large1_cells(const Fields<H> &f, const Consts &c
   if (!ln.store) return;
   int nb[6];
   load_nbr(f.nbr, col, nb);
-  const H *dch = f.dc + (size_t)col * 21;
-  const H *lch = f.lc + (size_t)col * 6;
+  if (LDSW) wave_copy_wait();
+  const H *dch = LDSW ? reinterpret_cast<const H *>(lds) + ln.cw * kDc : f.dc + (size_t)col * kDc;
+  const H *lch = LDSW ? reinterpret_cast<const H *>(lds1) + ln.cw * kLc : f.lc + (size_t)col * kLc;
   const double Kd = c.Kd;
   double irc2[kHq];
 #pragma unroll
@@ -1665,8 +1698,15 @@ __device__ __forceinline__ void large1_cells(const Fields<H> &f, const Consts &c
   }
 }
 
-template <typename H, bool VEC>
-__device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c, const HLane &ln) {
+template <typename H, bool VEC, bool LDSW>
+__device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c, const HLane &ln, char *lds) {
+  char *const lds1 = lds + wave_bytes(c.hcpw * kLc * (int)sizeof(H));
+  char *const lds2 = lds1 + wave_bytes(c.hcpw * kGt * (int)sizeof(H));
+  if (LDSW) {
+    wave_copy<kLc>(f.lc, c, ln.first, lds);
+    wave_copy<kGt>(f.gt, c, ln.first, lds1);
+    wave_copy<kFr>(f.frame, c, ln.first, lds2);
+  }
   const int lev0 = ln.lev0, nv = ln.nv, col = ln.col;
   const size_t idx = (size_t)col * c.S + lev0;
   const int lane = threadIdx.x & 63;
@@ -1676,7 +1716,10 @@ __device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c
   if (!ln.store) return;
   int nb[6];
   load_nbr(f.nbr, col, nb);
-  const H *lch = f.lc + (size_t)col * 6;
+  if (LDSW) wave_copy_wait();
+  const H *lch = LDSW ? reinterpret_cast<const H *>(lds) + ln.cw * kLc : f.lc + (size_t)col * kLc;
+  const H *gt = LDSW ? reinterpret_cast<const H *>(lds1) + ln.cw * kGt : f.gt + (size_t)col * kGt;
+  const H *fr = LDSW ? reinterpret_cast<const H *>(lds2) + ln.cw * kFr : f.frame + (size_t)col * kFr;
   double irc2[kHq];
 #pragma unroll
   for (int q = 0; q < kHq; ++q) {
@@ -1697,7 +1740,6 @@ __device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c
     // it below
     H fa[kHq], fb[kHq];
     {
-      const H *gt = f.gt + (size_t)col * 12;
       double p[kHq], ga[kHq], gb[kHq];
       ld4<VEC>(f.p_t + idx, nv, p);
 #pragma unroll
@@ -1721,7 +1763,6 @@ __device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c
         fb[q] = (H)(-(gb[q] * irc));
       }
     }
-    const H *fr = f.frame + (size_t)col * 9;
     double hx[kHq], hy[kHq], hz[kHq];
     lap4<VEC>(f.Xvx, nb, lch, c.S, lev0, nv, idx, hx);
     lap4<VEC>(f.Xvy, nb, lch, c.S, lev0, nv, idx, hy);
@@ -1771,8 +1812,6 @@ __device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c
   }
 THOR_HBODY(large0)
 THOR_HBODY(anel)
-THOR_HBODY(large1)
-THOR_HBODY(large2)
 #undef THOR_HBODY
 
 // Diagnostic field into f.diag (FP64, canonical layout [col][lev]).
@@ -1791,7 +1830,7 @@ __device__ __forceinline__ void b_diag(const Fields<H> &f, const Consts &c, cons
     const double p = c.p_ref * powd(c.Rd * f.rth_t[idx] / c.p_ref, c.gamma);
     out = field == THOR_F_P ? p : p / (rho * c.Rd);
   } else if (field == THOR_F_U || field == THOR_F_V) {
-    const H *e = f.frame + (size_t)col * 9 + (field == THOR_F_U ? 0 : 3);
+    const H *e = f.frame + (size_t)col * kFr + (field == THOR_F_U ? 0 : 3);
     const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
     out = (double)e[0] * vx + (double)e[1] * vy + (double)e[2] * vz;
   } else if (field == THOR_F_W) {
@@ -1980,47 +2019,90 @@ __device__ __forceinline__ void b_import(const Fields<H> &f, const Consts &c, co
   void kb_##NAME(const Planet<H> *P, const int2 *tiles, int parity PARAMS) {             \
     const int2 t = tiles[xcd_block()];                                                    \
     if (t.x < 0) return;                                                                  \
-    const Fields<H> &f = P[t.x].f[parity];                                                \
-    const Consts &c = P[t.x].c;                                                           \
+    const Fields<H> f = P[t.x].f[parity];                                                \
+    const Consts c = P[t.x].c;                                                           \
     b_##NAME(f, c, MAP(c, t.y) ARGS);                                                \
   }
 #define COMMA ,
 THOR_KERNEL(large0, 4, map_hlane, , )
 THOR_KERNEL(anel, 8, map_hlane, , )
-THOR_KERNEL(large1, sizeof(H) == 8 ? LARGE1_OCC_D : LARGE1_OCC_F, map_hlane, , )
-THOR_KERNEL(large2, 4, map_hlane, , )
 THOR_KERNEL(diag, 8, map_lane, COMMA int field, COMMA field)
 THOR_KERNEL(import, 8, map_lane, COMMA const double *blob, COMMA blob)
 THOR_KERNEL(friction, 8, map_hlane, , )
+// LDSW (here and below): the stencil weights go through LDS (wave_copy),
+// `lds_wave` bytes per wavefront.  Not for wavefronts of more than kLdsCols
+// columns (n_lev <= 12): 8 of their slices exceed a workgroup's 64 KiB.
+template <typename H, bool LDSW>
+__global__ __launch_bounds__(kMaxBlock)
+__attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F, sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F)))
+void k_hmom(Fields<H> f, Consts c, int div, int flags, int lds_wave) {
+  extern __shared__ __align__(16) char lds[];
+  b_hmom<H, LDSW>(f, c, map_hlane(c, xcd_block()), c.dt / div, flags, wave_lds(lds, lds_wave));
+}
+// An ensemble's kernels take the planet's pointers and constants by value: by
+// reference they are read again from memory after every copy to LDS and store
+// (9 planets: phase M 129 -> 94 us, slow terms 163 -> 144, large1 178 -> 157,
+// large2 183 -> 173).  Phase V, which has no copy, keeps the reference (126 us
+// against 134).
 template <typename H>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F, sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F)))
-void k_hmom(Fields<H> f, Consts c, int div, int flags) {
-  b_hmom<H, true>(f, c, map_hlane(c, xcd_block()), c.dt / div, flags);
-}
-template <typename H>
-__global__ __launch_bounds__(kMaxBlock)
-__attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F, sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F)))
-void kb_hmom(const Planet<H> *P, const int2 *tiles, int parity, int div, int flags) {
+void kb_hmom(const Planet<H> *P, const int2 *tiles, int parity, int div, int flags, int lds_wave) {
+  extern __shared__ __align__(16) char lds[];
   const int2 t = tiles[xcd_block()];
   if (t.x < 0) return;
-  const Fields<H> &f = P[t.x].f[parity];
-  const Consts &c = P[t.x].c;
-  b_hmom<H, false>(f, c, map_hlane(c, t.y), c.dt / div, flags);
+  const Fields<H> f = P[t.x].f[parity];
+  const Consts c = P[t.x].c;
+  if (c.hcpw <= kLdsCols)
+    b_hmom<H, true>(f, c, map_hlane(c, t.y), c.dt / div, flags, wave_lds(lds, lds_wave));
+  else
+    b_hmom<H, false>(f, c, map_hlane(c, t.y), c.dt / div, flags, nullptr);
+}
+// STAGED: whether wavefronts of at most kLdsCols columns stage their weights.
+#define THOR_LARGE(NAME, OCC, STAGED)                                                          \
+  template <typename H, bool LDSW>                                                            \
+  __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(OCC)))           \
+  void k_##NAME(Fields<H> f, Consts c, int lds_wave) {                                        \
+    extern __shared__ __align__(16) char lds[];                                               \
+    NAME##_cells<H, true, LDSW>(f, c, map_hlane(c, xcd_block()), wave_lds(lds, lds_wave));    \
+  }                                                                                           \
+  template <typename H>                                                                       \
+  __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(OCC)))           \
+  void kb_##NAME(const Planet<H> *P, const int2 *tiles, int parity, int lds_wave) {           \
+    extern __shared__ __align__(16) char lds[];                                               \
+    const int2 t = tiles[xcd_block()];                                                        \
+    if (t.x < 0) return;                                                                      \
+    const Fields<H> f = P[t.x].f[parity];                                                    \
+    const Consts c = P[t.x].c;                                                               \
+    if constexpr (STAGED) {                                                                   \
+      if (c.hcpw <= kLdsCols) {                                                               \
+        NAME##_cells<H, true, true>(f, c, map_hlane(c, t.y), wave_lds(lds, lds_wave));        \
+        return;                                                                               \
+      }                                                                                       \
+    }                                                                                         \
+    NAME##_cells<H, true, false>(f, c, map_hlane(c, t.y), nullptr);                           \
+  }
+THOR_LARGE(large1, sizeof(H) == 8 ? LARGE1_OCC_D : LARGE1_OCC_F, kStageLarge1<H>)
+THOR_LARGE(large2, 4, true)
+#undef THOR_LARGE
+template <typename H, bool FROM_T, bool LDSW>
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? 2 : 4)))
+void k_slow(Fields<H> f, Consts c, int lds_wave) {
+  extern __shared__ __align__(16) char lds[];
+  b_slow<H, FROM_T, false, 1, LDSW>(f, c, map_hlane(c, xcd_block()), wave_lds(lds, lds_wave));
 }
 template <typename H, bool FROM_T>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? 2 : 4)))
-void k_slow(Fields<H> f, Consts c) {
-  b_slow<H, FROM_T>(f, c, map_hlane(c, xcd_block()));
-}
-template <typename H, bool FROM_T>
-__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? 2 : 4)))
-void kb_slow(const Planet<H> *P, const int2 *tiles, int parity) {
+void kb_slow(const Planet<H> *P, const int2 *tiles, int parity, int lds_wave) {
+  extern __shared__ __align__(16) char lds[];
   const int2 t = tiles[xcd_block()];
   if (t.x < 0) return;
-  const Fields<H> &f = P[t.x].f[parity];
-  const Consts &c = P[t.x].c;
-  b_slow<H, FROM_T>(f, c, map_hlane(c, t.y));
+  const Fields<H> f = P[t.x].f[parity];
+  const Consts c = P[t.x].c;
+  if (c.hcpw <= kLdsCols)
+    b_slow<H, FROM_T, false, 1, true>(f, c, map_hlane(c, t.y), wave_lds(lds, lds_wave));
+  else
+    b_slow<H, FROM_T, false, 1, false>(f, c, map_hlane(c, t.y), nullptr);
 }
 // slow terms of the shallow-atmosphere form and of the cubic vertical
 // interpolation (single states only)
@@ -2028,7 +2110,7 @@ template <typename H, bool FROM_T, bool SHALLOW, int ORD>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? (SHALLOW && ORD == 3 ? 1 : 2) : (SHALLOW && ORD == 3 ? 2 : 3))))
 void k_slow_var(Fields<H> f, Consts c) {
-  b_slow<H, FROM_T, SHALLOW, ORD>(f, c, map_hlane(c, xcd_block()));
+  b_slow<H, FROM_T, SHALLOW, ORD, false>(f, c, map_hlane(c, xcd_block()), nullptr);
 }
 template <typename H, bool LAST>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? 4 : (LAST ? 5 : 6))))
@@ -2070,17 +2152,26 @@ void kb_vert(const Planet<H> *P, const int2 *tiles, int parity, int div, int fla
 // One dispatch; with events (timing) they are recorded by the dispatch
 // itself, at the kernel's start and end.
 template <typename K, typename... Args>
-void dispatch(K kernel, dim3 g, dim3 b, hipStream_t s, hipEvent_t e0, hipEvent_t e1, Args... args) {
+void dispatch_lds(K kernel, dim3 g, dim3 b, unsigned lds, hipStream_t s, hipEvent_t e0, hipEvent_t e1, Args... args) {
   if (e0 || e1)
-    hipExtLaunchKernelGGL(kernel, g, b, 0, s, e0, e1, 0, args...);
+    hipExtLaunchKernelGGL(kernel, g, b, lds, s, e0, e1, 0, args...);
   else
-    hipLaunchKernelGGL(kernel, g, b, 0, s, args...);
+    hipLaunchKernelGGL(kernel, g, b, lds, s, args...);
+}
+template <typename K, typename... Args>
+void dispatch(K kernel, dim3 g, dim3 b, hipStream_t s, hipEvent_t e0, hipEvent_t e1, Args... args) {
+  dispatch_lds(kernel, g, b, 0, s, e0, e1, args...);
 }
 
 template <typename H>
 void launch_hmom(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, bool last, hipStream_t s,
                  hipEvent_t ev0, hipEvent_t ev1) {
-  dispatch(k_hmom<H>, dim3(n_blocks_h(c, wpb)), dim3(64 * wpb), s, ev0, ev1, f, c, div, (int)first | (int)last << 1);
+  const dim3 g(n_blocks_h(c, wpb)), b(64 * wpb);
+  const int lds = hmom_lds<H>(c.hcpw), flags = (int)first | (int)last << 1;
+  if (lds)
+    dispatch_lds(k_hmom<H, true>, g, b, lds * wpb, s, ev0, ev1, f, c, div, flags, lds);
+  else
+    dispatch(k_hmom<H, false>, g, b, s, ev0, ev1, f, c, div, flags, 0);
 }
 template <typename H>
 void launch_vert(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, bool stage_end, bool physics,
@@ -2116,30 +2207,41 @@ void launch_vert(const Fields<H> &f, const Consts &c, int wpb, int div, bool fir
   }
 }
 template <typename H, bool FROM_T>
-void dispatch_slow(const Fields<H> &f, const Consts &c, dim3 g, dim3 b, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+void dispatch_slow(const Fields<H> &f, const Consts &c, dim3 g, dim3 b, int wpb, hipStream_t s, hipEvent_t ev0,
+                   hipEvent_t ev1) {
+  const int lds = slow_lds<H>(c.hcpw);
   if (c.vorder == 3 && c.shallow)
     dispatch(k_slow_var<H, FROM_T, true, 3>, g, b, s, ev0, ev1, f, c);
   else if (c.vorder == 3)
     dispatch(k_slow_var<H, FROM_T, false, 3>, g, b, s, ev0, ev1, f, c);
   else if (c.shallow)
     dispatch(k_slow_var<H, FROM_T, true, 1>, g, b, s, ev0, ev1, f, c);
+  else if (lds)
+    dispatch_lds(k_slow<H, FROM_T, true>, g, b, lds * wpb, s, ev0, ev1, f, c, lds);
   else
-    dispatch(k_slow<H, FROM_T>, g, b, s, ev0, ev1, f, c);
+    dispatch(k_slow<H, FROM_T, false>, g, b, s, ev0, ev1, f, c, 0);
 }
 template <typename H>
 void launch_slow(const Fields<H> &f, const Consts &c, int wpb, bool from_t, hipStream_t s, hipEvent_t ev0,
                  hipEvent_t ev1) {
   const dim3 g(n_blocks_h(c, wpb)), b(64 * wpb);
-  if (from_t) dispatch_slow<H, true>(f, c, g, b, s, ev0, ev1);
-  else dispatch_slow<H, false>(f, c, g, b, s, ev0, ev1);
+  if (from_t) dispatch_slow<H, true>(f, c, g, b, wpb, s, ev0, ev1);
+  else dispatch_slow<H, false>(f, c, g, b, wpb, s, ev0, ev1);
 }
 template <typename H>
 void launch_large(const Fields<H> &f, const Consts &c, int wpb, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const dim3 g(n_blocks_h(c, wpb)), b(64 * wpb);
   dispatch(k_large0<H>, g, b, s, ev0, nullptr, f, c);
   if (c.anelastic) dispatch(k_anel<H>, g, b, s, nullptr, nullptr, f, c);
-  dispatch(k_large1<H>, g, b, s, nullptr, nullptr, f, c);
-  dispatch(k_large2<H>, g, b, s, nullptr, ev1, f, c);
+  const int l1 = large1_lds<H>(c.hcpw);
+  if constexpr (kStageLarge1<H>) {
+    if (l1) dispatch_lds(k_large1<H, true>, g, b, l1 * wpb, s, nullptr, nullptr, f, c, l1);
+  }
+  if (!l1) dispatch(k_large1<H, false>, g, b, s, nullptr, nullptr, f, c, 0);
+  if (const int l2 = large2_lds<H>(c.hcpw))
+    dispatch_lds(k_large2<H, true>, g, b, l2 * wpb, s, nullptr, ev1, f, c, l2);
+  else
+    dispatch(k_large2<H, false>, g, b, s, nullptr, ev1, f, c, 0);
 }
 template <typename H>
 void launch_diag_field(const Fields<H> &f, const Consts &c, int field, hipStream_t s) {
@@ -2174,20 +2276,22 @@ void launch_to_state(const Fields<H> &f, const Consts &c, const double *blob, hi
 // workgroups of `wpb` wavefronts.
 template <typename H>
 void launch_batch(const Planet<H> *P, const int2 *tiles, int n_tiles, int wpb, int parity, BatchOp op,
-                  int arg0, int arg1, hipStream_t s) {
+                  int arg0, int arg1, int max_cols, hipStream_t s) {
   const dim3 g(n_tiles), b(64 * wpb);
+  const int lds = hmom_lds<H>(max_cols), slds = slow_lds<H>(max_cols), l1 = large1_lds<H>(max_cols),
+            l2 = large2_lds<H>(max_cols);
   switch (op) {
     case BatchOp::Large:
       hipLaunchKernelGGL(kb_large0<H>, g, b, 0, s, P, tiles, parity);
-      hipLaunchKernelGGL(kb_large1<H>, g, b, 0, s, P, tiles, parity);
-      hipLaunchKernelGGL(kb_large2<H>, g, b, 0, s, P, tiles, parity);
+      hipLaunchKernelGGL(kb_large1<H>, g, b, l1 * wpb, s, P, tiles, parity, l1);
+      hipLaunchKernelGGL(kb_large2<H>, g, b, l2 * wpb, s, P, tiles, parity, l2);
       break;
     case BatchOp::Slow:
-      if (arg0) hipLaunchKernelGGL((kb_slow<H, true>), g, b, 0, s, P, tiles, parity);
-      else hipLaunchKernelGGL((kb_slow<H, false>), g, b, 0, s, P, tiles, parity);
+      if (arg0) hipLaunchKernelGGL((kb_slow<H, true>), g, b, slds * wpb, s, P, tiles, parity, slds);
+      else hipLaunchKernelGGL((kb_slow<H, false>), g, b, slds * wpb, s, P, tiles, parity, slds);
       break;
     case BatchOp::Hmom:
-      hipLaunchKernelGGL(kb_hmom<H>, g, b, 0, s, P, tiles, parity, arg0, arg1);
+      hipLaunchKernelGGL(kb_hmom<H>, g, b, lds * wpb, s, P, tiles, parity, arg0, arg1, lds);
       break;
     case BatchOp::Vert:
       hipLaunchKernelGGL((kb_vert<H, false>), g, b, 0, s, P, tiles, parity, arg0, arg1);
@@ -2214,7 +2318,7 @@ void launch_batch(const Planet<H> *P, const int2 *tiles, int n_tiles, int wpb, i
   template void launch_energy<H>(const Fields<H> &, const Consts &, int, double *, hipStream_t, int *); \
   template void launch_fixer<H>(const Fields<H> &, const Consts &, hipStream_t);                     \
   template void launch_batch<H>(const Planet<H> *, const int2 *, int, int, int, BatchOp, int, int,  \
-                                hipStream_t);
+                                int, hipStream_t);
 
 THOR_INSTANTIATE(double)
 THOR_INSTANTIATE(float)

@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kZthreads) void k_zinterp(Fields<H> f, Consts c, co
     const size_t idx = (size_t)col * c.S + lev;   // state row stride
     const double rho = f.rho_t[idx], rth = f.rth_t[idx];
     const double p = c.p_ref * powd(c.Rd * rth / c.p_ref, c.gamma);
-    const H *fr = f.frame + (size_t)col * 9;
+    const H *fr = f.frame + (size_t)col * kFr;
     const double e[2] = {fr[0], fr[1]}, n[3] = {fr[3], fr[4], fr[5]};
     const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
     double *o = zs + lev * kZpitch + cb;

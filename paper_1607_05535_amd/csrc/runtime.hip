@@ -57,14 +57,14 @@ template <typename H>
 void carve(Carver &cv, Fields<H> &f, size_t N, size_t L, bool anelastic) {
   const size_t NL = N * row_stride(L), NLc = N * L;
   f.nbr = cv.take<int32_t>(N * 6);
-  f.dc = cv.take<H>(N * 21);
-  f.lc = cv.take<H>(N * 6);
+  f.dc = cv.take<H>(N * kDc);
+  f.lc = cv.take<H>(N * kLc);
   f.rhat = cv.take<H>(N * 3);
-  f.frame = cv.take<H>(N * 9);
-  f.dv = cv.take<H>(N * 14);
-  f.gt = cv.take<H>(N * 12);
+  f.frame = cv.take<H>(N * kFr);
+  f.dv = cv.take<H>(N * kDv);
+  f.gt = cv.take<H>(N * kGt);
   f.ddi = cv.take<int32_t>(N * kRing2);
-  f.ddw = cv.take<H>(N * kRing2 * 2);
+  f.ddw = cv.take<H>(N * kDw);
   f.area = cv.take<double>(N);
   f.teq = cv.take<double>(N);
   f.rho = cv.take<double>(NL);
@@ -224,6 +224,12 @@ struct HostArray {
       ptr = own.data();
     }
   }
+  // records of `have` values, zero-padded to `want`
+  HostArray(const std::vector<double> &v, size_t have, size_t want) : own(v.size() / have * want, (H)0), n(own.size()) {
+    for (size_t i = 0; i < v.size() / have; ++i)
+      for (size_t k = 0; k < have; ++k) own[i * want + k] = (H)v[i * have + k];
+    ptr = own.data();
+  }
   const H *data() const { return ptr; }
   size_t size() const { return n; }
 };
@@ -240,7 +246,8 @@ int upload(thor_state *s, const Grid &G, const thor_planet *pl, const thor_verti
   const Fields<H> &f = fp[0];
   const Consts &c = s->c;
   // geometry
-  const HostArray<H> dc(G.div_coef), lc(G.lap_coef), frame(G.frame), dv(G.div_t), gt(G.grad_t), ddw(G.dd_t);
+  const HostArray<H> dc(G.div_coef, 21, kDc), lc(G.lap_coef, 6, kLc), frame(G.frame), dv(G.div_t), gt(G.grad_t),
+      ddw(G.dd_t);
   std::vector<H> rh(N * 3);
   std::vector<double> teq(N);
   for (size_t i = 0; i < N; ++i) {
@@ -285,14 +292,14 @@ int upload(thor_state *s, const Grid &G, const thor_planet *pl, const thor_verti
       rth[i * S + k] = rth[i * S + L - 1];
     }
   hipStream_t st = s->stream;
-  bool ok = hip_ok(hipMemcpyAsync((void *)f.nbr, G.nbr.data(), N * 6 * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy nbr") &&
+  bool ok = hip_ok(hipMemcpyAsync((void *)f.nbr, G.nbr_own.data(), N * 6 * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy nbr") &&
             hip_ok(hipMemcpyAsync((void *)f.dc, dc.data(), dc.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy dc") &&
             hip_ok(hipMemcpyAsync((void *)f.lc, lc.data(), lc.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy lc") &&
             hip_ok(hipMemcpyAsync((void *)f.rhat, rh.data(), rh.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy rhat") &&
             hip_ok(hipMemcpyAsync((void *)f.frame, frame.data(), frame.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy frame") &&
             hip_ok(hipMemcpyAsync((void *)f.dv, dv.data(), dv.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy dv") &&
             hip_ok(hipMemcpyAsync((void *)f.gt, gt.data(), gt.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy gt") &&
-            hip_ok(hipMemcpyAsync((void *)f.ddi, G.dd_idx.data(), G.dd_idx.size() * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy ddi") &&
+            hip_ok(hipMemcpyAsync((void *)f.ddi, G.dd_own.data(), G.dd_own.size() * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy ddi") &&
             hip_ok(hipMemcpyAsync((void *)f.ddw, ddw.data(), ddw.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy ddw") &&
             hip_ok(hipMemcpyAsync((void *)f.area, G.area.data(), N * sizeof(double), hipMemcpyHostToDevice, st), "copy area") &&
             hip_ok(hipMemcpyAsync((void *)f.teq, teq.data(), N * sizeof(double), hipMemcpyHostToDevice, st), "copy teq") &&
@@ -786,6 +793,7 @@ struct thor_batch {
   size_t tile_cap = 0;             // entries reserved per tile table
   int n_tiles[FAM_COUNT] = {0, 0, 0, 0};
   int wpb[FAM_COUNT] = {1, 1, 1, 1};   // set by default_wpb
+  int max_cols = 0;                // most columns per wavefront of a member, of those up to kLdsCols
   int parity = 0;
   hipStream_t stream = nullptr;
   hipStream_t cap_stream = nullptr;
@@ -842,7 +850,7 @@ void enqueue_batch_step(thor_batch *b, int n, int parity, hipStream_t st) {
   const size_t pb = planet_table_bytes<H>(b->n);
   const Planet<H> *P = planet_table<H>(b);
   auto L = [&](int fam, BatchOp op, int a0, int a1) {
-    launch_batch<H>(P, tile_table(b, fam, pb), b->n_tiles[fam], b->wpb[fam], parity, op, a0, a1, st);
+    launch_batch<H>(P, tile_table(b, fam, pb), b->n_tiles[fam], b->wpb[fam], parity, op, a0, a1, b->max_cols, st);
   };
   L(FAM_LARGE, BatchOp::Large, 0, 0);
   const int ns[3] = {1, n / 2, n};
@@ -935,7 +943,10 @@ int thor_batch_init(int n, const thor_grid *const *grids, const thor_planet *pl,
     off += align256(bytes);
   }
   long waves = 0;
-  for (auto m : b->members) waves += n_waves_h(m->c);
+  for (auto m : b->members) {
+    waves += n_waves_h(m->c);
+    if (m->c.hcpw <= kLdsCols) b->max_cols = std::max(b->max_cols, m->c.hcpw);
+  }
   default_wpb(waves, b->precision == THOR_MIXED, true, b->wpb);
   b->tables = base + off;
   b->tile_cap = batch_tile_cap(n, grids, v);

@@ -45,6 +45,27 @@ def test_members_equal_single_runs_bitwise(precision):
         assert np.array_equal(got, ref), w.name
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("levels", [(12, 13), (16, 17), (1, 3), (64, 5)])
+def test_members_equal_single_runs_where_weight_staging_changes(levels, precision):
+    """Stencil weights go through LDS for at most 16 columns per wavefront
+    (13 levels and up): members on both sides of that line in one launch."""
+    from paper_1607_05535_amd import thor
+    ws = workloads.ensemble(n=4, seed=3, glevels=(2, 3), levels=levels)
+    for k, w in enumerate(ws):
+        w.n_lev = levels[k % 2]
+        w.z_top *= min(1.0, w.n_lev / 8)
+    grids = _grids(ws)
+    members = [thor.structs_from_workload(w, precision) for w in ws]
+    b = thor.Batch(grids, members)
+    b.step(2, 4)
+    for i, (w, m) in enumerate(zip(ws, members)):
+        st = thor.State(grids[i], *m)
+        st.step(2, 4)
+        ref, rc = st.export()
+        assert rc == 0 and np.array_equal(b.members[i].export()[0], ref), (w.name, w.n_lev)
+
+
 def test_member_cannot_be_stepped_alone():
     from paper_1607_05535_amd import thor
     ws = _small_ensemble()[:2]
