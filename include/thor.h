@@ -335,10 +335,11 @@ int thor_autotune(thor_state *s, int n_acoustic, int *wpb_out);
  * (ceil(n_lev / 2) lanes per column) or 4 levels per lane (ceil(n_lev / 4)
  * lanes per column, 16-byte row accesses, two in-lane steps of odd-even
  * reduction before the cyclic reduction across lanes), the same arithmetic
- * either way up to rounding.  The default is 4 (1 with lagrange_order 3),
- * the ensemble kernels' mapping, so that a planet run alone equals its
- * ensemble member bitwise; thor_autotune may choose another (then the two
- * agree to rounding).
+ * either way up to rounding.  The default is 4, the ensemble kernels'
+ * mapping, so that a planet run alone equals its ensemble member bitwise;
+ * thor_autotune may choose another (then the two agree to rounding).  With
+ * lagrange_order 3 phase V has one mapping, four levels per lane with the
+ * cubic interface theta, and the only value taken here is 1, which keeps it.
  * EINVAL: nl not 1, 2 or 4; 2 where n_lev <= 32; 2 or 4 where
  * lagrange_order is 3; 1 or 2 with the anelastic switch.  Synchronises. */
 int thor_set_vert_levels_per_lane(thor_state *s, int nl);

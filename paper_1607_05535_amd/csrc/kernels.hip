@@ -464,7 +464,7 @@ __device__ __forceinline__ double physics_p(const Consts &c, const double *teq, 
     if (z <= zs) {
       const double a = c.hj_lapse * (z - zs) / 2.0;
       const double tv = c.hj_Tsurf - c.hj_lapse * (zs + (z - zs) / 2.0) + sqrt(a * a + c.hj_dTstrat * c.hj_dTstrat);
-      const double beta = sin(M_PI * (p / ps - c.hj_sstrat) / (2.0 * (1.0 - c.hj_sstrat)));
+      const double beta = sinpi((p / ps - c.hj_sstrat) / (2.0 * (1.0 - c.hj_sstrat)));
       Teq = tv + beta * c.hj_dTep * teq[col];
     } else {
       Teq = c.hj_Tsurf - c.hj_lapse * zs + c.hj_dTstrat;
@@ -479,7 +479,8 @@ __device__ __forceinline__ double physics_p(const Consts &c, const double *teq, 
     const double ramp = fmax(0.0, (sigma - c.hs_sb) / (1.0 - c.hs_sb));
     const double KT = c.hs_ka + (c.hs_ks - c.hs_ka) * ramp * c2 * c2;
     const double x = p / c.hs_pstar;
-    const double Teq = fmax(c.hs_Tmin, (c.hs_Ttop - c.hs_dTy * s2 - c.hs_dthz * log(x) * c2) * pow(x, c.Rd / c.Cp));
+    const double lx = powd_ln(x);   // serves ln x and x^(Rd / Cp)
+    const double Teq = fmax(c.hs_Tmin, (c.hs_Ttop - c.hs_dTy * s2 - c.hs_dthz * lx * c2) * powd_exp(c.Rd / c.Cp * lx));
     const double kt = c.dt * KT;
     const double Tn = (T + kt * Teq) / (1.0 + kt);
     p = rho * c.Rd * Tn;
@@ -493,7 +494,7 @@ __device__ __forceinline__ double physics_p(const Consts &c, const double *teq, 
 // combined), its solution, and the density / rho-theta updates with the new
 // W; pressure from the nonlinear equation of state (Eq. theta_to_p).
 // ---------------------------------------------------------------------------
-template <typename H, bool LAST, int ORD = 1>
+template <typename H, bool LAST>
 __device__ __forceinline__ void b_vert(const Fields<H> &f, const Consts &c, const Lane &ln, double dtau, int flags) {
   const bool first = (flags & 1) != 0, end = (flags & 2) != 0;
   const int L = c.L, lev = ln.lev, col = ln.col;
@@ -538,19 +539,7 @@ __device__ __forceinline__ void b_vert(const Fields<H> &f, const Consts &c, cons
 
   const int lm = ln.lane > 0 ? ln.lane - 1 : 0;
   const int lp = ln.lane < 63 ? ln.lane + 1 : 63;
-  double thI;   // theta at interface lev
-  if (ORD == 3) {
-    double tw[6];   // centres lev-3 .. lev+2 of the column (0 outside it)
-#pragma unroll
-    for (int o = -3; o <= 2; ++o) {
-      const int src = min(max(ln.lane + o, 0), 63);
-      const double v = shfl(thC, src);
-      tw[o + 3] = (lev + o < 0 || lev + o >= L) ? 0.0 : v;
-    }
-    thI = cubic_c2i(tw, lev, L);
-  } else {
-    thI = 0.5 * (shfl(thC, lm) + thC);
-  }
+  const double thI = 0.5 * (shfl(thC, lm) + thC);   // theta at interface lev
   const double thI_m = shfl(thI, lm);
   const double thI_p = shfl(thI, lp);
   const double gam_m = shfl(gam, lm);
@@ -886,11 +875,15 @@ __device__ __forceinline__ VLane map_vlane(const Consts &c, int lb) {
 // rho[t]: g6 L32 FP64 43.3 -> 37.4 us, mixed 29.2 -> 27.6, g5 L37 FP64 16.4
 // -> 15.2.
 //
+// ORD = 3 (cubic vertical interpolation): theta at the interfaces from the
+// four nearest centres; with one level per lane, as before, a wavefront held
+// one column of 33 levels and phase V took 26.4 us at g5 L33 against 14.4 here.
+//
 // ANEL (the anelastic switch): the density update takes the divergence of
 // the reference-density mass flux, fC M horizontally and fI W vertically,
 // and the buoyancy terms of the tridiagonal the matching fI W; the
 // divergence-damping D keeps the plain momentum divergence.
-template <typename H, bool LAST, bool ANEL = false>
+template <typename H, bool LAST, bool ANEL = false, int ORD = 1>
 __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, const VLane &ln, double dtau,
                                         int flags) {
   const bool first = (flags & 1) != 0, end = (flags & 2) != 0;
@@ -1013,11 +1006,19 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
   }
 
   // theta at the lane's interfaces and at interface lev0 + 4 (lane above)
+  // (interface 0 only meets W = 0)
   double thI[kHq];
-  const double thC_dn = shfl(thC[3], lm);
-  thI[0] = ln.sub == 0 ? thC[0] : 0.5 * (thC_dn + thC[0]);   // interface 0 only meets W = 0
+  if (ORD == 3) {
+    double win[10];
+    level_window(thC, lev0, L, lm, lp, win);
 #pragma unroll
-  for (int q = 1; q < kHq; ++q) thI[q] = 0.5 * (thC[q - 1] + thC[q]);
+    for (int q = 0; q < kHq; ++q) thI[q] = cubic_c2i(win + q, lev0 + q, L);
+  } else {
+    const double thC_dn = shfl(thC[3], lm);
+    thI[0] = ln.sub == 0 ? thC[0] : 0.5 * (thC_dn + thC[0]);
+#pragma unroll
+    for (int q = 1; q < kHq; ++q) thI[q] = 0.5 * (thC[q - 1] + thC[q]);
+  }
   const double thI_up = shfl(thI[0], lp);
   const double gam_m = shfl(gam[3], lm), phs_m = shfl(phs[3], lm), rhs_m = shfl(rhs[3], lm);
 
@@ -2124,16 +2125,10 @@ void k_vert2(Fields<H> f, Consts c, int div, int flags) {
   b_vert2<H, LAST>(f, c, map_lane2(c, xcd_block()), c.dt / div, flags);
 }
 // phase V on the gather mapping (kHq levels per lane)
-template <typename H, bool LAST, bool ANEL = false>
+template <typename H, bool LAST, bool ANEL = false, int ORD = 1>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(VERT4_OCC)))
 void k_vert4(Fields<H> f, Consts c, int div, int flags) {
-  b_vert4<H, LAST, ANEL>(f, c, map_vlane(c, xcd_block()), c.dt / div, flags);
-}
-// phase V with the cubic interface theta (single states only)
-template <typename H, bool LAST>
-__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? 3 : 4)))
-void k_vert3(Fields<H> f, Consts c, int div, int flags) {
-  b_vert<H, LAST, 3>(f, c, map_lane(c, xcd_block()), c.dt / div, flags);
+  b_vert4<H, LAST, ANEL, ORD>(f, c, map_vlane(c, xcd_block()), c.dt / div, flags);
 }
 template <typename H, bool LAST>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(VERT4_OCC)))
@@ -2173,38 +2168,33 @@ void launch_hmom(const Fields<H> &f, const Consts &c, int wpb, int div, bool fir
   else
     dispatch(k_hmom<H, false>, g, b, s, ev0, ev1, f, c, div, flags, 0);
 }
+template <typename H, bool LAST>
+void dispatch_vert(const Fields<H> &f, const Consts &c, int wpb, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1,
+                   int div, int flags) {
+  const dim3 b(64 * wpb);
+  if (c.anelastic)
+    dispatch(k_vert4<H, LAST, true>, dim3(n_blocks_h(c, wpb)), b, s, ev0, ev1, f, c, div, flags);
+  else if (c.vorder == 3)
+    dispatch(k_vert4<H, LAST, false, 3>, dim3(n_blocks_h(c, wpb)), b, s, ev0, ev1, f, c, div, flags);
+  else if (c.vnl == 4)
+    dispatch(k_vert4<H, LAST>, dim3(n_blocks_h(c, wpb)), b, s, ev0, ev1, f, c, div, flags);
+  else if (c.vnl == 2)
+    dispatch(k_vert2<H, LAST>, dim3(n_blocks_for(c.N, c.vcpw, wpb)), b, s, ev0, ev1, f, c, div, flags);
+  else
+    dispatch(k_vert<H, LAST>, dim3(n_blocks(c, wpb)), b, s, ev0, ev1, f, c, div, flags);
+}
 template <typename H>
 void launch_vert(const Fields<H> &f, const Consts &c, int wpb, int div, bool first, bool stage_end, bool physics,
                  hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const int flags = (int)first | (int)stage_end << 1;
-  const dim3 g(c.vnl == 4 ? n_blocks_h(c, wpb) : c.vnl == 2 ? n_blocks_for(c.N, c.vcpw, wpb) : n_blocks(c, wpb)),
-      b(64 * wpb);
-  const bool fr = physics && c.forcing == THOR_FORCING_HELD_SUAREZ;
-  hipEvent_t e1 = fr ? nullptr : ev1;   // with the friction kernel, the family ends with it
-  if (physics) {
-    if (c.anelastic)
-      dispatch(k_vert4<H, true, true>, g, b, s, ev0, e1, f, c, div, flags);
-    else if (c.vnl == 4)
-      dispatch(k_vert4<H, true>, g, b, s, ev0, e1, f, c, div, flags);
-    else if (c.vnl == 2)
-      dispatch(k_vert2<H, true>, g, b, s, ev0, e1, f, c, div, flags);
-    else if (c.vorder == 3)
-      dispatch(k_vert3<H, true>, g, b, s, ev0, e1, f, c, div, flags);
-    else
-      dispatch(k_vert<H, true>, g, b, s, ev0, e1, f, c, div, flags);
-    if (fr) dispatch(k_friction<H>, dim3(n_blocks_h(c, 4)), dim3(256), s, nullptr, ev1, f, c);
-  } else {
-    if (c.anelastic)
-      dispatch(k_vert4<H, false, true>, g, b, s, ev0, ev1, f, c, div, flags);
-    else if (c.vnl == 4)
-      dispatch(k_vert4<H, false>, g, b, s, ev0, ev1, f, c, div, flags);
-    else if (c.vnl == 2)
-      dispatch(k_vert2<H, false>, g, b, s, ev0, ev1, f, c, div, flags);
-    else if (c.vorder == 3)
-      dispatch(k_vert3<H, false>, g, b, s, ev0, ev1, f, c, div, flags);
-    else
-      dispatch(k_vert<H, false>, g, b, s, ev0, ev1, f, c, div, flags);
+  if (!physics) {
+    dispatch_vert<H, false>(f, c, wpb, s, ev0, ev1, div, flags);
+    return;
   }
+  // with the friction kernel, the family ends with it
+  const bool fr = c.forcing == THOR_FORCING_HELD_SUAREZ;
+  dispatch_vert<H, true>(f, c, wpb, s, ev0, fr ? nullptr : ev1, div, flags);
+  if (fr) dispatch(k_friction<H>, dim3(n_blocks_h(c, 4)), dim3(256), s, nullptr, ev1, f, c);
 }
 template <typename H, bool FROM_T>
 void dispatch_slow(const Fields<H> &f, const Consts &c, dim3 g, dim3 b, int wpb, hipStream_t s, hipEvent_t ev0,

@@ -571,8 +571,8 @@ int thor_state_init(const thor_grid *g, const thor_planet *pl, const thor_vertic
   c.anelastic = num->anelastic;
   // phase V: four levels per lane (the gather mapping), as in the ensemble
   // kernels, so that a planet's results equal its ensemble member's bitwise;
-  // with cubic interpolation one level per lane.  thor_autotune may choose
-  // another mapping.
+  // thor_autotune may choose another mapping.  (Cubic interpolation has the
+  // four-level kernel only, whatever vnl holds.)
   c.vnl = c.vorder == 1 ? 4 : 1;
   c.vlpc = (c.L + 1) / 2;
   c.vcpw = 64 / c.vlpc;
