@@ -141,3 +141,41 @@ def test_corrector_at_its_own_configuration():
     for k, bar in (("T", 1.5), ("p", 1.5), ("w", 1.5), ("u", 1.2)):
         assert ho[k]["gain"] > bar, (k, ho[k])
     assert rep["speedup_vs_fine"] > 4.0
+
+
+@pytest.mark.parametrize("n_lev", [32, 64])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_batch_rows_equal_the_stored_fields(n_lev, shift):
+    """Training rows against a plain FP32 evaluation of the same expressions,
+    from 16-byte aligned arrays and from arrays one value off."""
+    import torch
+    from paper_1607_05535_amd import thor
+    w = workloads.gas_giant(2, n_lev, 3, 1, dt=2400.0)
+    g = thor.Grid(2)
+    st = thor.State(g, *thor.structs_from_workload(w))
+    N, L, B, n = g.n, n_lev, 37, 3
+    net = thor.MLP([35 * L, 32, 5 * L], max(N, B))
+    rs = np.random.default_rng(5)
+    norm = np.concatenate([rs.normal(size=5 * L), rs.uniform(0.5, 2, 5 * L), rs.normal(size=5 * L),
+                           rs.uniform(0.5, 2, 5 * L)]).astype(np.float32)
+    corr = thor.Corrector(st, net, norm)
+
+    def off(a, dtype=torch.float32):
+        buf = torch.empty(a.size + 8, dtype=dtype, device="cuda:0")
+        v = buf[shift:shift + a.size].view(a.shape)
+        v.copy_(torch.from_numpy(a))
+        return v
+    C, F = (rs.normal(size=(n, 5, N, L)).astype(np.float32) for _ in range(2))
+    pairs, cols = rs.integers(0, n, B).astype(np.int32), rs.integers(0, N, B).astype(np.int32)
+    cols[0] = N - 1   # a pentagon
+    x, t = off(np.zeros((B, 35 * L), np.float32), torch.bfloat16), off(np.zeros((B, 5 * L), np.float32))
+    corr.batch(off(C), off(F), 5 * N * L, torch.from_numpy(pairs).cuda(), torch.from_numpy(cols).cuda(), x, t)
+    nbr = g.export()[0]
+    src = np.concatenate([cols[:, None], np.where(nbr[cols] < 0, cols[:, None], nbr[cols])], 1)   # [B, 7]
+    m = norm.reshape(4, 5, L)
+    v = C.transpose(0, 2, 1, 3)[pairs[:, None], src]                      # [B, 7, 5, L]
+    ref_x = torch.from_numpy(((v - m[0]) / m[1]).reshape(B, -1)).to(torch.bfloat16)
+    d = F.transpose(0, 2, 1, 3)[pairs, cols] - C.transpose(0, 2, 1, 3)[pairs, cols]
+    ref_t = ((d - m[2]) / m[3]).reshape(B, -1)
+    assert torch.equal(x.cpu(), ref_x)
+    assert np.array_equal(t.cpu().numpy(), ref_t)
