@@ -9,6 +9,10 @@
 //   forward    Z  = H_prev W^T     A = H_prev [B][in],   B = W [out][in]
 //   input grad dH = dZ W           A = dZ [B][out],      B = W read as [k=out][n=in]
 //   weight grad dW = dZ^T H_prev   A = dZ read as [k=B][m=out], B = H_prev read as [k=B][n=in]
+// Pre-activation gradients are formed in the epilogues of the products before
+// them, and the gradients of all layers and the update take one launch each: an
+// Adam step at the corrector's shape (4096 rows) is 9 launches and 136 us, where
+// a kernel per layer and purpose took 35 and 287.
 // The weight gradient reduces over the batch in fixed chunks (split K) whose
 // partial sums are added in a fixed order, so results are reproducible.
 #include <hip/hip_runtime.h>
@@ -32,8 +36,9 @@ constexpr int kStepK = 64;   // k per staged tile (two MFMA k-steps of 32)
 constexpr int kRow = kStepK + 8;   // LDS row of a staged tile (bf16), padded
 constexpr int kMaxSplit = 8;       // batch chunks of the weight gradient
 constexpr int kBiasSplit = 32;     // batch chunks of the bias gradient
+constexpr int kMaxLayers = 16;
 
-enum Epilogue { EPI_STORE = 0, EPI_GELU = 1, EPI_GELU_ONLY = 2 };
+enum Epilogue { EPI_STORE = 0, EPI_GELU = 1, EPI_GELU_ONLY = 2, EPI_LOSS = 3, EPI_ACT_GRAD = 4 };
 
 // erf by Abramowitz & Stegun 7.1.26: erf x = 1 - t (a1 + t (a2 + ... a5 t))
 // e^(-x^2), t = 1 / (1 + p x) for x >= 0, odd in x; absolute error below
@@ -64,60 +69,85 @@ __device__ __forceinline__ bf16x8 tile_load(const __bf16 *P, int ld, int rows, i
     const int row = r0 + (t >> 2), k = k0 + (t & 3) * 16 + 8 * h;
     return row < rows && k < k_hi ? *reinterpret_cast<const bf16x8 *>(P + (size_t)row * ld + k) : zero;
   } else {
-    const int k = k0 + (t >> 3) + 32 * h, rc = r0 + (t & 7) * 8;   // rows is a multiple of 8
+    const int k = k0 + 2 * (t >> 3) + h, rc = r0 + (t & 7) * 8;   // rows is a multiple of 8
     return rc < rows && k < k_hi ? *reinterpret_cast<const bf16x8 *>(P + (size_t)k * ld + rc) : zero;
   }
 }
 
-// The same piece into the LDS tile S[row][k] (rows of kRow values).
+// Position of (row, k) in the LDS tile, rows of kRow values.  A KOUTER tile is
+// transposed on the way in, two k at a time; its 8-value chunks are permuted
+// by the row's group of eight, so that a wavefront's 32-bit stores (8 row
+// groups, 8 k pairs) meet 64 different banks.
 template <bool KOUTER>
-__device__ __forceinline__ void tile_store(__bf16 *S, const bf16x8 v, int h) {
+__device__ __forceinline__ int tile_at(int row, int k) {
+  return row * kRow + (KOUTER ? k ^ (row & 56) : k);
+}
+
+// Both pieces into the LDS tile.
+template <bool KOUTER>
+__device__ __forceinline__ void tile_store(__bf16 *S, const bf16x8 v[2]) {
   const int t = threadIdx.x;
   if (!KOUTER) {
-    *reinterpret_cast<bf16x8 *>(S + (t >> 2) * kRow + (t & 3) * 16 + 8 * h) = v;
-  } else {
-    const int kr = (t >> 3) + 32 * h, rc = (t & 7) * 8;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) S[(rc + i) * kRow + kr] = v[i];
+    for (int h = 0; h < 2; ++h) *reinterpret_cast<bf16x8 *>(S + (t >> 2) * kRow + (t & 3) * 16 + 8 * h) = v[h];
+  } else {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const int k = 2 * (t >> 3), rc = (t & 7) * 8;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<bf16x2 *>(S + tile_at<true>(rc + i, k)) = bf16x2{v[0][i], v[1][i]};
   }
 }
+
+// What the epilogues read and write beside C.
+struct Epi {
+  const float *bias = nullptr;   // [N]
+  __bf16 *H = nullptr;           // EPI_GELU*: activations; EPI_LOSS, EPI_ACT_GRAD: gradient of the pre-activations
+  const float *ref = nullptr;    // EPI_LOSS: targets [M][N]; EPI_ACT_GRAD: pre-activations [M][N]
+  float *loss = nullptr;         // EPI_LOSS: partial loss sums, [column tile][row tile]
+  float scale = 0.f;             // EPI_LOSS: M N (the gradient is 2 d / (M N))
+};
 
 // C tile (m0, n0) of the product over k in [k_lo, k_hi), 4 wavefronts, LDS
 // double-buffered in tiles of 64 k.  Wavefront w owns rows 32 (w / 2) .. + 31 and columns
 // 32 (w % 2) .. + 31 of the tile as 2 x 2 MFMA tiles of 16 x 16; lane l holds
 // A(row l % 16, k0 + 8 (l / 16) .. + 7), B(col l % 16, same k) and
 // accumulates D[4 (l / 16) + i][l % 16], i = 0..3.
-//   EPI_STORE: C = acc (+ bias), or the split's partial C + z M ldc.
+//   EPI_STORE: C = acc (+ bias).
 //   EPI_GELU:  C = acc + bias (pre-activation), H = gelu(C) in bf16.
 //   EPI_GELU_ONLY: H only (inference keeps no pre-activation).
+//   EPI_LOSS: y = acc + bias, d = y - target, C = 2 d / (M N), H = C in bf16, and the sums of d^2.
+//   EPI_ACT_GRAD: C = acc gelu'(ref), H = C in bf16.
+// The last two form the gradient where its product is, so that neither y nor
+// dH goes through memory for a kernel of its own.
 template <bool AK, bool BK, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(const __bf16 *__restrict__ A, int lda, const __bf16 *__restrict__ B,
-                                              int ldb, float *__restrict__ C, int ldc, const float *__restrict__ bias,
-                                              __bf16 *__restrict__ H, int M, int N, int K, int k_chunk) {
+__device__ __forceinline__ void gemm_tile(const __bf16 *__restrict__ A, int lda, const __bf16 *__restrict__ B, int ldb,
+                                          float *__restrict__ C, int ldc, const Epi &epi, int M, int N, int k_lo,
+                                          int k_hi, int tm, int tn) {
   __shared__ __align__(16) __bf16 As[2][kTile * kRow];
   __shared__ __align__(16) __bf16 Bs[2][kTile * kRow];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int m0 = blockIdx.x * kTile, n0 = blockIdx.y * kTile;
+  const int m0 = tm * kTile, n0 = tn * kTile;
   const int wm = 32 * (w >> 1), wn = 32 * (w & 1);
   const int r = lane & 15, kq = (lane >> 4) * 8;
-  const int k_lo = blockIdx.z * k_chunk, k_hi = min(K, k_lo + k_chunk);
   f32x4 acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   int buf = 0;
+  bf16x8 na[2], nbv[2];
   if (k_lo < k_hi) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      tile_store<AK>(As[0], tile_load<AK>(A, lda, M, m0, k_lo, k_hi, h), h);
-      tile_store<BK>(Bs[0], tile_load<BK>(B, ldb, N, n0, k_lo, k_hi, h), h);
+      na[h] = tile_load<AK>(A, lda, M, m0, k_lo, k_hi, h);
+      nbv[h] = tile_load<BK>(B, ldb, N, n0, k_lo, k_hi, h);
     }
+    tile_store<AK>(As[0], na);
+    tile_store<BK>(Bs[0], nbv);
   }
   __syncthreads();
   for (int k0 = k_lo; k0 < k_hi; k0 += kStepK) {
     const bool more = k0 + kStepK < k_hi;
-    bf16x8 na[2], nbv[2];
     if (more) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -130,8 +160,8 @@ __global__ __launch_bounds__(256) void k_gemm(const __bf16 *__restrict__ A, int 
       bf16x8 a[2], b[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        a[i] = *reinterpret_cast<const bf16x8 *>(&As[buf][(wm + 16 * i + r) * kRow + kk + kq]);
-        b[i] = *reinterpret_cast<const bf16x8 *>(&Bs[buf][(wn + 16 * i + r) * kRow + kk + kq]);
+        a[i] = *reinterpret_cast<const bf16x8 *>(&As[buf][tile_at<AK>(wm + 16 * i + r, kk + kq)]);
+        b[i] = *reinterpret_cast<const bf16x8 *>(&Bs[buf][tile_at<BK>(wn + 16 * i + r, kk + kq)]);
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
@@ -140,32 +170,173 @@ __global__ __launch_bounds__(256) void k_gemm(const __bf16 *__restrict__ A, int 
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
     if (more) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        tile_store<AK>(As[buf ^ 1], na[h], h);
-        tile_store<BK>(Bs[buf ^ 1], nbv[h], h);
-      }
+      tile_store<AK>(As[buf ^ 1], na);
+      tile_store<BK>(Bs[buf ^ 1], nbv);
     }
     __syncthreads();
     buf ^= 1;
   }
-  float *Cz = C + (size_t)blockIdx.z * M * ldc;
+  float sq = 0.f;   // this lane's squared errors
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int col = n0 + wn + 16 * j + r;
       if (col >= N) continue;
-      const float bb = bias ? bias[col] : 0.f;
+      const float bb = epi.bias ? epi.bias[col] : 0.f;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int row = m0 + wm + 16 * i + (lane >> 4) * 4 + q;
         if (row >= M) continue;
         const float z = acc[i][j][q] + bb;
-        if (EPI != EPI_GELU_ONLY) Cz[(size_t)row * ldc + col] = z;
-        if (EPI != EPI_STORE) H[(size_t)row * N + col] = (__bf16)gelu_f(z);
+        if (EPI == EPI_STORE || EPI == EPI_GELU) C[(size_t)row * ldc + col] = z;
+        if (EPI == EPI_GELU || EPI == EPI_GELU_ONLY) epi.H[(size_t)row * N + col] = (__bf16)gelu_f(z);
+        if (EPI == EPI_LOSS || EPI == EPI_ACT_GRAD) {
+          const float ref = epi.ref[(size_t)row * N + col];
+          float g;
+          if (EPI == EPI_LOSS) {
+            const float d = z - ref;
+            sq += d * d;
+            g = 2.f * d / epi.scale;
+          } else {
+            g = z * gelu_grad_f(ref);
+          }
+          C[(size_t)row * ldc + col] = g;
+          epi.H[(size_t)row * N + col] = (__bf16)g;
+        }
       }
     }
+  if (EPI == EPI_LOSS) {
+    // (the operand tiles are free: every wavefront passed the last barrier)
+    float *sm = reinterpret_cast<float *>(As[0]);
+    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+    if (lane == 0) sm[w] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) epi.loss[(size_t)tn * ((M + kTile - 1) / kTile) + tm] = ((sm[0] + sm[1]) + sm[2]) + sm[3];
+  }
+}
+
+template <bool AK, bool BK, int EPI>
+__global__ __launch_bounds__(256) void k_gemm(const __bf16 *__restrict__ A, int lda, const __bf16 *__restrict__ B,
+                                              int ldb, float *__restrict__ C, int ldc, Epi epi, int M, int N, int K) {
+  gemm_tile<AK, BK, EPI>(A, lda, B, ldb, C, ldc, epi, M, N, 0, K, blockIdx.x, blockIdx.y);
+}
+
+// Column sums of X[B][N] over row chunk `chunk` into part[chunk][N]: 64
+// columns from n0, 4 row groups combined in a fixed order.
+__device__ __forceinline__ void colsum_tile(const float *X, int B, int N, int rows_per, int n0, int chunk, float *part) {
+  __shared__ float sm[4][64];
+  const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int n = n0 + c;
+  const int b0 = chunk * rows_per, b1 = min(B, b0 + rows_per);
+  float s = 0.f;
+  if (n < N) {
+#pragma unroll 8
+    for (int b = b0 + g; b < b1; b += 4) s += X[(size_t)b * N + n];
+  }
+  sm[g][c] = s;
+  __syncthreads();
+  if (g == 0 && n < N) part[(size_t)chunk * N + n] = ((sm[0][c] + sm[1][c]) + sm[2][c]) + sm[3][c];
+}
+
+// Weight and bias gradients of every layer in one launch (they only need the
+// pre-activation gradients and the activations, which all exist by then, and
+// one layer's 16-72 tiles fill few compute units).  dW[N][K] = dZ^T H_prev,
+// both operands read with the batch as outer index, in S batch chunks of
+// `chunk` rows whose partial products go to split + z N K; db = the column
+// sums of dZ in kBiasSplit chunks of `rows_per` rows.  The first S x (tiles)
+// workgroups take the products, the rest the sums.
+struct GradLayer {
+  const __bf16 *dZb, *prev;
+  const float *dZ;
+  float *split, *bsum;
+  int N, K, tn, first, bfirst;   // widths; column tiles; first product and sum workgroup of the layer
+};
+struct GradNet {
+  GradLayer l[kMaxLayers];
+  int nl, tiles, S;   // product workgroups per batch chunk
+};
+__global__ __launch_bounds__(256) void k_grad(GradNet net, int B, int chunk, int rows_per) {
+  const int wg = blockIdx.x, products = net.tiles * net.S;
+  if (wg < products) {
+    const int z = wg / net.tiles, i = wg - z * net.tiles;
+    int l = 0;
+    while (l + 1 < net.nl && i >= net.l[l + 1].first) ++l;
+    const GradLayer &g = net.l[l];
+    const int t = i - g.first, k_lo = z * chunk;
+    gemm_tile<true, true, EPI_STORE>(g.dZb, g.N, g.prev, g.K, g.split + (size_t)z * g.N * g.K, g.K, Epi{}, g.N, g.K,
+                                     k_lo, min(B, k_lo + chunk), t / g.tn, t % g.tn);
+  } else {
+    const int i = wg - products;
+    int l = 0;
+    while (l + 1 < net.nl && i >= net.l[l + 1].bfirst) ++l;
+    const GradLayer &g = net.l[l];
+    const int t = i - g.bfirst;
+    colsum_tile(g.dZ, B, g.N, rows_per, t / kBiasSplit * 64, t % kBiasSplit, g.bsum);
+  }
+}
+
+// The end of a backward pass, eight consecutive parameters per thread: the
+// gradient as the sum of its partial sums in order, then (ADAM) Adam on the
+// packed fp32 parameters and the bf16 copies of the weights, row-major and in
+// fragment order; else the gradient alone.  One launch where reductions,
+// Adam and copies of each layer were eighteen.
+struct UpdateLayer {
+  const float *split, *bias;   // S partial weight gradients; kBiasSplit partial bias gradients
+  __bf16 *Wb, *Wf;
+  size_t woff;                 // weights at woff, biases at woff + N K
+  int N, K;
+};
+struct UpdateNet {
+  UpdateLayer l[kMaxLayers];
+  int nl, S;
+};
+struct Adam {
+  float lr, b1, b2, eps, c1, c2;
+};
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_update(UpdateNet net, size_t n, float *p, float *m, float *v, float *grad,
+                                                Adam a) {
+  const size_t i = (blockIdx.x * (size_t)blockDim.x + threadIdx.x) * 8;
+  if (i >= n) return;
+  int l = 0;
+  while (l + 1 < net.nl && i >= net.l[l + 1].woff) ++l;
+  const UpdateLayer &L = net.l[l];
+  const size_t j = i - L.woff, nw = (size_t)L.N * L.K;
+  const bool weight = j < nw;
+  const float *src = weight ? L.split + j : L.bias + (j - nw);
+  const size_t step = weight ? nw : (size_t)L.N;
+  const int parts = weight ? net.S : kBiasSplit;
+  float g[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int z = 0; z < parts; ++z) {
+    const float4 x = *reinterpret_cast<const float4 *>(src + z * step);
+    const float4 y = *reinterpret_cast<const float4 *>(src + z * step + 4);
+    g[0] += x.x; g[1] += x.y; g[2] += x.z; g[3] += x.w;
+    g[4] += y.x; g[5] += y.y; g[6] += y.z; g[7] += y.w;
+  }
+  if (!ADAM) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) grad[i + e] = g[e];
+    return;
+  }
+  bf16x8 b;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float mi = a.b1 * m[i + e] + (1.f - a.b1) * g[e];
+    const float vi = a.b2 * v[i + e] + (1.f - a.b2) * g[e] * g[e];
+    m[i + e] = mi;
+    v[i + e] = vi;
+    const float pi = p[i + e] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+    p[i + e] = pi;
+    b[e] = (__bf16)pi;
+  }
+  if (!weight) return;
+  *reinterpret_cast<bf16x8 *>(L.Wb + j) = b;
+  // fragment order of k_weights_frag: these are W[row][k .. k + 7]
+  const int row = (int)(j / L.K), k = (int)(j % L.K);
+  const size_t f = ((size_t)(row / 16) * (L.K / 32) + k / 32) * 64 + row % 16 + 16 * (k % 32 / 8);
+  *reinterpret_cast<bf16x8 *>(L.Wf + f * 8) = b;
 }
 
 // ---------------------------------------------------------------------------
@@ -370,74 +541,6 @@ __global__ __launch_bounds__(64 * kFW) void k_mlp_fused4(FusedNet net, const __b
   }
 }
 
-// out[i] = sum_{z < S} part[z][i] in order z = 0, 1, ...
-__global__ void k_reduce(const float *part, int S, size_t n, float *out) {
-  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = 0.f;
-  for (int z = 0; z < S; ++z) s += part[(size_t)z * n + i];
-  out[i] = s;
-}
-
-// Column sums of X[B][N] over row chunk blockIdx.y into part[chunk][N]:
-// 64 columns per workgroup, 4 row groups combined in a fixed order.
-__global__ __launch_bounds__(256) void k_colsum(const float *X, int B, int N, int rows_per, float *part) {
-  __shared__ float sm[4][64];
-  const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + c;
-  const int b0 = blockIdx.y * rows_per, b1 = min(B, b0 + rows_per);
-  float s = 0.f;
-  if (n < N)
-    for (int b = b0 + g; b < b1; b += 4) s += X[(size_t)b * N + n];
-  sm[g][c] = s;
-  __syncthreads();
-  if (g == 0 && n < N) part[(size_t)blockIdx.y * N + n] = ((sm[0][c] + sm[1][c]) + sm[2][c]) + sm[3][c];
-}
-
-// Output layer: dZ = 2 (Y - T) / (B N); per-workgroup partial loss sums.
-__global__ __launch_bounds__(256) void k_loss(const float *Y, const float *T, float *dZ, __bf16 *dZb,
-                                              float *partial, int B, int N) {
-  __shared__ float sm[256];
-  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  float l = 0.f;
-  if (i < (size_t)B * N) {
-    const float d = Y[i] - T[i];
-    l = d * d;
-    const float g = 2.f * d / ((float)B * (float)N);
-    dZ[i] = g;
-    dZb[i] = (__bf16)g;
-  }
-  sm[threadIdx.x] = l;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sm[threadIdx.x] += sm[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[blockIdx.x] = sm[0];
-}
-
-// Hidden layer: dZ = dH * g'(Z) in fp32 and bf16.
-__global__ void k_act_grad(const float *dH, const float *Z, float *dZ, __bf16 *dZb, size_t n) {
-  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float g = dH[i] * gelu_grad_f(Z[i]);
-  dZ[i] = g;
-  dZb[i] = (__bf16)g;
-}
-
-// Adam on the packed fp32 parameters.
-__global__ void k_adam(float *p, const float *g, float *m, float *v, size_t n, float lr, float b1, float b2,
-                       float eps, float c1, float c2) {
-  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
 // bf16 copy of one layer's fp32 weights.
 __global__ void k_weights_bf16(const float *W, __bf16 *Wb, size_t n) {
   const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
@@ -479,13 +582,13 @@ struct thor_mlp {
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
   std::vector<__bf16 *> Wb;      // bf16 copies of W_l [out][in]
   std::vector<__bf16 *> Wf;      // the same in MFMA fragment order (fused inference)
-  std::vector<float *> Z;        // pre-activations, [B][w_{l+1}]
+  std::vector<float *> Z;        // pre-activations of the hidden layers, [B][w_{l+1}]
   std::vector<__bf16 *> H;       // hidden activations, [B][w_{l+1}]
-  std::vector<float *> dZ;
+  std::vector<float *> dZ;       // gradients of the pre-activations
   std::vector<__bf16 *> dZb;
-  float *dH = nullptr;           // [B][max width]
-  float *split = nullptr;        // split-K partial sums of one weight gradient
-  float *partial = nullptr;      // loss partial sums
+  std::vector<float *> split;    // partial sums of the weight gradient, [kMaxSplit][w_{l+1}][w_l]
+  std::vector<float *> bsum;     // and of the bias gradient, [kBiasSplit][w_{l+1}]
+  float *partial = nullptr;      // loss partial sums, one per output tile
   int adam_t = 0;
   bool fused = true;             // inference through k_mlp_fused4 where the shape allows
   hipStream_t stream = nullptr;
@@ -508,10 +611,7 @@ size_t mlp_layout(thor_mlp *M, char *base) {
     return ptr;
   };
   const int B = M->max_batch, nl = M->nl;
-  int wmax = 0;
-  size_t wprod = 0;
-  for (int x : M->w) wmax = std::max(wmax, x);
-  for (int l = 0; l < nl; ++l) wprod = std::max(wprod, (size_t)M->w[l] * M->w[l + 1]);
+  const size_t tiles = ((size_t)B + kTile - 1) / kTile;
   M->p = (float *)take(M->n_params * 4);
   M->g = (float *)take(M->n_params * 4);
   M->m = (float *)take(M->n_params * 4);
@@ -522,23 +622,27 @@ size_t mlp_layout(thor_mlp *M, char *base) {
   M->H.assign(nl, nullptr);
   M->dZ.assign(nl, nullptr);
   M->dZb.assign(nl, nullptr);
+  M->split.assign(nl, nullptr);
+  M->bsum.assign(nl, nullptr);
   for (int l = 0; l < nl; ++l) {
     const size_t wsz = (size_t)M->w[l] * M->w[l + 1];
     M->Wb[l] = (__bf16 *)take(wsz * 2);
     M->Wf[l] = (__bf16 *)take(wsz * 2);
-    M->Z[l] = (float *)take((size_t)B * M->w[l + 1] * 4);
-    M->H[l] = (__bf16 *)take((size_t)B * M->w[l + 1] * 2);
+    if (l + 1 < nl) {
+      M->Z[l] = (float *)take((size_t)B * M->w[l + 1] * 4);
+      M->H[l] = (__bf16 *)take((size_t)B * M->w[l + 1] * 2);
+    }
     M->dZ[l] = (float *)take((size_t)B * M->w[l + 1] * 4);
     M->dZb[l] = (__bf16 *)take((size_t)B * M->w[l + 1] * 2);
+    M->split[l] = (float *)take(kMaxSplit * wsz * 4);
+    M->bsum[l] = (float *)take((size_t)kBiasSplit * M->w[l + 1] * 4);
   }
-  M->dH = (float *)take((size_t)B * wmax * 4);
-  M->split = (float *)take(std::max((size_t)kMaxSplit * wprod, (size_t)kBiasSplit * wmax) * 4);
-  M->partial = (float *)take((size_t)nb((size_t)B * M->w[nl]) * 4);
+  M->partial = (float *)take(tiles * ((M->w[nl] + kTile - 1) / kTile) * 4);
   return off;
 }
 
 bool mlp_shape(thor_mlp *M, int n_layers, const int *widths, int max_batch) {
-  if (n_layers < 1 || n_layers > 16 || !widths || max_batch < 1) {
+  if (n_layers < 1 || n_layers > kMaxLayers || !widths || max_batch < 1) {
     set_error("thor_mlp: need 1..16 layers, widths and max_batch >= 1");
     return false;
   }
@@ -571,14 +675,12 @@ void refresh_bf16(thor_mlp *M) {
   }
 }
 
-// C[M][N] = sum_k A(m, k) B(n, k); see k_gemm for the operand forms.
+// C[M][N] = sum_k A(m, k) B(n, k); see gemm_tile for the operand forms.
 template <bool AK, bool BK, int EPI>
-void gemm(const __bf16 *A, int lda, const __bf16 *B, int ldb, float *C, int ldc, const float *bias, __bf16 *H,
-          int Mr, int N, int K, int splits, hipStream_t s) {
-  const int chunk = ((K + splits - 1) / splits + kStepK - 1) / kStepK * kStepK;
-  const int S = (K + chunk - 1) / chunk;
-  dim3 grid((Mr + kTile - 1) / kTile, (N + kTile - 1) / kTile, S);
-  hipLaunchKernelGGL((k_gemm<AK, BK, EPI>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, bias, H, Mr, N, K, chunk);
+void gemm(const __bf16 *A, int lda, const __bf16 *B, int ldb, float *C, int ldc, const Epi &epi, int Mr, int N, int K,
+          hipStream_t s) {
+  dim3 grid((Mr + kTile - 1) / kTile, (N + kTile - 1) / kTile);
+  hipLaunchKernelGGL((k_gemm<AK, BK, EPI>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, epi, Mr, N, K);
 }
 
 // Number of batch chunks of a weight gradient: chunks of at least 256 rows.
@@ -591,10 +693,10 @@ bool fused_shape(const thor_mlp *M) {
          M->w[4] <= kFH;
 }
 
-// Forward pass; the output layer's pre-activation goes to y if given
-// (inference: hidden pre-activations are not kept), else to Z[nl - 1].
-void forward(thor_mlp *M, const __bf16 *X, int B, float *y) {
-  if (y && fused_shape(M) && M->fused) {
+// Inference: the output layer's pre-activation to y (hidden pre-activations
+// are not kept).
+void infer(thor_mlp *M, const __bf16 *X, int B, float *y) {
+  if (fused_shape(M) && M->fused) {
     FusedNet net;
     for (int l = 0; l < 4; ++l) {
       net.W[l] = M->Wf[l];
@@ -608,45 +710,72 @@ void forward(thor_mlp *M, const __bf16 *X, int B, float *y) {
   const __bf16 *in = X;
   for (int l = 0; l < M->nl; ++l) {
     const int K = M->w[l], N = M->w[l + 1];
-    const float *bias = M->p + M->boff[l];
+    Epi e;
+    e.bias = M->p + M->boff[l];
     if (l + 1 < M->nl) {
-      if (y)
-        gemm<false, false, EPI_GELU_ONLY>(in, K, M->Wb[l], K, M->Z[l], N, bias, M->H[l], B, N, K, 1, M->stream);
-      else
-        gemm<false, false, EPI_GELU>(in, K, M->Wb[l], K, M->Z[l], N, bias, M->H[l], B, N, K, 1, M->stream);
+      e.H = M->H[l];
+      gemm<false, false, EPI_GELU_ONLY>(in, K, M->Wb[l], K, nullptr, N, e, B, N, K, M->stream);
       in = M->H[l];
     } else {
-      gemm<false, false, EPI_STORE>(in, K, M->Wb[l], K, y ? y : M->Z[l], N, bias, nullptr, B, N, K, 1, M->stream);
+      gemm<false, false, EPI_STORE>(in, K, M->Wb[l], K, y, N, e, B, N, K, M->stream);
     }
   }
 }
 
-// Gradients of the mean-squared loss into M->g; partial loss sums in M->partial.
-void backward(thor_mlp *M, const __bf16 *X, const float *T, int B) {
+// Forward and backward pass of the mean-squared loss, up to the partial sums
+// of the gradients (M->split, M->bsum) and of the loss (M->partial); returns
+// the number of batch chunks of a weight gradient.
+int loss_and_grad(thor_mlp *M, const __bf16 *X, const float *T, int B) {
   const int nl = M->nl;
   hipStream_t s = M->stream;
-  const int No = M->w[nl];
-  hipLaunchKernelGGL(k_loss, dim3(nb((size_t)B * No)), dim3(256), 0, s, M->Z[nl - 1], T, M->dZ[nl - 1],
-                     M->dZb[nl - 1], M->partial, B, No);
-  const int S = grad_splits(B);
-  for (int l = nl - 1; l >= 0; --l) {
+  for (int l = 0; l < nl; ++l) {
     const int K = M->w[l], N = M->w[l + 1];
-    const __bf16 *prev = l == 0 ? X : M->H[l - 1];
-    // dW[N][K] = dZ^T H_prev: both operands read with the batch as outer index
-    gemm<true, true, EPI_STORE>(M->dZb[l], N, prev, K, M->split, K, nullptr, nullptr, N, K, B, S, s);
-    const size_t nw = (size_t)N * K;
-    hipLaunchKernelGGL(k_reduce, dim3(nb(nw)), dim3(256), 0, s, M->split, S, nw, M->g + M->woff[l]);
-    // db[N] = column sums of dZ
-    const int rows = (B + kBiasSplit - 1) / kBiasSplit;
-    hipLaunchKernelGGL(k_colsum, dim3((N + 63) / 64, kBiasSplit), dim3(256), 0, s, M->dZ[l], B, N, rows, M->split);
-    hipLaunchKernelGGL(k_reduce, dim3(nb(N)), dim3(256), 0, s, M->split, kBiasSplit, (size_t)N, M->g + M->boff[l]);
-    if (l > 0) {
-      // dH[B][K] = dZ W, W read as [k = out][n = in]; then through the activation
-      gemm<false, true, EPI_STORE>(M->dZb[l], N, M->Wb[l], K, M->dH, K, nullptr, nullptr, B, K, N, 1, s);
-      const size_t n = (size_t)B * K;
-      hipLaunchKernelGGL(k_act_grad, dim3(nb(n)), dim3(256), 0, s, M->dH, M->Z[l - 1], M->dZ[l - 1], M->dZb[l - 1], n);
+    const __bf16 *in = l ? M->H[l - 1] : X;
+    Epi e;
+    e.bias = M->p + M->boff[l];
+    if (l + 1 < nl) {
+      e.H = M->H[l];
+      gemm<false, false, EPI_GELU>(in, K, M->Wb[l], K, M->Z[l], N, e, B, N, K, s);
+    } else {
+      e.H = M->dZb[l];
+      e.ref = T;
+      e.loss = M->partial;
+      e.scale = (float)B * (float)N;
+      gemm<false, false, EPI_LOSS>(in, K, M->Wb[l], K, M->dZ[l], N, e, B, N, K, s);
     }
   }
+  for (int l = nl - 1; l > 0; --l) {
+    const int K = M->w[l], N = M->w[l + 1];
+    // dH[B][K] = dZ W, W read as [k = out][n = in], through the activation
+    Epi e;
+    e.H = M->dZb[l - 1];
+    e.ref = M->Z[l - 1];
+    gemm<false, true, EPI_ACT_GRAD>(M->dZb[l], N, M->Wb[l], K, M->dZ[l - 1], K, e, B, K, N, s);
+  }
+  const int splits = grad_splits(B);
+  const int chunk = ((B + splits - 1) / splits + kStepK - 1) / kStepK * kStepK, S = (B + chunk - 1) / chunk;
+  GradNet g{};
+  g.nl = nl;
+  g.S = S;
+  int sums = 0;
+  for (int l = 0; l < nl; ++l) {
+    const int K = M->w[l], N = M->w[l + 1], tn = (K + kTile - 1) / kTile;
+    g.l[l] = GradLayer{M->dZb[l], l ? M->H[l - 1] : X, M->dZ[l], M->split[l], M->bsum[l], N, K, tn, g.tiles, sums};
+    g.tiles += (N + kTile - 1) / kTile * tn;
+    sums += (N + 63) / 64 * kBiasSplit;
+  }
+  hipLaunchKernelGGL(k_grad, dim3(g.tiles * S + sums), dim3(256), 0, s, g, B, chunk,
+                     (B + kBiasSplit - 1) / kBiasSplit);
+  return S;
+}
+
+UpdateNet update_net(thor_mlp *M, int S) {
+  UpdateNet u{};
+  u.nl = M->nl;
+  u.S = S;
+  for (int l = 0; l < M->nl; ++l)
+    u.l[l] = UpdateLayer{M->split[l], M->bsum[l], M->Wb[l], M->Wf[l], M->woff[l], M->w[l + 1], M->w[l]};
+  return u;
 }
 
 // SplitMix64 stream and Box-Muller normals for the initial weights.
@@ -745,7 +874,7 @@ int thor_mlp_forward(thor_mlp *m, const void *x_bf16, int B, float *y) {
   if (!m || !x_bf16 || !y) { set_error("thor_mlp_forward: NULL argument"); return THOR_EINVAL; }
   if (B < 1 || B > m->max_batch) { set_error("thor_mlp_forward: batch outside 1..max_batch"); return THOR_EINVAL; }
   if (((uintptr_t)x_bf16 & 15) != 0) { set_error("thor_mlp_forward: inputs must be 16-byte aligned"); return THOR_EINVAL; }
-  forward(m, (const __bf16 *)x_bf16, B, y);
+  infer(m, (const __bf16 *)x_bf16, B, y);
   return mlp_ok(hipGetLastError(), "mlp forward") ? THOR_OK : THOR_EHIP;
 }
 
@@ -754,9 +883,10 @@ int thor_mlp_loss_grad(thor_mlp *m, const void *x_bf16, const float *t, int B, d
   if (!m || !x_bf16 || !t) { set_error("thor_mlp_loss_grad: NULL argument"); return THOR_EINVAL; }
   if (B < 1 || B > m->max_batch || B % 32) { set_error("thor_mlp_loss_grad: batch must be a multiple of 32 within max_batch"); return THOR_EINVAL; }
   if (((uintptr_t)x_bf16 & 15) != 0) { set_error("thor_mlp_loss_grad: inputs must be 16-byte aligned"); return THOR_EINVAL; }
-  forward(m, (const __bf16 *)x_bf16, B, nullptr);
-  backward(m, (const __bf16 *)x_bf16, t, B);
-  const size_t np = nb((size_t)B * m->w[m->nl]);
+  const int S = loss_and_grad(m, (const __bf16 *)x_bf16, t, B);
+  hipLaunchKernelGGL(k_update<false>, dim3(nb(m->n_params / 8)), dim3(256), 0, m->stream, update_net(m, S),
+                     m->n_params, (float *)nullptr, (float *)nullptr, (float *)nullptr, m->g, Adam{});
+  const size_t np = (size_t)((B + kTile - 1) / kTile) * ((m->w[m->nl] + kTile - 1) / kTile);
   std::vector<float> part(np);
   if (!mlp_ok(hipMemcpyAsync(part.data(), m->partial, np * 4, hipMemcpyDeviceToHost, m->stream), "copy loss"))
     return THOR_EHIP;
@@ -774,14 +904,12 @@ int thor_mlp_train_step(thor_mlp *m, const void *x_bf16, const float *t, int B, 
   if (!m || !x_bf16 || !t) { set_error("thor_mlp_train_step: NULL argument"); return THOR_EINVAL; }
   if (B < 1 || B > m->max_batch || B % 32 || !(lr > 0)) { set_error("thor_mlp_train_step: batch must be a multiple of 32 within max_batch, lr > 0"); return THOR_EINVAL; }
   if (((uintptr_t)x_bf16 & 15) != 0) { set_error("thor_mlp_train_step: inputs must be 16-byte aligned"); return THOR_EINVAL; }
-  forward(m, (const __bf16 *)x_bf16, B, nullptr);
-  backward(m, (const __bf16 *)x_bf16, t, B);
+  const int S = loss_and_grad(m, (const __bf16 *)x_bf16, t, B);
   m->adam_t += 1;
   const float b1 = 0.9f, b2 = 0.999f;
   const float c1 = 1.f - std::pow(b1, (float)m->adam_t), c2 = 1.f - std::pow(b2, (float)m->adam_t);
-  hipLaunchKernelGGL(k_adam, dim3(nb(m->n_params)), dim3(256), 0, m->stream, m->p, m->g, m->m, m->v, m->n_params, lr,
-                     b1, b2, 1e-8f, c1, c2);
-  refresh_bf16(m);
+  hipLaunchKernelGGL(k_update<true>, dim3(nb(m->n_params / 8)), dim3(256), 0, m->stream, update_net(m, S),
+                     m->n_params, m->p, m->m, m->v, (float *)nullptr, Adam{lr, b1, b2, 1e-8f, c1, c2});
   return mlp_ok(hipGetLastError(), "train step") ? THOR_OK : THOR_EHIP;
 }
 

@@ -123,3 +123,38 @@ def test_split_batch_gradients_match_reference_and_repeat_bitwise():
     net.forward(x, y)
     d = y.cpu().numpy().astype(np.float64) - tr
     assert abs(np.mean(d * d) / loss - 1) < 1e-6
+
+
+@pytest.mark.parametrize("widths,B", [([32, 32], 32), ([96, 160, 32], 96), ([64, 256, 96, 160], 1056),
+                                      ([1120, 256, 256, 256, 160], 320)])
+def test_gradients_and_adam_at_ragged_tiles(widths, B):
+    """Batches and widths that leave part of the 64 x 64 tiles over, one layer
+    to four: gradients against the reference, one Adam step against the same
+    formula in FP32 on the returned gradient, and the two inference paths on
+    the updated weights against each other."""
+    import torch
+    from paper_1607_05535_amd import thor
+    net = thor.MLP(widths, B, seed=2)
+    rs = np.random.default_rng(4)
+    x = torch.from_numpy(rs.normal(size=(B, widths[0])).astype(np.float32)).to("cuda:0").to(torch.bfloat16)
+    t32 = rs.normal(size=(B, widths[-1])).astype(np.float32)
+    t = torch.from_numpy(t32).to("cuda:0")
+    p0 = net.get_params()
+    loss, g = net.loss_grad(x, t)
+    params, xr = _ref_params(net), x.float().cpu().numpy().astype(np.float64)
+    assert abs(loss / omlp.loss(params, xr, t32.astype(np.float64)) - 1) < 2e-2
+    for (gW, gb), (rW, rb) in zip(net.unpack(g.astype(np.float64)),
+                                  omlp.backward(params, xr, t32.astype(np.float64))):
+        for a, r in ((gW, rW), (gb, rb)):
+            assert np.linalg.norm(a - r) < 2e-2 * np.linalg.norm(r)
+    net.train_step(x, t, 1e-2)
+    f = np.float32
+    m, v = f(0.1) * g, f(1) * (f(1) - f(0.999)) * g * g
+    ref = p0 - f(1e-2) * (m / (f(1) - f(0.9))) / (np.sqrt(v / (f(1) - f(0.999))) + f(1e-8))
+    # a few FP32 roundings of the parameter and of a step of at most 1e-2
+    assert np.abs(net.get_params() - ref).max() <= 8 * 2.0 ** -24 * (np.abs(p0).max() + 1e-2)
+    y = [torch.empty(B, widths[-1], device="cuda:0") for _ in range(2)]
+    net.forward(x, y[0])
+    net.set_fused(False)
+    net.forward(x, y[1])
+    assert torch.equal(y[0], y[1])
