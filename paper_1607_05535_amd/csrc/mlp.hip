@@ -21,6 +21,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -59,19 +60,21 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
 
 // Piece h (0, 1) of a 64 x 64 operand tile, 16 bytes per thread (256
 // threads), read from global memory: rows r0.. of an operand with `rows`
-// rows, k from k0, zero at k >= k_hi (k_hi a multiple of 32).  KOUTER:
-// stored [k][row] with leading dimension ld, else [row][k].
+// rows, k from k0.  KOUTER: stored [k][row] with leading dimension ld, else
+// [row][k].  Rows past the end repeat the last ones (their products are not
+// stored), k past k_hi the tile's first k (tile_store writes zeros there), so
+// that the loads are unconditional and nothing waits on a branch.
+template <bool KOUTER>
+__device__ __forceinline__ int tile_k(int h) {
+  const int t = threadIdx.x;
+  return KOUTER ? 2 * (t >> 3) + h : (t & 3) * 16 + 8 * h;
+}
 template <bool KOUTER>
 __device__ __forceinline__ bf16x8 tile_load(const __bf16 *P, int ld, int rows, int r0, int k0, int k_hi, int h) {
   const int t = threadIdx.x;
-  const bf16x8 zero = {};
-  if (!KOUTER) {
-    const int row = r0 + (t >> 2), k = k0 + (t & 3) * 16 + 8 * h;
-    return row < rows && k < k_hi ? *reinterpret_cast<const bf16x8 *>(P + (size_t)row * ld + k) : zero;
-  } else {
-    const int k = k0 + 2 * (t >> 3) + h, rc = r0 + (t & 7) * 8;   // rows is a multiple of 8
-    return rc < rows && k < k_hi ? *reinterpret_cast<const bf16x8 *>(P + (size_t)k * ld + rc) : zero;
-  }
+  const int kk = k0 + tile_k<KOUTER>(h), k = kk < k_hi ? kk : k0;
+  if (!KOUTER) return *reinterpret_cast<const bf16x8 *>(P + (size_t)min(r0 + (t >> 2), rows - 1) * ld + k);
+  return *reinterpret_cast<const bf16x8 *>(P + (size_t)k * ld + min(r0 + (t & 7) * 8, rows - 8));   // rows % 8 == 0
 }
 
 // Position of (row, k) in the LDS tile, rows of kRow values.  A KOUTER tile is
@@ -83,10 +86,14 @@ __device__ __forceinline__ int tile_at(int row, int k) {
   return row * kRow + (KOUTER ? k ^ (row & 56) : k);
 }
 
-// Both pieces into the LDS tile.
+// Both pieces into the LDS tile, zeros from k = k_n on (k_n = 64 or a
+// multiple of 32 below).
 template <bool KOUTER>
-__device__ __forceinline__ void tile_store(__bf16 *S, const bf16x8 v[2]) {
+__device__ __forceinline__ void tile_store(__bf16 *S, const bf16x8 vin[2], int k_n) {
   const int t = threadIdx.x;
+  bf16x8 v[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) v[h] = tile_k<KOUTER>(h) < k_n ? vin[h] : bf16x8{};
   if (!KOUTER) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) *reinterpret_cast<bf16x8 *>(S + (t >> 2) * kRow + (t & 3) * 16 + 8 * h) = v[h];
@@ -134,48 +141,51 @@ __device__ __forceinline__ void gemm_tile(const __bf16 *__restrict__ A, int lda,
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  int buf = 0;
-  bf16x8 na[2], nbv[2];
-  if (k_lo < k_hi) {
+  // Tile i sits in LDS buffer i % 2; tile i + 1 is in registers since the
+  // iteration before and goes to LDS after the products of tile i, while the
+  // loads of tile i + 2 are in flight for a whole iteration.
+  bf16x8 ra[2][2], rb[2][2];
+  const int nt = (k_hi - k_lo + kStepK - 1) / kStepK;
+  auto load = [&](int i, bf16x8 a[2], bf16x8 b[2]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      na[h] = tile_load<AK>(A, lda, M, m0, k_lo, k_hi, h);
-      nbv[h] = tile_load<BK>(B, ldb, N, n0, k_lo, k_hi, h);
+      a[h] = tile_load<AK>(A, lda, M, m0, k_lo + i * kStepK, k_hi, h);
+      b[h] = tile_load<BK>(B, ldb, N, n0, k_lo + i * kStepK, k_hi, h);
     }
-    tile_store<AK>(As[0], na);
-    tile_store<BK>(Bs[0], nbv);
-  }
-  __syncthreads();
-  for (int k0 = k_lo; k0 < k_hi; k0 += kStepK) {
-    const bool more = k0 + kStepK < k_hi;
-    if (more) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        na[h] = tile_load<AK>(A, lda, M, m0, k0 + kStepK, k_hi, h);
-        nbv[h] = tile_load<BK>(B, ldb, N, n0, k0 + kStepK, k_hi, h);
-      }
-    }
+  };
+  auto step = [&](int i, auto sc) __attribute__((always_inline)) {
+    constexpr int s = decltype(sc)::value;
+    load(min(i + 2, nt - 1), ra[s], rb[s]);
 #pragma unroll
     for (int kk = 0; kk < kStepK; kk += 32) {
       bf16x8 a[2], b[2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        a[i] = *reinterpret_cast<const bf16x8 *>(&As[buf][tile_at<AK>(wm + 16 * i + r, kk + kq)]);
-        b[i] = *reinterpret_cast<const bf16x8 *>(&Bs[buf][tile_at<BK>(wn + 16 * i + r, kk + kq)]);
+      for (int q = 0; q < 2; ++q) {
+        a[q] = *reinterpret_cast<const bf16x8 *>(&As[s][tile_at<AK>(wm + 16 * q + r, kk + kq)]);
+        b[q] = *reinterpret_cast<const bf16x8 *>(&Bs[s][tile_at<BK>(wn + 16 * q + r, kk + kq)]);
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+          acc[q][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q], b[j], acc[q][j], 0, 0, 0);
     }
-    if (more) {
-      tile_store<AK>(As[buf ^ 1], na);
-      tile_store<BK>(Bs[buf ^ 1], nbv);
-    }
+    const int k_n = k_hi - k_lo - (i + 1) * kStepK;   // of tile i + 1; past the end that buffer is not read
+    tile_store<AK>(As[s ^ 1], ra[s ^ 1], k_n);
+    tile_store<BK>(Bs[s ^ 1], rb[s ^ 1], k_n);
     __syncthreads();
-    buf ^= 1;
+  };
+  load(0, ra[0], rb[0]);   // k_lo < k_hi
+  load(min(1, nt - 1), ra[1], rb[1]);
+  tile_store<AK>(As[0], ra[0], k_hi - k_lo);
+  tile_store<BK>(Bs[0], rb[0], k_hi - k_lo);
+  __syncthreads();
+  int i = 0;
+  for (; i + 1 < nt; i += 2) {
+    step(i, std::integral_constant<int, 0>());
+    step(i + 1, std::integral_constant<int, 1>());
   }
+  if (i < nt) step(i, std::integral_constant<int, 0>());
   float sq = 0.f;   // this lane's squared errors
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -276,11 +286,12 @@ __global__ __launch_bounds__(256) void k_grad(GradNet net, int B, int chunk, int
   }
 }
 
-// The end of a backward pass, eight consecutive parameters per thread: the
+// The end of a backward pass, kUpd consecutive parameters per thread: the
 // gradient as the sum of its partial sums in order, then (ADAM) Adam on the
 // packed fp32 parameters and the bf16 copies of the weights, row-major and in
 // fragment order; else the gradient alone.  One launch where reductions,
 // Adam and copies of each layer were eighteen.
+constexpr int kUpd = 4;
 struct UpdateLayer {
   const float *split, *bias;   // S partial weight gradients; kBiasSplit partial bias gradients
   __bf16 *Wb, *Wf;
@@ -297,7 +308,7 @@ struct Adam {
 template <bool ADAM>
 __global__ __launch_bounds__(256) void k_update(UpdateNet net, size_t n, float *p, float *m, float *v, float *grad,
                                                 Adam a) {
-  const size_t i = (blockIdx.x * (size_t)blockDim.x + threadIdx.x) * 8;
+  const size_t i = (blockIdx.x * (size_t)blockDim.x + threadIdx.x) * kUpd;
   if (i >= n) return;
   int l = 0;
   while (l + 1 < net.nl && i >= net.l[l + 1].woff) ++l;
@@ -307,36 +318,35 @@ __global__ __launch_bounds__(256) void k_update(UpdateNet net, size_t n, float *
   const float *src = weight ? L.split + j : L.bias + (j - nw);
   const size_t step = weight ? nw : (size_t)L.N;
   const int parts = weight ? net.S : kBiasSplit;
-  float g[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float g[kUpd] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
   for (int z = 0; z < parts; ++z) {
     const float4 x = *reinterpret_cast<const float4 *>(src + z * step);
-    const float4 y = *reinterpret_cast<const float4 *>(src + z * step + 4);
     g[0] += x.x; g[1] += x.y; g[2] += x.z; g[3] += x.w;
-    g[4] += y.x; g[5] += y.y; g[6] += y.z; g[7] += y.w;
   }
   if (!ADAM) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) grad[i + e] = g[e];
+    *reinterpret_cast<float4 *>(grad + i) = make_float4(g[0], g[1], g[2], g[3]);
     return;
   }
-  bf16x8 b;
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  float pi[kUpd], mi[kUpd], vi[kUpd];
+  bf16x4 b;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float mi = a.b1 * m[i + e] + (1.f - a.b1) * g[e];
-    const float vi = a.b2 * v[i + e] + (1.f - a.b2) * g[e] * g[e];
-    m[i + e] = mi;
-    v[i + e] = vi;
-    const float pi = p[i + e] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
-    p[i + e] = pi;
-    b[e] = (__bf16)pi;
+  for (int e = 0; e < kUpd; ++e) {
+    mi[e] = a.b1 * m[i + e] + (1.f - a.b1) * g[e];
+    vi[e] = a.b2 * v[i + e] + (1.f - a.b2) * g[e] * g[e];
+    pi[e] = p[i + e] - a.lr * (mi[e] / a.c1) / (sqrtf(vi[e] / a.c2) + a.eps);
+    b[e] = (__bf16)pi[e];
   }
+  *reinterpret_cast<float4 *>(m + i) = make_float4(mi[0], mi[1], mi[2], mi[3]);
+  *reinterpret_cast<float4 *>(v + i) = make_float4(vi[0], vi[1], vi[2], vi[3]);
+  *reinterpret_cast<float4 *>(p + i) = make_float4(pi[0], pi[1], pi[2], pi[3]);
   if (!weight) return;
-  *reinterpret_cast<bf16x8 *>(L.Wb + j) = b;
-  // fragment order of k_weights_frag: these are W[row][k .. k + 7]
+  *reinterpret_cast<bf16x4 *>(L.Wb + j) = b;
+  // fragment order of k_weights_frag: half of the 8 values from W[row][k & ~7]
   const int row = (int)(j / L.K), k = (int)(j % L.K);
   const size_t f = ((size_t)(row / 16) * (L.K / 32) + k / 32) * 64 + row % 16 + 16 * (k % 32 / 8);
-  *reinterpret_cast<bf16x8 *>(L.Wf + f * 8) = b;
+  *reinterpret_cast<bf16x4 *>(L.Wf + f * 8 + k % 8) = b;
 }
 
 // ---------------------------------------------------------------------------
@@ -884,7 +894,7 @@ int thor_mlp_loss_grad(thor_mlp *m, const void *x_bf16, const float *t, int B, d
   if (B < 1 || B > m->max_batch || B % 32) { set_error("thor_mlp_loss_grad: batch must be a multiple of 32 within max_batch"); return THOR_EINVAL; }
   if (((uintptr_t)x_bf16 & 15) != 0) { set_error("thor_mlp_loss_grad: inputs must be 16-byte aligned"); return THOR_EINVAL; }
   const int S = loss_and_grad(m, (const __bf16 *)x_bf16, t, B);
-  hipLaunchKernelGGL(k_update<false>, dim3(nb(m->n_params / 8)), dim3(256), 0, m->stream, update_net(m, S),
+  hipLaunchKernelGGL(k_update<false>, dim3(nb(m->n_params / kUpd)), dim3(256), 0, m->stream, update_net(m, S),
                      m->n_params, (float *)nullptr, (float *)nullptr, (float *)nullptr, m->g, Adam{});
   const size_t np = (size_t)((B + kTile - 1) / kTile) * ((m->w[m->nl] + kTile - 1) / kTile);
   std::vector<float> part(np);
@@ -908,7 +918,7 @@ int thor_mlp_train_step(thor_mlp *m, const void *x_bf16, const float *t, int B, 
   m->adam_t += 1;
   const float b1 = 0.9f, b2 = 0.999f;
   const float c1 = 1.f - std::pow(b1, (float)m->adam_t), c2 = 1.f - std::pow(b2, (float)m->adam_t);
-  hipLaunchKernelGGL(k_update<true>, dim3(nb(m->n_params / 8)), dim3(256), 0, m->stream, update_net(m, S),
+  hipLaunchKernelGGL(k_update<true>, dim3(nb(m->n_params / kUpd)), dim3(256), 0, m->stream, update_net(m, S),
                      m->n_params, m->p, m->m, m->v, (float *)nullptr, Adam{lr, b1, b2, 1e-8f, c1, c2});
   return mlp_ok(hipGetLastError(), "train step") ? THOR_OK : THOR_EHIP;
 }
