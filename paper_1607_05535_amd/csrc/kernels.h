@@ -188,8 +188,14 @@ void launch_large(const Fields<H> &f, const Consts &c, int wpb, hipStream_t s, h
                   hipEvent_t ev1 = nullptr);
 template <typename H>
 void launch_diag_field(const Fields<H> &f, const Consts &c, int field, hipStream_t s);
+// The checkpoint's fields into f.diag.
 template <typename H>
-void launch_mass(const Fields<H> &f, const Consts &c, hipStream_t s, int *nblocks_out);
+void launch_export(const Fields<H> &f, const Consts &c, hipStream_t s);
+// Per workgroup: largest speed and |w|, smallest and largest T of Phi[t].
+template <typename H>
+void launch_extremes(const Fields<H> &f, const Consts &c, double *out, hipStream_t s, int *nblocks_out);
+template <typename H>
+void launch_mass(const Fields<H> &f, const Consts &c, double *out, hipStream_t s, int *nblocks_out);
 template <typename H>
 void launch_to_state(const Fields<H> &f, const Consts &c, const double *blob, hipStream_t s);
 // Total energy and mass partial sums of the state Phi[t] (which = 0) or of

@@ -1854,7 +1854,7 @@ __device__ __forceinline__ void b_diag(const Fields<H> &f, const Consts &c, cons
 
 // Mass partial sums and a non-finite count per block (fixed reduction order).
 template <typename H>
-__global__ __launch_bounds__(256) void k_mass(Fields<H> f, Consts c) {
+__global__ __launch_bounds__(256) void k_mass(Fields<H> f, Consts c, double *out) {
   __shared__ double sm[4][2];
   const Lane ln = map_lane(c, xcd_block());
   const int lev = ln.lev, col = ln.col;
@@ -1884,8 +1884,68 @@ __global__ __launch_bounds__(256) void k_mass(Fields<H> f, Consts c) {
       a += sm[i][0];
       b2 += sm[i][1];
     }
-    f.partial[2 * blockIdx.x] = a;
-    f.partial[2 * blockIdx.x + 1] = b2;
+    out[2 * blockIdx.x] = a;
+    out[2 * blockIdx.x + 1] = b2;
+  }
+}
+
+// The prognostic fields rho, Mx, My, Mz, rho theta, W of Phi[t] in FP64 and the
+// canonical [col][lev] layout, one after the other in f.diag: a checkpoint in
+// one launch and one copy, where each field took a launch, a copy and a
+// synchronisation.
+template <typename H>
+__global__ __launch_bounds__(256) void k_export(Fields<H> f, Consts c) {
+  const size_t NL = (size_t)c.N * c.L, i = blockIdx.x * (size_t)256 + threadIdx.x;
+  if (i >= NL) return;
+  const unsigned col = (unsigned)i / (unsigned)c.L, lev = (unsigned)i - col * (unsigned)c.L;
+  const size_t idx = (size_t)col * c.S + lev;
+  f.diag[i] = f.rho_t[idx];
+  f.diag[NL + i] = (double)f.Mx_t[idx];
+  f.diag[2 * NL + i] = (double)f.My_t[idx];
+  f.diag[3 * NL + i] = (double)f.Mz_t[idx];
+  f.diag[4 * NL + i] = f.rth_t[idx];
+  f.diag[5 * NL + i] = lev == 0 ? 0.0 : f.W_t[idx];
+}
+
+// Largest speed and |w|, smallest and largest T of Phi[t] per workgroup
+// (out[4 b] ..), each value as the field diagnostics form it; NaN is passed
+// over, and T of a workgroup without a number is NaN.  Copying the four
+// fields and scanning them on the host took 2040 us at 10242 columns x 37
+// levels; the reduction and the copy of its sums take 70.
+template <typename H>
+__global__ __launch_bounds__(256) void k_extremes(Fields<H> f, Consts c, double *out) {
+  __shared__ double sm[4][4];
+  const size_t NL = (size_t)c.N * c.L, i = blockIdx.x * (size_t)256 + threadIdx.x;
+  double e[4] = {0.0, 0.0, NAN, NAN};
+  if (i < NL) {
+    const unsigned col = (unsigned)i / (unsigned)c.L, lev = (unsigned)i - col * (unsigned)c.L;
+    const size_t idx = (size_t)col * c.S + lev;
+    const double rho = f.rho_t[idx];
+    const double W = lev == 0 ? 0.0 : f.W_t[idx], W1 = (int)lev == c.L - 1 ? 0.0 : f.W_t[idx + 1];
+    const H *fr = f.frame + (size_t)col * kFr;
+    const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
+    const double u = (double)fr[0] * vx + (double)fr[1] * vy + (double)fr[2] * vz;
+    const double v = (double)fr[3] * vx + (double)fr[4] * vy + (double)fr[5] * vz;
+    const double w = 0.5 * (W + W1) / rho;
+    const double p = c.p_ref * powd(c.Rd * f.rth_t[idx] / c.p_ref, c.gamma);
+    e[0] = fmax(0.0, sqrt(u * u + v * v + w * w));
+    e[1] = fmax(0.0, fabs(w));
+    e[2] = e[3] = p / (rho * c.Rd);
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    e[0] = fmax(e[0], __shfl_xor(e[0], o, 64));
+    e[1] = fmax(e[1], __shfl_xor(e[1], o, 64));
+    e[2] = fmin(e[2], __shfl_xor(e[2], o, 64));
+    e[3] = fmax(e[3], __shfl_xor(e[3], o, 64));
+  }
+  if ((threadIdx.x & 63) == 0)
+    for (int k = 0; k < 4; ++k) sm[threadIdx.x >> 6][k] = e[k];
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    const int k = threadIdx.x;
+    double a = sm[0][k];
+    for (int i = 1; i < 4; ++i) a = k == 2 ? fmin(a, sm[i][k]) : fmax(a, sm[i][k]);
+    out[4 * (size_t)blockIdx.x + k] = a;
   }
 }
 
@@ -2238,9 +2298,18 @@ void launch_diag_field(const Fields<H> &f, const Consts &c, int field, hipStream
   hipLaunchKernelGGL(k_diag<H>, dim3(n_blocks(c, 4)), dim3(256), 0, s, f, c, field);
 }
 template <typename H>
-void launch_mass(const Fields<H> &f, const Consts &c, hipStream_t s, int *nblocks_out) {
+void launch_export(const Fields<H> &f, const Consts &c, hipStream_t s) {
+  hipLaunchKernelGGL(k_export<H>, dim3((unsigned)(((size_t)c.N * c.L + 255) / 256)), dim3(256), 0, s, f, c);
+}
+template <typename H>
+void launch_extremes(const Fields<H> &f, const Consts &c, double *out, hipStream_t s, int *nblocks_out) {
+  *nblocks_out = (int)(((size_t)c.N * c.L + 255) / 256);
+  hipLaunchKernelGGL(k_extremes<H>, dim3(*nblocks_out), dim3(256), 0, s, f, c, out);
+}
+template <typename H>
+void launch_mass(const Fields<H> &f, const Consts &c, double *out, hipStream_t s, int *nblocks_out) {
   *nblocks_out = n_blocks(c, 4);
-  hipLaunchKernelGGL(k_mass<H>, dim3(n_blocks(c, 4)), dim3(256), 0, s, f, c);
+  hipLaunchKernelGGL(k_mass<H>, dim3(n_blocks(c, 4)), dim3(256), 0, s, f, c, out);
 }
 template <typename H>
 void launch_energy(const Fields<H> &f, const Consts &c, int which, double *out, hipStream_t s, int *nblocks_out) {
@@ -2303,7 +2372,9 @@ void launch_batch(const Planet<H> *P, const int2 *tiles, int n_tiles, int wpb, i
                                hipEvent_t);                                                          \
   template void launch_large<H>(const Fields<H> &, const Consts &, int, hipStream_t, hipEvent_t, hipEvent_t); \
   template void launch_diag_field<H>(const Fields<H> &, const Consts &, int, hipStream_t);           \
-  template void launch_mass<H>(const Fields<H> &, const Consts &, hipStream_t, int *);               \
+  template void launch_export<H>(const Fields<H> &, const Consts &, hipStream_t);                    \
+  template void launch_extremes<H>(const Fields<H> &, const Consts &, double *, hipStream_t, int *); \
+  template void launch_mass<H>(const Fields<H> &, const Consts &, double *, hipStream_t, int *);     \
   template void launch_to_state<H>(const Fields<H> &, const Consts &, const double *, hipStream_t);  \
   template void launch_energy<H>(const Fields<H> &, const Consts &, int, double *, hipStream_t, int *); \
   template void launch_fixer<H>(const Fields<H> &, const Consts &, hipStream_t);                     \

@@ -427,79 +427,65 @@ int diag_impl(thor_state *s, const Fields<H> &f, int kind, int field, void *host
     set_error("thor_diag: unknown kind");
     return THOR_EINVAL;
   }
-  // mass and non-finite scan
-  int nb = 0;
-  launch_mass(f, c, st, &nb);
-  std::vector<double> part(2 * (size_t)nb);
-  if (!hip_ok(hipMemcpyAsync(part.data(), f.partial, part.size() * sizeof(double), hipMemcpyDeviceToHost, st), "copy partial") ||
-      !hip_ok(hipStreamSynchronize(st), "diag synchronize"))
-    return THOR_EHIP;
-  double mass = 0.0, bad = 0.0;
-  for (int i = 0; i < nb; ++i) {
-    mass += part[2 * i];
-    bad += part[2 * i + 1];
-  }
-  auto field_to_host = [&](int fld, double *dst) -> bool {
-    launch_diag_field(f, c, fld, st);
-    return hip_ok(hipMemcpyAsync(dst, f.diag, NL * sizeof(double), hipMemcpyDeviceToHost, st), "copy field") &&
-           hip_ok(hipStreamSynchronize(st), "diag synchronize");
-  };
-  if (kind == THOR_DIAG_MASS) {
-    *(double *)host_out = mass;
-  } else if (kind == THOR_DIAG_ENERGY) {
-    int ne = 0;
-    launch_energy(f, c, 0, f.partial, st, &ne);
-    std::vector<double> ep(2 * (size_t)ne);
-    if (!hip_ok(hipMemcpyAsync(ep.data(), f.partial, ep.size() * sizeof(double), hipMemcpyDeviceToHost, st), "copy energy") ||
-        !hip_ok(hipStreamSynchronize(st), "diag synchronize"))
-      return THOR_EHIP;
-    double e = 0.0;
-    for (int i = 0; i < ne; ++i) e += ep[2 * i];
-    *(double *)host_out = e;
+  // Every kernel of the request is enqueued before the one synchronisation.
+  // The mass and the non-finite scan come with each; a second reduction's sums
+  // lie in the staging area before theirs, so that one copy fetches both.
+  int nb = 0, nx = 0, each = 0;   // workgroups, doubles per workgroup of the second reduction
+  double *sums = f.diag;
+  if (kind == THOR_DIAG_ENERGY) {
+    launch_energy(f, c, 0, f.diag, st, &nx);
+    each = 2;
   } else if (kind == THOR_DIAG_ANGULAR_MOMENTUM) {
-    int na = 0;
-    launch_angmom(f, c, f.partial, st, &na);
-    std::vector<double> ap((size_t)na);
-    if (!hip_ok(hipMemcpyAsync(ap.data(), f.partial, ap.size() * sizeof(double), hipMemcpyDeviceToHost, st), "copy angular momentum") ||
-        !hip_ok(hipStreamSynchronize(st), "diag synchronize"))
-      return THOR_EHIP;
-    double a = 0.0;
-    for (int i = 0; i < na; ++i) a += ap[i];
-    *(double *)host_out = a;
-  } else if (kind == THOR_DIAG_FIELD) {
-    if (!field_to_host(field, (double *)host_out)) return THOR_EHIP;
+    launch_angmom(f, c, f.diag, st, &nx);
+    each = 1;
   } else if (kind == THOR_DIAG_SCALARS) {
-    std::vector<double> a(NL), b(NL), w(NL);
-    thor_scalars sc{};
-    sc.mass = mass;
-    if (!field_to_host(THOR_F_U, a.data()) || !field_to_host(THOR_F_V, b.data()) || !field_to_host(THOR_F_W, w.data()))
-      return THOR_EHIP;
-    double ms = 0, mw = 0;
-    for (size_t i = 0; i < NL; ++i) {
-      ms = std::fmax(ms, std::sqrt(a[i] * a[i] + b[i] * b[i] + w[i] * w[i]));
-      mw = std::fmax(mw, std::fabs(w[i]));
-    }
-    if (!field_to_host(THOR_F_T, a.data())) return THOR_EHIP;
-    double tmin = a[0], tmax = a[0];
-    for (size_t i = 0; i < NL; ++i) {
-      tmin = std::fmin(tmin, a[i]);
-      tmax = std::fmax(tmax, a[i]);
-    }
-    sc.max_speed = ms;
-    sc.max_w = mw;
-    sc.min_T = tmin;
-    sc.max_T = tmax;
-    std::memcpy(host_out, &sc, sizeof(sc));
+    launch_extremes(f, c, f.diag, st, &nx);
+    each = 4;
   } else {
+    sums = f.partial;   // the staging area takes the fields
+  }
+  launch_mass(f, c, sums + (size_t)each * nx, st, &nb);
+  std::vector<double> extra((size_t)each * nx + 2 * (size_t)nb);
+  bool ok = hip_ok(hipMemcpyAsync(extra.data(), sums, extra.size() * sizeof(double), hipMemcpyDeviceToHost, st), "copy sums");
+  if (kind == THOR_DIAG_FIELD) {
+    launch_diag_field(f, c, field, st);
+    ok = ok && hip_ok(hipMemcpyAsync(host_out, f.diag, NL * sizeof(double), hipMemcpyDeviceToHost, st), "copy field");
+  } else if (kind == THOR_DIAG_STATE_EXPORT) {
     // checkpoint: header (magic, N, L) then rho, Mx, My, Mz, rho theta, W
     double *out = (double *)host_out;
     out[0] = 1953460050.0;  // 'THOR' tag
     out[1] = (double)c.N;
     out[2] = (double)c.L;
     out[3] = 0.0;
-    const int flds[6] = {THOR_F_RHO, THOR_F_MX, THOR_F_MY, THOR_F_MZ, THOR_F_RHOTHETA, THOR_F_WI};
-    for (int i = 0; i < 6; ++i)
-      if (!field_to_host(flds[i], out + 4 + i * NL)) return THOR_EHIP;
+    launch_export(f, c, st);
+    ok = ok && hip_ok(hipMemcpyAsync(out + 4, f.diag, 6 * NL * sizeof(double), hipMemcpyDeviceToHost, st), "copy state");
+  }
+  if (!hip_ok(hipStreamSynchronize(st), "diag synchronize") || !ok) return THOR_EHIP;
+  const double *part = extra.data() + (size_t)each * nx;
+  double mass = 0.0, bad = 0.0;
+  for (int i = 0; i < nb; ++i) {
+    mass += part[2 * i];
+    bad += part[2 * i + 1];
+  }
+  if (kind == THOR_DIAG_MASS) {
+    *(double *)host_out = mass;
+  } else if (kind == THOR_DIAG_ENERGY) {
+    double e = 0.0;
+    for (int i = 0; i < nx; ++i) e += extra[2 * i];
+    *(double *)host_out = e;
+  } else if (kind == THOR_DIAG_ANGULAR_MOMENTUM) {
+    double a = 0.0;
+    for (int i = 0; i < nx; ++i) a += extra[i];
+    *(double *)host_out = a;
+  } else if (kind == THOR_DIAG_SCALARS) {
+    thor_scalars sc{mass, 0.0, 0.0, extra[2], extra[3]};
+    for (int i = 0; i < nx; ++i) {
+      sc.max_speed = std::fmax(sc.max_speed, extra[4 * (size_t)i]);
+      sc.max_w = std::fmax(sc.max_w, extra[4 * (size_t)i + 1]);
+      sc.min_T = std::fmin(sc.min_T, extra[4 * (size_t)i + 2]);
+      sc.max_T = std::fmax(sc.max_T, extra[4 * (size_t)i + 3]);
+    }
+    std::memcpy(host_out, &sc, sizeof(sc));
   }
   if (bad > 0) {
     set_error("thor_diag: state holds non-finite values");
