@@ -86,6 +86,7 @@ struct Consts {
   int hlpc, hcpw;         // phase-M mapping: lanes per column, columns per wavefront
   double radius, omega, grav, Rd, Cp, Cv, gamma, p_ref;
   double dz, Kd;
+  double idz, rd_p;       // 1 / dz and Rd / p_ref
   double rdz;             // radial spacing of the levels: dz, or 0 (shallow atmosphere)
   double dt;
   int div_damp;

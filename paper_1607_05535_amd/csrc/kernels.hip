@@ -97,7 +97,7 @@ __device__ __forceinline__ float shfl(float v, int src) { return __shfl(v, src, 
 
 template <typename H>
 __device__ __forceinline__ H eos(double rth, const Consts &c) {
-  return (H)(c.p_ref * powd(c.Rd * rth / c.p_ref, c.gamma));
+  return (H)(c.p_ref * powd(c.rd_p * rth, c.gamma));
 }
 
 // Distance from the planet's centre of level centres and interfaces; the
@@ -106,15 +106,33 @@ __device__ __forceinline__ H eos(double rth, const Consts &c) {
 __device__ __forceinline__ double radius_c(const Consts &c, int lev) { return c.radius + (lev + 0.5) * c.rdz; }
 __device__ __forceinline__ double radius_i(const Consts &c, int lev) { return c.radius + lev * c.rdz; }
 
-// 1 / x from the hardware reciprocal estimate refined by two Newton steps
-// (within an ulp or two of the quotient; for the geometric factors and the
-// pivots of the column solve, where no correctly rounded quotient is needed).
+// 1 / x from the hardware reciprocal estimate refined by Newton steps, the
+// last of which leaves half a unit of rounding and a term below 2^-40 of it;
+// x / y from r = 1 / y with the remainder's correction, rounded as well.
+// For normal operands and quotients (densities, pressures, radii, pivots).
+// The compiler's division also scales its operands and repairs special
+// cases, 11 instructions to 5 and 3: 21 of them made up 40 % of the FP64
+// instructions of the slow terms, 32 were 55 % of the large step's first
+// pass.  Large step g5 L37 37.2 -> 35.1 us, mixed 36.0 -> 33.1; slow terms
+// 12.85 -> 12.6 and 10.1 -> 9.4; phase V 14.7 -> 14.4 and 11.7 -> 11.5.
 __device__ __forceinline__ double rcpd(double x) {
   double r = __builtin_amdgcn_rcp(x);
   double e = fma(-x, r, 1.0);
   r = fma(r, e, r);
   e = fma(-x, r, 1.0);
   return fma(r, e, r);
+}
+__device__ __forceinline__ float rcpd(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(r, fmaf(-x, r, 1.0f), r);
+}
+__device__ __forceinline__ double quot(double x, double y, double r) {
+  const double q = x * r;
+  return fma(fma(-y, q, x), r, q);
+}
+__device__ __forceinline__ float quot(float x, float y, float r) {
+  const float q = x * r;
+  return fmaf(fmaf(-y, q, x), r, q);
 }
 
 // Neighbour ids of a column; a pentagon's missing 6th neighbour points at the
@@ -323,7 +341,7 @@ __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, 
   if (LDSW) wave_copy_wait();
   H ir[kHq];
 #pragma unroll
-  for (int q = 0; q < kHq; ++q) ir[q] = (H)1 / (H)radius_c(c, ln.lev0 + q);
+  for (int q = 0; q < kHq; ++q) ir[q] = rcpd((H)radius_c(c, ln.lev0 + q));
   H ga[kHq], gb[kHq];
 #pragma unroll
   for (int q = 0; q < kHq; ++q) ga[q] = gb[q] = 0;
@@ -601,7 +619,7 @@ __device__ __forceinline__ void b_vert(const Fields<H> &f, const Consts &c, cons
   double rho_new = rhs - ap * Wp + am * Wn;
   if (end) rho_new += rt;
   double rth_new = rth_hat - ap * thI_p * Wp + am * thI * Wn;
-  double p = c.p_ref * powd(c.Rd * rth_new / c.p_ref, c.gamma);
+  double p = c.p_ref * powd(c.rd_p * rth_new, c.gamma);
   double hs_sigma = 0.0;
   if (LAST && c.forcing != THOR_FORCING_NONE) {
     const int l0 = ln.lane - lev;   // the column's lowest cell
@@ -798,7 +816,7 @@ __device__ __forceinline__ void b_vert2(const Fields<H> &f, const Consts &c, con
     rho_new[q] = rhs[q] - ap * Wp[q] + am * Wn[q];
     if (end) rho_new[q] += rt[q];
     rth_new[q] = rth_hat[q] - ap * thIp * Wp[q] + am * thI[q] * Wn[q];
-    p[q] = c.p_ref * powd(c.Rd * rth_new[q] / c.p_ref, c.gamma);
+    p[q] = c.p_ref * powd(c.rd_p * rth_new[q], c.gamma);
   }
   double hs_sigma[2] = {0.0, 0.0};
   if (LAST && c.forcing != THOR_FORCING_NONE) {
@@ -897,7 +915,7 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
 
   // radial factors g+ = r_I(k+1)^2 / (r_C^2 dz), g- = r_I(k)^2 / (r_C^2 dz)
   // and 1 / r_C of cells lev0 - 1 .. lev0 + 3 (index k - lev0 + 1)
-  const double idz = 1.0 / c.dz;
+  const double idz = c.idz;
   double gp[kHq + 1], gm[kHq + 1], irc[kHq + 1];
 #pragma unroll
   for (int k = 0; k <= kHq; ++k) {
@@ -1141,7 +1159,7 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
     }
     if (end) rho_new[q] += rt[q];
     rth_new[q] = rth_hat[q] - ap * thIp * Wp[q] + am * thI[q] * Wn[q];
-    p[q] = c.p_ref * powd(c.Rd * rth_new[q] / c.p_ref, c.gamma);
+    p[q] = c.p_ref * powd(c.rd_p * rth_new[q], c.gamma);
   }
   double hs_sigma[kHq] = {0.0, 0.0, 0.0, 0.0};
   if (LAST && c.forcing != THOR_FORCING_NONE) {
@@ -1286,7 +1304,7 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
         fy[q] = my0[q] + wbar * ry;
         fz[q] = mz0[q] + wbar * rz;
       }
-      const H irho0 = (H)1 / (H)rho0[q];
+      const H irho0 = rcpd((H)rho0[q]);
       vx0[q] = fx[q] * irho0;
       vy0[q] = fy[q] * irho0;
       vz0[q] = fz[q] * irho0;
@@ -1340,7 +1358,7 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
     for (int q = 0; q < kHq; ++q) {
       const double up = lev0 + q == L - 1 ? 0.0 : (q + 1 < kHq ? wn[q + 1] : wnn);
       const H wb = ORD == 3 ? (H)cubic_i2c(wwin + q + 1, lev0 + q, L) : (H)(0.5 * (wn[q] + up));
-      const H t = tj[q] / (H)rj[q];
+      const H r = (H)rj[q], t = quot(tj[q], r, rcpd(r));
       if (SHALLOW) {
         Ax[q] += mxj[q] * t;
         Ay[q] += myj[q] * t;
@@ -1392,11 +1410,11 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
     const H nx = shfl(Fx[0], lp), ny = shfl(Fy[0], lp), nz = shfl(Fz[0], lp);
     const H nr = SHALLOW ? shfl(Fr[0], lp) : (H)0;
     const H om2 = (H)(2.0 * c.omega);
-    const H idz = (H)(1.0 / c.dz);
+    const H idz = (H)c.idz;
 #pragma unroll
     for (int q = 0; q < kHq; ++q) {
       const int lev = lev0 + q;
-      const H irc = (H)1 / (H)radius_c(c, lev);
+      const H irc = rcpd((H)radius_c(c, lev));
       H Fx1 = q + 1 < kHq ? Fx[q + 1] : nx, Fy1 = q + 1 < kHq ? Fy[q + 1] : ny,
         Fz1 = q + 1 < kHq ? Fz[q + 1] : nz;
       if (lev == L - 1) Fx1 = Fy1 = Fz1 = 0;
@@ -1450,8 +1468,8 @@ __device__ __forceinline__ void slow_cells(const Fields<H> &f, const Consts &c, 
       sw[q] = lev0 + q == 0 ? 0.0 : fw[q] - 0.5 * ((double)am + (double)acr[q]);
     // linearisation coefficients
     const double p0 = pt[q] + (FROM_T ? 0.0 : (double)ps[q]);
-    thl[q] = (H)(rth0[q] / rho0[q]);
-    gam[q] = (H)(c.gamma * p0 / rth0[q]);
+    thl[q] = (H)quot(rth0[q], rho0[q], rcpd(rho0[q]));
+    gam[q] = (H)quot(c.gamma * p0, rth0[q], rcpd(rth0[q]));
   }
   st4<VEC>(f.SMa + idx, nv, sma);
   st4<VEC>(f.SMb + idx, nv, smb);
@@ -1506,25 +1524,25 @@ __device__ __forceinline__ void large0_cells(const Fields<H> &f, const Consts &c
   double p[kHq], wI[kHq];
 #pragma unroll
   for (int q = 0; q < kHq; ++q) {
-    p[q] = c.p_ref * powd(c.Rd * rth[q] / c.p_ref, c.gamma);
-    wI[q] = lev0 + q == 0 ? 0.0 : W[q] / rhoI[q];
+    p[q] = c.p_ref * powd(c.rd_p * rth[q], c.gamma);
+    wI[q] = lev0 + q == 0 ? 0.0 : quot(W[q], rhoI[q], rcpd(rhoI[q]));
   }
   st4<VEC>(f.p_t + idx, nv, p);
   st4<VEC>(f.wI + idx, nv, wI);
 }
 
-// The velocity M / rho and temperature p / (rho Rd) of kHq cells, the
-// Laplacian inputs of the momentum and pressure hyperdiffusion, formed where
+// The velocity M / rho and Rd T = p / rho of kHq cells, the Laplacian
+// inputs of the momentum and pressure hyperdiffusion, formed where
 // they are gathered (every cell forms them the same way, so a neighbour's
 // value equals its own).
 template <typename H>
-__device__ __forceinline__ void vel_temp(const Consts &c, const double rho[kHq], const double p[kHq], const H mx[kHq],
-                                         const H my[kHq], const H mz[kHq], double vx[kHq], double vy[kHq],
-                                         double vz[kHq], double T[kHq]) {
+__device__ __forceinline__ void vel_temp(const double rho[kHq], const double p[kHq], const H mx[kHq], const H my[kHq],
+                                         const H mz[kHq], double vx[kHq], double vy[kHq], double vz[kHq],
+                                         double T[kHq]) {
 #pragma unroll
   for (int q = 0; q < kHq; ++q) {
-    const double irho = 1.0 / rho[q];
-    T[q] = p[q] * irho / c.Rd;
+    const double irho = rcpd(rho[q]);
+    T[q] = p[q] * irho;
     vx[q] = (double)mx[q] * irho;
     vy[q] = (double)my[q] * irho;
     vz[q] = (double)mz[q] * irho;
@@ -1616,7 +1634,7 @@ __device__ __forceinline__ void large1_cells(const Fields<H> &f, const Consts &c
 #pragma unroll
   for (int q = 0; q < kHq; ++q) {
     const double rC = radius_c(c, lev0 + q);
-    irc2[q] = 1.0 / (rC * rC);
+    irc2[q] = rcpd(rC * rC);
   }
   // Laplacian fields: rho, vx, vy, vz, T, w (rho is rho[] itself)
   double s0[6][kHq], lap[6][kHq];
@@ -1628,7 +1646,7 @@ __device__ __forceinline__ void large1_cells(const Fields<H> &f, const Consts &c
     ld4<VEC>(f.Mz_t + idx, nv, mz);
 #pragma unroll
     for (int q = 0; q < kHq; ++q) dm[q] = dch[0] * mx[q] + dch[1] * my[q] + dch[2] * mz[q];
-    vel_temp<H>(c, rho, p, mx, my, mz, s0[1], s0[2], s0[3], s0[4]);
+    vel_temp<H>(rho, p, mx, my, mz, s0[1], s0[2], s0[3], s0[4]);
   }
 #pragma unroll
   for (int q = 0; q < kHq; ++q) s0[0][q] = rho[q];
@@ -1648,7 +1666,7 @@ __device__ __forceinline__ void large1_cells(const Fields<H> &f, const Consts &c
     ld4<VEC>(f.My_t + nj, nv, my);
     ld4<VEC>(f.Mz_t + nj, nv, mz);
     ld4<VEC>(f.wI + nj, nv, sj[5]);
-    vel_temp<H>(c, sj[0], pj, mx, my, mz, sj[1], sj[2], sj[3], sj[4]);
+    vel_temp<H>(sj[0], pj, mx, my, mz, sj[1], sj[2], sj[3], sj[4]);
     const double w = (double)lch[j];
     const H hx = dch[3 * (j + 1)], hy = dch[3 * (j + 1) + 1], hz = dch[3 * (j + 1) + 2];
 #pragma unroll
@@ -1678,7 +1696,7 @@ __device__ __forceinline__ void large1_cells(const Fields<H> &f, const Consts &c
     for (int q = 0; q < kHq; ++q) {
       const int lev = lev0 + q;
       const double rI = radius_i(c, lev);
-      l[q] = lev == 0 ? 0.0 : rhoI[q] * Kd / (rI * rI) * lap[5][q];
+      l[q] = lev == 0 ? 0.0 : rhoI[q] * Kd * rcpd(rI * rI) * lap[5][q];
     }
     st4<VEC>(f.Xw + idx, nv, l);
   }
@@ -1689,11 +1707,11 @@ __device__ __forceinline__ void large1_cells(const Fields<H> &f, const Consts &c
     for (int q = 0; q < kHq; ++q) {
       const int lev = lev0 + q;
       const double rC = radius_c(c, lev), rI = radius_i(c, lev);
-      const double irc = 1.0 / rC;
+      const double irc = rcpd(rC);
       const double W1 = lev == L - 1 ? 0.0 : (q + 1 < kHq ? W[q + 1] : W_n);
       const double Wl = lev == 0 ? 0.0 : W[q];
       const double rI1 = rI + c.rdz;
-      Dt[q] = (H)((double)dm[q] * irc + (rI1 * rI1 * W1 - rI * rI * Wl) * (irc * irc / c.dz));
+      Dt[q] = (H)((double)dm[q] * irc + (rI1 * rI1 * W1 - rI * rI * Wl) * (irc * irc * c.idz));
     }
     st4<VEC>(f.Dt + idx, nv, Dt);
   }
@@ -1725,7 +1743,7 @@ __device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c
 #pragma unroll
   for (int q = 0; q < kHq; ++q) {
     const double rC = radius_c(c, lev0 + q);
-    irc2[q] = 1.0 / (rC * rC);
+    irc2[q] = rcpd(rC * rC);
   }
   {
     double l[kHq];
@@ -1759,7 +1777,7 @@ __device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c
       }
 #pragma unroll
       for (int q = 0; q < kHq; ++q) {
-        const double irc = 1.0 / radius_c(c, lev0 + q);
+        const double irc = rcpd(radius_c(c, lev0 + q));
         fa[q] = (H)(-(ga[q] * irc));
         fb[q] = (H)(-(gb[q] * irc));
       }
@@ -1788,9 +1806,9 @@ __device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c
     for (int q = 0; q < kHq; ++q) {
       const int lev = lev0 + q;
       const double pm = q ? p[q - 1] : p_m, rm = q ? rho[q - 1] : rho_m;
-      fw[q] = lev == 0 ? 0.0 : -(p[q] - pm) / c.dz - 0.5 * c.grav * (rm + rho[q]);
+      fw[q] = lev == 0 ? 0.0 : -(p[q] - pm) * c.idz - 0.5 * c.grav * (rm + rho[q]);
       const double rI = radius_i(c, lev);
-      if (lev > 0) fw[q] += -l[q] / (rI * rI);
+      if (lev > 0) fw[q] += -l[q] * rcpd(rI * rI);
     }
     st4<VEC>(f.FW + idx, nv, fw);
   }
@@ -1801,7 +1819,10 @@ __device__ __forceinline__ void large2_cells(const Fields<H> &f, const Consts &c
     ld4<VEC>(f.p_t + idx, nv, p);
     H h[kHq];
 #pragma unroll
-    for (int q = 0; q < kHq; ++q) h[q] = (H)(rth[q] / (c.gamma * p[q]) * (-c.Rd * irc2[q] * l[q]));
+    for (int q = 0; q < kHq; ++q) {
+      const double gp = c.gamma * p[q];
+      h[q] = (H)(quot(rth[q], gp, rcpd(gp)) * (-irc2[q] * l[q]));
+    }
     st4<VEC>(f.Hrth + idx, nv, h);
   }
 }
@@ -1828,7 +1849,7 @@ __device__ __forceinline__ void b_diag(const Fields<H> &f, const Consts &c, cons
   const double rho = f.rho_t[idx];
   double out = 0.0;
   if (field == THOR_F_T || field == THOR_F_P) {
-    const double p = c.p_ref * powd(c.Rd * f.rth_t[idx] / c.p_ref, c.gamma);
+    const double p = c.p_ref * powd(c.rd_p * f.rth_t[idx], c.gamma);
     out = field == THOR_F_P ? p : p / (rho * c.Rd);
   } else if (field == THOR_F_U || field == THOR_F_V) {
     const H *e = f.frame + (size_t)col * kFr + (field == THOR_F_U ? 0 : 3);
@@ -1927,7 +1948,7 @@ __global__ __launch_bounds__(256) void k_extremes(Fields<H> f, Consts c, double 
     const double u = (double)fr[0] * vx + (double)fr[1] * vy + (double)fr[2] * vz;
     const double v = (double)fr[3] * vx + (double)fr[4] * vy + (double)fr[5] * vz;
     const double w = 0.5 * (W + W1) / rho;
-    const double p = c.p_ref * powd(c.Rd * f.rth_t[idx] / c.p_ref, c.gamma);
+    const double p = c.p_ref * powd(c.rd_p * f.rth_t[idx], c.gamma);
     e[0] = fmax(0.0, sqrt(u * u + v * v + w * w));
     e[1] = fmax(0.0, fabs(w));
     e[2] = e[3] = p / (rho * c.Rd);
@@ -1976,7 +1997,7 @@ __global__ __launch_bounds__(256) void k_energy(Fields<H> f, Consts c, int which
     const double rC = radius_c(c, lev);
     const double vol = f.area[col] * rC * rC * c.dz;
     const double rho = rho_a[idx];
-    const double p = c.p_ref * powd(c.Rd * rth_a[idx] / c.p_ref, c.gamma);
+    const double p = c.p_ref * powd(c.rd_p * rth_a[idx], c.gamma);
     const double mx = (double)Mx[idx], my = (double)My[idx], mz = (double)Mz[idx];
     const double wc = 0.5 * (W + W1);
     const double ke = 0.5 * (mx * mx + my * my + mz * mz + wc * wc) / rho;
@@ -2035,7 +2056,7 @@ __global__ __launch_bounds__(256) void k_fixphys(Fields<H> f, Consts c, const do
   const Lane ln = map_lane(c, xcd_block());
   const size_t idx = (size_t)ln.col * c.S + ln.lev;
   const double rho = f.rho[idx];
-  const double p0 = c.p_ref * powd(c.Rd * f.rth[idx] / c.p_ref, c.gamma);
+  const double p0 = c.p_ref * powd(c.rd_p * f.rth[idx], c.gamma);
   double p = rho * c.Rd * (p0 / (rho * c.Rd) + *dT);
   double sigma = 0.0;
   const int l0 = ln.lane - ln.lev;   // the column's lowest cell

@@ -545,6 +545,8 @@ int thor_state_init(const thor_grid *g, const thor_planet *pl, const thor_vertic
   c.gamma = pl->Cp / c.Cv;
   c.p_ref = pl->p_ref;
   c.dz = v->z_top / v->n_lev;
+  c.idz = 1.0 / c.dz;
+  c.rd_p = pl->Rd / pl->p_ref;
   const double dbar = std::sqrt(2.0 * M_PI / 5.0) * pl->radius / std::ldexp(1.0, g->g.glevel);  // Eq. grid_qts
   c.Kd = num->diff_D * std::pow(dbar, 4) / num->dt;                                             // Eq. kd
   c.dt = num->dt;
