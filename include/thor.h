@@ -426,9 +426,11 @@ int thor_mlp_forward(thor_mlp *m, const void *x_bf16, int B, float *y);
  * corrector's shape) as one fused kernel per 48-row tile: the tile's inputs
  * and then its hidden activations kept in LDS (147,456 bytes per
  * workgroup), the weights read from a copy in MFMA fragment order kept
- * beside the BF16 copy; other shapes stay layer by layer.  on = 0: layer by
- * layer.
- * Both give the same products in the same order (equal outputs). */
+ * beside the BF16 copy; thor_mlp_loss_grad and thor_mlp_train_step run the
+ * forward and backward products of such a network as one fused kernel.
+ * Other shapes stay layer by layer.  on = 0: layer by layer.
+ * Both give the same products in the same order (equal outputs, gradients
+ * and parameters; the loss adds its squares in another order). */
 int thor_mlp_set_fused(thor_mlp *m, int on);
 
 /* Mean-squared loss sum (y - t)^2 / (B out) and, if grad_host is not NULL,

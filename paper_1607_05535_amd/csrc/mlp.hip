@@ -10,9 +10,10 @@
 //   input grad dH = dZ W           A = dZ [B][out],      B = W read as [k=out][n=in]
 //   weight grad dW = dZ^T H_prev   A = dZ read as [k=B][m=out], B = H_prev read as [k=B][n=in]
 // Pre-activation gradients are formed in the epilogues of the products before
-// them, and the gradients of all layers and the update take one launch each: an
-// Adam step at the corrector's shape (4096 rows) is 9 launches and 136 us, where
-// a kernel per layer and purpose took 35 and 287.
+// them, and the gradients of all layers and the update take one launch each.
+// For the corrector's shape the forward and backward products are one launch
+// too (k_mlp_train4): an Adam step on 4096 rows is 3 launches and 53 us, where
+// a kernel per layer and purpose took 35 and 260.
 // The weight gradient reduces over the batch in fixed chunks (split K) whose
 // partial sums are added in a fixed order, so results are reproducible.
 #include <hip/hip_runtime.h>
@@ -286,6 +287,12 @@ __global__ __launch_bounds__(256) void k_grad(GradNet net, int B, int chunk, int
   }
 }
 
+// Position of W[n][k], N rows, in the transposed copy in fragment order (see
+// k_weights_frag_t).
+__device__ __forceinline__ size_t frag_t(int n, int k, int N) {
+  return (((size_t)(k / 16) * (N / 32) + n / 32) * 64 + k % 16 + 16 * (n % 32 / 8)) * 8 + n % 8;
+}
+
 // The end of a backward pass, kUpd consecutive parameters per thread: the
 // gradient as the sum of its partial sums in order, then (ADAM) Adam on the
 // packed fp32 parameters and the bf16 copies of the weights, row-major and in
@@ -294,7 +301,7 @@ __global__ __launch_bounds__(256) void k_grad(GradNet net, int B, int chunk, int
 constexpr int kUpd = 4;
 struct UpdateLayer {
   const float *split, *bias;   // S partial weight gradients; kBiasSplit partial bias gradients
-  __bf16 *Wb, *Wf;
+  __bf16 *Wb, *Wf, *Wt;        // Wt: null unless the fused training pass reads it
   size_t woff;                 // weights at woff, biases at woff + N K
   int N, K;
 };
@@ -347,6 +354,11 @@ __global__ __launch_bounds__(256) void k_update(UpdateNet net, size_t n, float *
   const int row = (int)(j / L.K), k = (int)(j % L.K);
   const size_t f = ((size_t)(row / 16) * (L.K / 32) + k / 32) * 64 + row % 16 + 16 * (k % 32 / 8);
   *reinterpret_cast<bf16x4 *>(L.Wf + f * 8 + k % 8) = b;
+  if (L.Wt) {
+    __bf16 *t = L.Wt + frag_t(row, k, L.N);
+#pragma unroll
+    for (int e = 0; e < kUpd; ++e) t[8 * e] = b[e];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -429,28 +441,28 @@ __device__ __forceinline__ void fused_load(const FusedW &fw, int t, bf16x8 fr[kF
 // layer's k, with ring[d] holding substep d on entry (the caller issues
 // those loads early: before the input tile's wait, or before the previous
 // layer's epilogue).  KC: the layer's k width if known at compile time,
-// else 0.  XS: A is the staged input tile ([k / 8][row][8]), else the
-// hidden activations ([row][kHRow]).  Tiles with use[j] false are loaded
+// else 0.  XS: A is the staged input tile ([k / 8][SLOTS rows][8]), else the
+// hidden activations ([row][kHRow]).  FI: 16-row tiles of the workgroup.  Tiles with use[j] false are loaded
 // (from a valid row) but not multiplied.  The ring is refilled
 // unconditionally, so every substep issues the same loads and the wait
 // before a substep's products covers only its own fragments, kFD substeps
 // old.
-template <bool XS, int KC>
+template <bool XS, int KC, int FI, int SLOTS>
 __device__ __forceinline__ void fused_layer(const FusedW &fw, const bool use[kFT], const __bf16 *lds,
-                                            f32x4 acc[kFI][kFT], bf16x8 ring[kFD][kFT]) {
+                                            f32x4 acc[FI][kFT], bf16x8 ring[kFD][kFT]) {
   const int lane = threadIdx.x & 63, r = lane & 15, kq = (lane >> 4) * 8;
   const int nsub = KC ? KC >> 5 : fw.nsub, nfull = nsub / kFD;
   auto mul = [&](int t, const bf16x8 fr[kFT]) {
-    bf16x8 a[kFI];
+    bf16x8 a[FI];
 #pragma unroll
-    for (int i = 0; i < kFI; ++i)
-      a[i] = XS ? *reinterpret_cast<const bf16x8 *>(lds + ((((32 * t + kq) >> 3) * kFR) + 16 * i + r) * 8)
+    for (int i = 0; i < FI; ++i)
+      a[i] = XS ? *reinterpret_cast<const bf16x8 *>(lds + ((((32 * t + kq) >> 3) * SLOTS) + 16 * i + r) * 8)
                 : *reinterpret_cast<const bf16x8 *>(lds + (16 * i + r) * kHRow + 32 * t + kq);
 #pragma unroll
     for (int j = 0; j < kFT; ++j)
       if (use[j])
 #pragma unroll
-        for (int i = 0; i < kFI; ++i)
+        for (int i = 0; i < FI; ++i)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], fr[j], acc[i][j], 0, 0, 0);
   };
   for (int b = 0; b < nfull; ++b) {
@@ -507,9 +519,9 @@ __global__ __launch_bounds__(64 * kFW) void k_mlp_fused4(FusedNet net, const __b
 #pragma unroll
       for (int j = 0; j < kFT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (l == 0)
-      fused_layer<true, 0>(fw, use, lds, acc, ring);
+      fused_layer<true, 0, kFI, kFR>(fw, use, lds, acc, ring);
     else
-      fused_layer<false, kFH>(fw, use, lds, acc, ring);
+      fused_layer<false, kFH, kFI, kFR>(fw, use, lds, acc, ring);
     // the next layer's first weights go in flight before this epilogue
     int tile_n[kFT];
     bool use_n[kFT];
@@ -551,6 +563,173 @@ __global__ __launch_bounds__(64 * kFW) void k_mlp_fused4(FusedNet net, const __b
   }
 }
 
+// ---------------------------------------------------------------------------
+// Forward and backward pass of the same networks in one launch: a workgroup
+// takes 16 FI rows through the four layers and back to the gradient of the
+// first layer's pre-activation, seven products whose operand passes from one
+// to the next in LDS (two buffers in turn, so one barrier a product) while
+// the next product's first weights are in flight.  A wavefront owns the same
+// column tiles in every hidden layer, so the pre-activations that the
+// backward pass needs stay in its registers.  To memory go the activations
+// and the gradients of the pre-activations, for the weight gradients.  The
+// backward products read W with the output index as k, from a transposed
+// copy in fragment order.
+// As seven products of 64 x 64 tiles, each a launch of 256 workgroups or
+// fewer that waits on its operands for most of 8-17 us, they took 75 us at
+// 4096 rows; this takes 23, and an Adam step 100 -> 53 (256 rows 76 -> 33,
+// 8192 rows 133 -> 77).  Here the bound is the weights' way from L2, 1.26 MB
+// per workgroup at the corrector's widths, 8 us at 64 bytes per clock, and
+// the seven latencies.
+// Products and their order equal k_gemm's, so the results do bit for bit.
+// ---------------------------------------------------------------------------
+struct TrainNet {
+  const __bf16 *W[4], *Wt[4];   // fragment order; Wt: transposed (unused for the first layer)
+  const float *b[4];
+  __bf16 *H[3], *dZb[4];
+  float *dZ[4];
+  int in, out;
+};
+
+// Largest batch in 16-row workgroups: up to one workgroup per compute unit
+// they leave fewer units idle (an Adam step on 2048 / 4096 rows 41.6 / 52.8
+// us against 45.9 / 55.4 with 32), past that 32 rows per workgroup fetch the
+// weights half as often (6144 / 8192 rows 65.0 / 76.5 us against 77.5 / 88.8).
+constexpr int kTrain16 = 16 * 256;
+
+// R rows of N bf16 values from LDS rows of kHRow to dst[R][N], N % 8 == 0.
+template <int R>
+__device__ __forceinline__ void store_rows(const __bf16 *src, __bf16 *dst, int N) {
+  const int per = N / 8;
+  for (int i = threadIdx.x; i < R * per; i += 64 * kFW) {
+    const int row = i / per, c = 8 * (i - row * per);
+    *reinterpret_cast<bf16x8 *>(dst + (size_t)row * N + c) = *reinterpret_cast<const bf16x8 *>(src + row * kHRow + c);
+  }
+}
+
+template <int FI>
+__global__ __launch_bounds__(64 * kFW) void k_mlp_train4(TrainNet net, const __bf16 *__restrict__ X,
+                                                         const float *__restrict__ T, float scale,
+                                                         float *__restrict__ loss) {
+  constexpr int R = 16 * FI, KB = 64 / R;   // rows; 8-value k blocks per wavefront load
+  __shared__ __align__(16) __bf16 xs[kFK0Max * R];
+  __shared__ __align__(16) __bf16 hid[2][R * kHRow];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int r = lane & 15, r4 = (lane >> 4) * 4;
+  const size_t m0 = (size_t)blockIdx.x * R;
+  const int K0 = net.in, N3 = net.out;
+  {
+    // input tile [k / 8][row][8]: lane = (k block, row)
+    const __bf16 *src = X + (m0 + lane % R) * K0 + 8 * (lane / R);
+    for (int i = w; i < K0 / (8 * KB); i += kFW)
+      __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void *)(src + 8 * KB * i),
+                                       (__attribute__((address_space(3))) void *)(xs + i * 512), 16, 0, 0);
+  }
+  int tile[kFT], tile3[kFT];
+  bool use[kFT], use3[kFT];
+  fused_tiles(w, kFH / 16, tile, use);
+  fused_tiles(w, N3 / 16, tile3, use3);
+  bf16x8 ring[kFD][kFT];
+  FusedW fw;
+  auto weights = [&](const __bf16 *W, int K, const int t[kFT]) {
+    fw = fused_w(W, K, t);
+#pragma unroll
+    for (int d = 0; d < kFD; ++d) fused_load(fw, d, ring[d]);
+  };
+  weights(net.W[0], K0, tile);
+  __builtin_amdgcn_s_waitcnt(0);   // the direct-to-LDS loads have landed
+  __syncthreads();
+  f32x4 acc[FI][kFT], z[3][FI][kFT];
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+#pragma unroll
+      for (int j = 0; j < kFT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+#pragma unroll
+  for (int l = 0; l < 3; ++l) {
+    clear();
+    if (l == 0)
+      fused_layer<true, 0, FI, R>(fw, use, xs, acc, ring);
+    else
+      fused_layer<false, kFH, FI, R>(fw, use, hid[(l - 1) & 1], acc, ring);
+    weights(net.W[l + 1], kFH, l < 2 ? tile : tile3);
+#pragma unroll
+    for (int j = 0; j < kFT; ++j) {
+      const int col = 16 * tile[j] + r;
+      const float bb = net.b[l][col];
+#pragma unroll
+      for (int i = 0; i < FI; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          z[l][i][j][q] = acc[i][j][q] + bb;
+          hid[l & 1][(16 * i + r4 + q) * kHRow + col] = (__bf16)gelu_f(z[l][i][j][q]);
+        }
+    }
+    __syncthreads();
+    store_rows<R>(hid[l & 1], net.H[l] + m0 * kFH, kFH);
+  }
+  clear();
+  fused_layer<false, kFH, FI, R>(fw, use3, hid[0], acc, ring);
+  weights(net.Wt[3], N3, tile);
+  float sq = 0.f;
+#pragma unroll
+  for (int j = 0; j < kFT; ++j) {
+    if (!use3[j]) continue;
+    const int col = 16 * tile3[j] + r;
+    const float bb = net.b[3][col];
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = 16 * i + r4 + q;
+        const size_t o = (m0 + row) * N3 + col;
+        const float y = acc[i][j][q] + bb;
+        const float d = y - T[o];
+        sq += d * d;
+        const float g = 2.f * d / scale;
+        net.dZ[3][o] = g;
+        hid[1][row * kHRow + col] = (__bf16)g;
+      }
+  }
+  for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+  float *sums = reinterpret_cast<float *>(xs);   // the input tile is free
+  if (lane == 0) sums[w] = sq;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float s = 0.f;
+    for (int i = 0; i < kFW; ++i) s += sums[i];
+    loss[blockIdx.x] = s;
+  }
+  store_rows<R>(hid[1], net.dZb[3] + m0 * N3, N3);
+#pragma unroll
+  for (int l = 2; l >= 0; --l) {
+    // gradient of layer l's pre-activation from that of layer l + 1
+    const __bf16 *in = hid[(l + 1) & 1];
+    __bf16 *out = hid[l & 1];
+    clear();
+    if (l == 2)
+      fused_layer<false, 0, FI, R>(fw, use, hid[1], acc, ring);
+    else
+      fused_layer<false, kFH, FI, R>(fw, use, in, acc, ring);
+    if (l > 0) weights(net.Wt[l], kFH, tile);
+#pragma unroll
+    for (int j = 0; j < kFT; ++j) {
+      const int col = 16 * tile[j] + r;
+#pragma unroll
+      for (int i = 0; i < FI; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row = 16 * i + r4 + q;
+          const float g = acc[i][j][q] * gelu_grad_f(z[l][i][j][q]);
+          net.dZ[l][(m0 + row) * kFH + col] = g;
+          out[row * kHRow + col] = (__bf16)g;
+        }
+    }
+    __syncthreads();
+    store_rows<R>(out, net.dZb[l] + m0 * kFH, kFH);
+  }
+}
+
 // bf16 copy of one layer's fp32 weights.
 __global__ void k_weights_bf16(const float *W, __bf16 *Wb, size_t n) {
   const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
@@ -575,6 +754,14 @@ __global__ void k_weights_frag(const float *W, __bf16 *Wf, int N, int K) {
   *reinterpret_cast<bf16x8 *>(Wf + f * 8) = v;
 }
 
+// The same of the transpose of W[N][K]: rows of K, the N as 32-k substeps.
+__global__ void k_weights_frag_t(const float *W, __bf16 *Wt, int N, int K) {
+  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  if (i >= (size_t)N * K) return;
+  const int n = (int)(i / K), k = (int)(i % K);
+  Wt[frag_t(n, k, N)] = (__bf16)W[i];
+}
+
 inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 inline unsigned nb(size_t n, unsigned t = 256) { return (unsigned)((n + t - 1) / t); }
 
@@ -591,16 +778,17 @@ struct thor_mlp {
   std::vector<size_t> woff, boff;   // offsets of W_l, b_l in the packed arrays
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
   std::vector<__bf16 *> Wb;      // bf16 copies of W_l [out][in]
-  std::vector<__bf16 *> Wf;      // the same in MFMA fragment order (fused inference)
+  std::vector<__bf16 *> Wf;      // the same in MFMA fragment order (fused inference and training)
+  std::vector<__bf16 *> Wt;      // W_l^T in fragment order (fused training; null where it is not read)
   std::vector<float *> Z;        // pre-activations of the hidden layers, [B][w_{l+1}]
   std::vector<__bf16 *> H;       // hidden activations, [B][w_{l+1}]
   std::vector<float *> dZ;       // gradients of the pre-activations
   std::vector<__bf16 *> dZb;
   std::vector<float *> split;    // partial sums of the weight gradient, [kMaxSplit][w_{l+1}][w_l]
   std::vector<float *> bsum;     // and of the bias gradient, [kBiasSplit][w_{l+1}]
-  float *partial = nullptr;      // loss partial sums, one per output tile
+  float *partial = nullptr;      // loss partial sums, one per output tile or workgroup of the fused pass
   int adam_t = 0;
-  bool fused = true;             // inference through k_mlp_fused4 where the shape allows
+  bool fused = true;             // k_mlp_fused4 and k_mlp_train4 where the shape allows
   hipStream_t stream = nullptr;
 };
 
@@ -610,6 +798,13 @@ bool mlp_ok(hipError_t e, const char *what) {
   if (e == hipSuccess) return true;
   set_error(std::string(what) + ": " + hipGetErrorString(e));
   return false;
+}
+
+// The fused kernels serve 4-layer networks with hidden widths kFH, an input
+// width of at most kFK0Max and an output width of at most kFH.
+bool fused_shape(const thor_mlp *M) {
+  return M->nl == 4 && M->w[0] <= kFK0Max && M->w[1] == kFH && M->w[2] == kFH && M->w[3] == kFH &&
+         M->w[4] <= kFH;
 }
 
 // Sizes every device array; with base == nullptr only counts bytes.
@@ -628,6 +823,7 @@ size_t mlp_layout(thor_mlp *M, char *base) {
   M->v = (float *)take(M->n_params * 4);
   M->Wb.assign(nl, nullptr);
   M->Wf.assign(nl, nullptr);
+  M->Wt.assign(nl, nullptr);
   M->Z.assign(nl, nullptr);
   M->H.assign(nl, nullptr);
   M->dZ.assign(nl, nullptr);
@@ -638,6 +834,7 @@ size_t mlp_layout(thor_mlp *M, char *base) {
     const size_t wsz = (size_t)M->w[l] * M->w[l + 1];
     M->Wb[l] = (__bf16 *)take(wsz * 2);
     M->Wf[l] = (__bf16 *)take(wsz * 2);
+    if (l > 0 && fused_shape(M)) M->Wt[l] = (__bf16 *)take(wsz * 2);
     if (l + 1 < nl) {
       M->Z[l] = (float *)take((size_t)B * M->w[l + 1] * 4);
       M->H[l] = (__bf16 *)take((size_t)B * M->w[l + 1] * 2);
@@ -647,7 +844,7 @@ size_t mlp_layout(thor_mlp *M, char *base) {
     M->split[l] = (float *)take(kMaxSplit * wsz * 4);
     M->bsum[l] = (float *)take((size_t)kBiasSplit * M->w[l + 1] * 4);
   }
-  M->partial = (float *)take(tiles * ((M->w[nl] + kTile - 1) / kTile) * 4);
+  M->partial = (float *)take(std::max(tiles * ((M->w[nl] + kTile - 1) / kTile), ((size_t)B + 15) / 16) * 4);
   return off;
 }
 
@@ -682,6 +879,9 @@ void refresh_bf16(thor_mlp *M) {
     hipLaunchKernelGGL(k_weights_bf16, dim3(nb(n)), dim3(256), 0, M->stream, M->p + M->woff[l], M->Wb[l], n);
     hipLaunchKernelGGL(k_weights_frag, dim3(nb(n / 8)), dim3(256), 0, M->stream, M->p + M->woff[l], M->Wf[l],
                        M->w[l + 1], M->w[l]);
+    if (M->Wt[l])
+      hipLaunchKernelGGL(k_weights_frag_t, dim3(nb(n)), dim3(256), 0, M->stream, M->p + M->woff[l], M->Wt[l],
+                         M->w[l + 1], M->w[l]);
   }
 }
 
@@ -695,13 +895,6 @@ void gemm(const __bf16 *A, int lda, const __bf16 *B, int ldb, float *C, int ldc,
 
 // Number of batch chunks of a weight gradient: chunks of at least 256 rows.
 int grad_splits(int B) { return std::max(1, std::min(kMaxSplit, B / 256)); }
-
-// The fused inference kernel serves 4-layer networks with hidden widths
-// kFH, an input width of at most kFK0Max and an output width of at most kFH.
-bool fused_shape(const thor_mlp *M) {
-  return M->nl == 4 && M->w[0] <= kFK0Max && M->w[1] == kFH && M->w[2] == kFH && M->w[3] == kFH &&
-         M->w[4] <= kFH;
-}
 
 // Inference: the output layer's pre-activation to y (hidden pre-activations
 // are not kept).
@@ -732,10 +925,10 @@ void infer(thor_mlp *M, const __bf16 *X, int B, float *y) {
   }
 }
 
-// Forward and backward pass of the mean-squared loss, up to the partial sums
-// of the gradients (M->split, M->bsum) and of the loss (M->partial); returns
-// the number of batch chunks of a weight gradient.
-int loss_and_grad(thor_mlp *M, const __bf16 *X, const float *T, int B) {
+// Forward and backward pass of the mean-squared loss up to the gradients of
+// the pre-activations and the partial sums of the loss (M->partial), layer by
+// layer; returns the number of those sums.
+int passes_by_layer(thor_mlp *M, const __bf16 *X, const float *T, int B) {
   const int nl = M->nl;
   hipStream_t s = M->stream;
   for (int l = 0; l < nl; ++l) {
@@ -762,6 +955,41 @@ int loss_and_grad(thor_mlp *M, const __bf16 *X, const float *T, int B) {
     e.ref = M->Z[l - 1];
     gemm<false, true, EPI_ACT_GRAD>(M->dZb[l], N, M->Wb[l], K, M->dZ[l - 1], K, e, B, K, N, s);
   }
+  return (B + kTile - 1) / kTile * ((M->w[nl] + kTile - 1) / kTile);
+}
+
+// The same in one launch; B % 32 == 0.
+int passes_fused(thor_mlp *M, const __bf16 *X, const float *T, int B) {
+  TrainNet net{};
+  for (int l = 0; l < 4; ++l) {
+    net.W[l] = M->Wf[l];
+    net.Wt[l] = M->Wt[l];
+    net.b[l] = M->p + M->boff[l];
+    net.dZ[l] = M->dZ[l];
+    net.dZb[l] = M->dZb[l];
+    if (l < 3) net.H[l] = M->H[l];
+  }
+  net.in = M->w[0];
+  net.out = M->w[4];
+  const float scale = (float)B * (float)net.out;
+  const int wg = B <= kTrain16 ? B / 16 : B / 32;
+  if (B <= kTrain16)
+    hipLaunchKernelGGL(k_mlp_train4<1>, dim3(wg), dim3(64 * kFW), 0, M->stream, net, X, T, scale, M->partial);
+  else
+    hipLaunchKernelGGL(k_mlp_train4<2>, dim3(wg), dim3(64 * kFW), 0, M->stream, net, X, T, scale, M->partial);
+  return wg;
+}
+
+struct Parts {
+  int grad, loss;   // batch chunks of a weight gradient; partial sums of the loss
+};
+
+// Forward and backward pass of the mean-squared loss, up to the partial sums
+// of the gradients (M->split, M->bsum) and of the loss (M->partial).
+Parts loss_and_grad(thor_mlp *M, const __bf16 *X, const float *T, int B) {
+  const int nl = M->nl;
+  hipStream_t s = M->stream;
+  const int n_loss = fused_shape(M) && M->fused ? passes_fused(M, X, T, B) : passes_by_layer(M, X, T, B);
   const int splits = grad_splits(B);
   const int chunk = ((B + splits - 1) / splits + kStepK - 1) / kStepK * kStepK, S = (B + chunk - 1) / chunk;
   GradNet g{};
@@ -776,7 +1004,7 @@ int loss_and_grad(thor_mlp *M, const __bf16 *X, const float *T, int B) {
   }
   hipLaunchKernelGGL(k_grad, dim3(g.tiles * S + sums), dim3(256), 0, s, g, B, chunk,
                      (B + kBiasSplit - 1) / kBiasSplit);
-  return S;
+  return Parts{S, n_loss};
 }
 
 UpdateNet update_net(thor_mlp *M, int S) {
@@ -784,7 +1012,7 @@ UpdateNet update_net(thor_mlp *M, int S) {
   u.nl = M->nl;
   u.S = S;
   for (int l = 0; l < M->nl; ++l)
-    u.l[l] = UpdateLayer{M->split[l], M->bsum[l], M->Wb[l], M->Wf[l], M->woff[l], M->w[l + 1], M->w[l]};
+    u.l[l] = UpdateLayer{M->split[l], M->bsum[l], M->Wb[l], M->Wf[l], M->Wt[l], M->woff[l], M->w[l + 1], M->w[l]};
   return u;
 }
 
@@ -893,10 +1121,10 @@ int thor_mlp_loss_grad(thor_mlp *m, const void *x_bf16, const float *t, int B, d
   if (!m || !x_bf16 || !t) { set_error("thor_mlp_loss_grad: NULL argument"); return THOR_EINVAL; }
   if (B < 1 || B > m->max_batch || B % 32) { set_error("thor_mlp_loss_grad: batch must be a multiple of 32 within max_batch"); return THOR_EINVAL; }
   if (((uintptr_t)x_bf16 & 15) != 0) { set_error("thor_mlp_loss_grad: inputs must be 16-byte aligned"); return THOR_EINVAL; }
-  const int S = loss_and_grad(m, (const __bf16 *)x_bf16, t, B);
-  hipLaunchKernelGGL(k_update<false>, dim3(nb(m->n_params / kUpd)), dim3(256), 0, m->stream, update_net(m, S),
+  const Parts parts = loss_and_grad(m, (const __bf16 *)x_bf16, t, B);
+  hipLaunchKernelGGL(k_update<false>, dim3(nb(m->n_params / kUpd)), dim3(256), 0, m->stream, update_net(m, parts.grad),
                      m->n_params, (float *)nullptr, (float *)nullptr, (float *)nullptr, m->g, Adam{});
-  const size_t np = (size_t)((B + kTile - 1) / kTile) * ((m->w[m->nl] + kTile - 1) / kTile);
+  const size_t np = parts.loss;
   std::vector<float> part(np);
   if (!mlp_ok(hipMemcpyAsync(part.data(), m->partial, np * 4, hipMemcpyDeviceToHost, m->stream), "copy loss"))
     return THOR_EHIP;
@@ -914,11 +1142,11 @@ int thor_mlp_train_step(thor_mlp *m, const void *x_bf16, const float *t, int B, 
   if (!m || !x_bf16 || !t) { set_error("thor_mlp_train_step: NULL argument"); return THOR_EINVAL; }
   if (B < 1 || B > m->max_batch || B % 32 || !(lr > 0)) { set_error("thor_mlp_train_step: batch must be a multiple of 32 within max_batch, lr > 0"); return THOR_EINVAL; }
   if (((uintptr_t)x_bf16 & 15) != 0) { set_error("thor_mlp_train_step: inputs must be 16-byte aligned"); return THOR_EINVAL; }
-  const int S = loss_and_grad(m, (const __bf16 *)x_bf16, t, B);
+  const Parts parts = loss_and_grad(m, (const __bf16 *)x_bf16, t, B);
   m->adam_t += 1;
   const float b1 = 0.9f, b2 = 0.999f;
   const float c1 = 1.f - std::pow(b1, (float)m->adam_t), c2 = 1.f - std::pow(b2, (float)m->adam_t);
-  hipLaunchKernelGGL(k_update<true>, dim3(nb(m->n_params / kUpd)), dim3(256), 0, m->stream, update_net(m, S),
+  hipLaunchKernelGGL(k_update<true>, dim3(nb(m->n_params / kUpd)), dim3(256), 0, m->stream, update_net(m, parts.grad),
                      m->n_params, m->p, m->m, m->v, (float *)nullptr, Adam{lr, b1, b2, 1e-8f, c1, c2});
   return mlp_ok(hipGetLastError(), "train step") ? THOR_OK : THOR_EHIP;
 }

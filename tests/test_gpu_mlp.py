@@ -158,3 +158,36 @@ def test_gradients_and_adam_at_ragged_tiles(widths, B):
     net.set_fused(False)
     net.forward(x, y[1])
     assert torch.equal(y[0], y[1])
+
+
+@pytest.mark.parametrize("w_in,w_out,B", [(32, 32, 32), (1152, 256, 96), (1120, 160, 4096), (1120, 160, 4128),
+                                          (64, 224, 8192)])
+def test_fused_training_equals_layer_by_layer(w_in, w_out, B):
+    """Forward and backward in one launch (16-row workgroups up to 4096 rows,
+    32-row above) against the layer-by-layer products: the same products in
+    the same order, so the same gradients and, over three Adam steps (whose
+    update also writes the transposed weights the pass reads), the same
+    parameters bit for bit.  The loss adds up to 4096 squares per partial sum
+    in FP32 in another order, at most 32 additions deep: 32 x 2^-24 on each
+    side."""
+    import torch
+    from paper_1607_05535_amd import thor
+    say(f"[mlp] fused training {w_in} -> {w_out}, B={B}")
+    widths = [w_in, 256, 256, 256, w_out]
+    rs = np.random.default_rng(B)
+    x = torch.from_numpy(rs.normal(size=(B, w_in)).astype(np.float32)).to("cuda:0").to(torch.bfloat16)
+    t = torch.from_numpy(rs.normal(size=(B, w_out)).astype(np.float32)).to("cuda:0")
+    res = []
+    for fused in (False, True):
+        net = thor.MLP(widths, B, seed=11)
+        net.set_fused(fused)
+        loss, g = net.loss_grad(x, t)
+        for _ in range(3):
+            net.train_step(x, t, 1e-3)
+        loss3, g3 = net.loss_grad(x, t)
+        res.append((loss, loss3, g, g3, net.get_params()))
+    a, b = res
+    for k in (0, 1):
+        assert abs(a[k] - b[k]) <= 64 * 2.0 ** -24 * a[k]
+    for k in (2, 3, 4):
+        assert np.array_equal(a[k], b[k])
