@@ -80,6 +80,31 @@ struct Fields {
   double *fI;             // [N][L]
 };
 
+// Local east and north of a column in FP64.  The FP64 state reads them from
+// its table; a mixed state's table is FP32, so what leaves it as FP64 or is
+// rounded once (diagnostics, zonal means, network inputs, corrections) forms
+// them from rhat: no angle is needed (at a pole the longitude counts as 0).
+template <typename H>
+__device__ __forceinline__ void tangent64(const Fields<H> &f, int col, double e[3], double n[3]) {
+  if (sizeof(H) == sizeof(double)) {
+    const H *fr = f.frame + (size_t)col * kFr;
+    for (int k = 0; k < 3; ++k) {
+      e[k] = fr[k];
+      n[k] = fr[3 + k];
+    }
+    return;
+  }
+  const H *rh = f.rhat + (size_t)col * 3;
+  const double x = rh[0], y = rh[1], z = fmin(1.0, fmax(-1.0, (double)rh[2])), h = sqrt(x * x + y * y);
+  const double cl = h < 1e-12 ? 1.0 : x / h, sl = h < 1e-12 ? 0.0 : y / h;
+  e[0] = -sl;
+  e[1] = cl;
+  e[2] = 0.0;
+  n[0] = -z * cl;
+  n[1] = -z * sl;
+  n[2] = sqrt((1.0 - z) * (1.0 + z));
+}
+
 struct Consts {
   int N, L, cpw;          // columns, levels, columns per wavefront
   int S;                  // row stride of the per-cell state arrays (L rounded up to a multiple of 4)

@@ -1852,9 +1852,11 @@ __device__ __forceinline__ void b_diag(const Fields<H> &f, const Consts &c, cons
     const double p = c.p_ref * powd(c.rd_p * f.rth_t[idx], c.gamma);
     out = field == THOR_F_P ? p : p / (rho * c.Rd);
   } else if (field == THOR_F_U || field == THOR_F_V) {
-    const H *e = f.frame + (size_t)col * kFr + (field == THOR_F_U ? 0 : 3);
+    double east[3], north[3];
+    tangent64(f, col, east, north);
+    const double *e = field == THOR_F_U ? east : north;
     const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
-    out = (double)e[0] * vx + (double)e[1] * vy + (double)e[2] * vz;
+    out = e[0] * vx + e[1] * vy + e[2] * vz;
   } else if (field == THOR_F_W) {
     out = 0.5 * (W + W1) / rho;
   } else if (field == THOR_F_RHO) {
@@ -1943,10 +1945,11 @@ __global__ __launch_bounds__(256) void k_extremes(Fields<H> f, Consts c, double 
     const size_t idx = (size_t)col * c.S + lev;
     const double rho = f.rho_t[idx];
     const double W = lev == 0 ? 0.0 : f.W_t[idx], W1 = (int)lev == c.L - 1 ? 0.0 : f.W_t[idx + 1];
-    const H *fr = f.frame + (size_t)col * kFr;
+    double east[3], north[3];
+    tangent64(f, (int)col, east, north);
     const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
-    const double u = (double)fr[0] * vx + (double)fr[1] * vy + (double)fr[2] * vz;
-    const double v = (double)fr[3] * vx + (double)fr[4] * vy + (double)fr[5] * vz;
+    const double u = east[0] * vx + east[1] * vy + east[2] * vz;
+    const double v = north[0] * vx + north[1] * vy + north[2] * vz;
     const double w = 0.5 * (W + W1) / rho;
     const double p = c.p_ref * powd(c.rd_p * f.rth_t[idx], c.gamma);
     e[0] = fmax(0.0, sqrt(u * u + v * v + w * w));

@@ -67,8 +67,8 @@ __global__ __launch_bounds__(kZthreads) void k_zinterp(Fields<H> f, Consts c, co
     const size_t idx = (size_t)col * c.S + lev;   // state row stride
     const double rho = f.rho_t[idx], rth = f.rth_t[idx];
     const double p = c.p_ref * powd(c.Rd * rth / c.p_ref, c.gamma);
-    const H *fr = f.frame + (size_t)col * kFr;
-    const double e[2] = {fr[0], fr[1]}, n[3] = {fr[3], fr[4], fr[5]};
+    double e[3], n[3];
+    tangent64(f, col, e, n);
     const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
     double *o = zs + lev * kZpitch + cb;
     o[0] = p;

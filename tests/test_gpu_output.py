@@ -46,3 +46,29 @@ def test_scalars_pass_over_nan_and_say_so():
     st.load(blob)
     check_scalars(st)
     assert st.scalars()[1] == thor.THOR_ENONFINITE
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_winds_use_a_double_basis(precision):
+    """u and v of the FP64 and of the mixed state against the momentum of the
+    checkpoint, projected in FP64 on east and north of the positions the state
+    holds (FP32 in the mixed one): a dozen FP64 roundings of values up to the
+    largest wind, far below the 3e-8 of an FP32 basis."""
+    st = lib_state(small_earth(glevel=3, n_lev=5), precision)
+    blob = st.export()[0]
+    NL = st.n_col * st.n_lev
+    rng = np.random.default_rng(4)
+    blob[4 + NL:4 + 4 * NL] = rng.standard_normal(3 * NL).astype(np.float32)
+    st.load(blob)
+    rho, mx, my, mz = (a.reshape(st.n_col, st.n_lev) for a in st.export()[0][4:4 + 4 * NL].reshape(4, NL))
+    r = st.grid.export()[1]
+    if precision:
+        r = r.astype(np.float32).astype(np.float64)
+    x, y, z = r.T
+    lam, phi = np.where(np.hypot(x, y) < 1e-12, 0.0, np.arctan2(y, x)), np.arcsin(np.clip(z, -1, 1))
+    east = np.stack([-np.sin(lam), np.cos(lam), 0 * lam])[..., None]
+    north = np.stack([-np.sin(phi) * np.cos(lam), -np.sin(phi) * np.sin(lam), np.cos(phi)])[..., None]
+    m = np.stack([mx, my, mz]) / rho
+    for name, basis in (("u", east), ("v", north)):
+        got, want = st.field(name)[0], (m * basis).sum(0)
+        assert np.abs(got - want).max() <= 1e-14 * np.abs(m).max(), name
