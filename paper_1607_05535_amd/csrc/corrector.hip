@@ -54,16 +54,6 @@ inline unsigned cblocks(int N, int L) {
   return (unsigned)((waves + 3) / 4);
 }
 
-// kHq consecutive values of a padded state row.
-__device__ __forceinline__ void row4(const double *p, double v[kHq]) {
-  const double2 a = *reinterpret_cast<const double2 *>(p), b = *reinterpret_cast<const double2 *>(p + 2);
-  v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
-}
-__device__ __forceinline__ void row4(const float *p, float v[kHq]) {
-  const float4 a = *reinterpret_cast<const float4 *>(p);
-  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-}
-
 // (T, u, v, w, p) of every cell of the state (FP32, [f][col][lev]).  A thread
 // takes kHq consecutive levels of a padded state row, so every lane works at
 // any level count and the state moves in 16-byte loads; VEC: so do the

@@ -80,6 +80,53 @@ struct Fields {
   double *fI;             // [N][L]
 };
 
+// Kernels dominated by horizontal gathers (acoustic phase M, slow terms) use
+// a second mapping: each lane owns kHq consecutive levels of one column,
+// hlpc = ceil(L / kHq) lanes per column and hcpw = floor(64 / hlpc) columns
+// per wavefront.  Per-column stencil weights are then loaded once per kHq
+// cells, rows move in 16-byte loads, and a vertical neighbour is a register
+// or, across a lane boundary, one shuffle.
+constexpr int kHq = 4;
+
+// 1 / x from the hardware reciprocal estimate refined by Newton steps, the
+// last of which leaves half a unit of rounding and a term below 2^-40 of it;
+// x / y from r = 1 / y with the remainder's correction, rounded as well.
+// For normal operands and quotients (densities, pressures, radii, pivots).
+// The compiler's division also scales its operands and repairs special
+// cases, 11 instructions to 5 and 3: 21 of them made up 40 % of the FP64
+// instructions of the slow terms, 32 were 55 % of the large step's first
+// pass.  Large step g5 L37 37.2 -> 35.1 us, mixed 36.0 -> 33.1; slow terms
+// 12.85 -> 12.6 and 10.1 -> 9.4; phase V 14.7 -> 14.4 and 11.7 -> 11.5.
+__device__ __forceinline__ double rcpd(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  double e = fma(-x, r, 1.0);
+  r = fma(r, e, r);
+  e = fma(-x, r, 1.0);
+  return fma(r, e, r);
+}
+__device__ __forceinline__ float rcpd(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(r, fmaf(-x, r, 1.0f), r);
+}
+__device__ __forceinline__ double quot(double x, double y, double r) {
+  const double q = x * r;
+  return fma(fma(-y, q, x), r, q);
+}
+__device__ __forceinline__ float quot(float x, float y, float r) {
+  const float q = x * r;
+  return fmaf(fmaf(-y, q, x), r, q);
+}
+
+// The kHq levels of a lane in 16-byte loads (rows have whole groups of kHq).
+__device__ __forceinline__ void row4(const double *p, double v[kHq]) {
+  const double2 a = *reinterpret_cast<const double2 *>(p), b = *reinterpret_cast<const double2 *>(p + 2);
+  v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+}
+__device__ __forceinline__ void row4(const float *p, float v[kHq]) {
+  const float4 a = *reinterpret_cast<const float4 *>(p);
+  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+}
+
 // Local east and north of a column in FP64.  The FP64 state reads them from
 // its table; a mixed state's table is FP32, so what leaves it as FP64 or is
 // rounded once (diagnostics, zonal means, network inputs, corrections) forms
@@ -142,13 +189,6 @@ inline int n_blocks_for(long n_col, int cols_per_wave, int wpb) {
 }
 inline int n_blocks(const Consts &c, int wpb) { return n_blocks_for(c.N, c.cpw, wpb); }
 
-// Kernels dominated by horizontal gathers (acoustic phase M, slow terms) use
-// a second mapping: each lane owns kHq consecutive levels of one column,
-// hlpc = ceil(L / kHq) lanes per column and hcpw = floor(64 / hlpc) columns
-// per wavefront.  Per-column stencil weights are then loaded once per kHq
-// cells, rows move in 16-byte loads, and a vertical neighbour is a register
-// or, across a lane boundary, one shuffle.
-constexpr int kHq = 4;
 inline int n_blocks_h(const Consts &c, int wpb) { return n_blocks_for(c.N, c.hcpw, wpb); }
 inline long n_waves_h(const Consts &c) { return (c.N + c.hcpw - 1) / c.hcpw; }
 

@@ -106,35 +106,6 @@ __device__ __forceinline__ H eos(double rth, const Consts &c) {
 __device__ __forceinline__ double radius_c(const Consts &c, int lev) { return c.radius + (lev + 0.5) * c.rdz; }
 __device__ __forceinline__ double radius_i(const Consts &c, int lev) { return c.radius + lev * c.rdz; }
 
-// 1 / x from the hardware reciprocal estimate refined by Newton steps, the
-// last of which leaves half a unit of rounding and a term below 2^-40 of it;
-// x / y from r = 1 / y with the remainder's correction, rounded as well.
-// For normal operands and quotients (densities, pressures, radii, pivots).
-// The compiler's division also scales its operands and repairs special
-// cases, 11 instructions to 5 and 3: 21 of them made up 40 % of the FP64
-// instructions of the slow terms, 32 were 55 % of the large step's first
-// pass.  Large step g5 L37 37.2 -> 35.1 us, mixed 36.0 -> 33.1; slow terms
-// 12.85 -> 12.6 and 10.1 -> 9.4; phase V 14.7 -> 14.4 and 11.7 -> 11.5.
-__device__ __forceinline__ double rcpd(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
-}
-__device__ __forceinline__ float rcpd(float x) {
-  const float r = __builtin_amdgcn_rcpf(x);
-  return fmaf(r, fmaf(-x, r, 1.0f), r);
-}
-__device__ __forceinline__ double quot(double x, double y, double r) {
-  const double q = x * r;
-  return fma(fma(-y, q, x), r, q);
-}
-__device__ __forceinline__ float quot(float x, float y, float r) {
-  const float q = x * r;
-  return fmaf(fmaf(-y, q, x), r, q);
-}
-
 // Neighbour ids of a column; a pentagon's missing 6th neighbour points at the
 // column itself (its coefficients are zero).
 __device__ __forceinline__ void load_nbr(const int32_t *nbr, int col, int nb[6]) {

@@ -33,9 +33,11 @@ namespace thor {
 namespace {
 
 constexpr int kZq = 4;          // interpolated quantities: u, v, T, theta
-constexpr int kZslot = kZq + 1; // + valid flag
+constexpr int kZslot = kZq + 1; // + pressure, in LDS
+constexpr int kZrec = 11;       // a tile's record: 2 areas, 4 sums, 2 co-moments, 3 remainders
 constexpr int kZthreads = 256;  // threads of a workgroup
 constexpr int kZcols = 16;      // columns per workgroup of the interpolation
+constexpr int kZlev = 64;        // pressure levels per pass of the interpolation
 constexpr int kZpitch = kZcols + 1;   // LDS row of one level over those columns, padded
 
 bool zok(hipError_t e, const char *what) {
@@ -44,23 +46,51 @@ bool zok(hipError_t e, const char *what) {
   return false;
 }
 
-// Columns pos0 .. pos0 + kZcols - 1 of the band-sorted list `cols` per
-// workgroup: p, u, v, T, theta of every level into LDS ([quantity][level]
-// [column], dynamic), then one thread per (pressure level, column) looks for
-// the lowest-index level pair whose pressures bracket the level; the values
-// there go to Z[j][0..3][pos] and Z[j][4][pos] = 1 (0 if none).  Positions
-// along the lanes: 128-byte rows out, and the reduction reads a band's
-// columns contiguously.  Zw[pos] = w at the centre of the first layer (half
-// the momentum of the first interior interface over rho; the ground
-// interface carries none).
+// Sums over each 16 consecutive lanes (a DPP row, by rotations), to every one
+// of them.
+template <int ROT>
+__device__ __forceinline__ double row_ror(double x) {
+  union { double d; int i[2]; } u{x}, r;
+  r.i[0] = __builtin_amdgcn_update_dpp(0, u.i[0], 0x120 + ROT, 0xf, 0xf, true);
+  r.i[1] = __builtin_amdgcn_update_dpp(0, u.i[1], 0x120 + ROT, 0xf, 0xf, true);
+  return r.d;
+}
+template <int NV>
+__device__ __forceinline__ void lane16_sums(double v[NV]) {
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    v[k] += row_ror<8>(v[k]);
+    v[k] += row_ror<4>(v[k]);
+    v[k] += row_ror<2>(v[k]);
+    v[k] += row_ror<1>(v[k]);
+  }
+}
+
+// A tile of at most kZcols consecutive columns of the band-sorted list `cols`
+// per workgroup, all of one band (tiles[w] = first position, count): p, u, v,
+// T, theta of every level into LDS ([quantity][level][column], dynamic), then
+// 16 lanes per pressure level, one a column, look for the lowest-index level
+// pair whose pressures bracket the level.  What a band needs of the tile goes
+// to P[j][w]: the area with a value there, the whole area, the area-weighted
+// sums of u, v, T, theta, the co-moments u'v', v'T' about the tile's own
+// (rounded) means and the sums of u, v, T less those means: k_zreduce merges
+// them about the band's means as exactly as a second pass over the columns.
+// Zw[pos] = w at the centre of the first layer (half the momentum of the first
+// interior interface over rho; the ground interface carries none).
 // Bound by reading the state (40 bytes per cell); g6 L32, 20 levels:
-// 81 -> 29 us (one wavefront per column before, all its lanes
-// once through every pressure level, and the angles of every cell).
+// 81 -> 30 us by columns in LDS, -> 28 by records instead of every value
+// (33 MB) out and a scatter of each level pair to the pressure levels it
+// brackets instead of a search through the pairs for each.  Twice the
+// threads 37 us, more wavefronts per SIMD (7) 39, four levels per thread 30.
 template <typename H>
-__global__ __launch_bounds__(kZthreads) void k_zinterp(Fields<H> f, Consts c, const int32_t *cols, const double *plev,
-                                                       int np, double *Z, double *Zw) {
+__global__ __launch_bounds__(kZthreads) void k_zinterp(Fields<H> f, Consts c, const int32_t *cols, const int2 *tiles,
+                                                       const double *area, const double *plev, int np, double *P,
+                                                       double *Zw) {
   extern __shared__ double zs[];
-  const int L = c.L, N = c.N, pos0 = blockIdx.x * kZcols, nc = min(kZcols, N - pos0);
+  __shared__ int below[kZlev * kZcols];   // lower level of the bracketing pair, L if none
+  __shared__ double pl[kZlev];
+  const int2 tile = tiles[blockIdx.x];
+  const int L = c.L, pos0 = tile.x, nc = tile.y;
   const int plane = L * kZpitch;   // one quantity
   for (int i = threadIdx.x; i < nc * L; i += kZthreads) {
     const int cb = i / L, lev = i - cb * L, col = cols[pos0 + cb];
@@ -69,44 +99,70 @@ __global__ __launch_bounds__(kZthreads) void k_zinterp(Fields<H> f, Consts c, co
     const double p = c.p_ref * powd(c.Rd * rth / c.p_ref, c.gamma);
     double e[3], n[3];
     tangent64(f, col, e, n);
-    const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
+    const double ir = rcpd(rho);
+    const double vx = quot((double)f.Mx_t[idx], rho, ir), vy = quot((double)f.My_t[idx], rho, ir),
+                 vz = quot((double)f.Mz_t[idx], rho, ir);
     double *o = zs + lev * kZpitch + cb;
     o[0] = p;
     o[plane] = e[0] * vx + e[1] * vy;
     o[2 * plane] = n[0] * vx + n[1] * vy + n[2] * vz;
     o[3 * plane] = p / (rho * c.Rd);
-    o[4 * plane] = rth / rho;
+    o[4 * plane] = quot(rth, rho, ir);
     if (lev == 0) Zw[pos0 + cb] = L > 1 ? 0.5 * f.W_t[idx + 1] / rho : 0.0;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < np * kZcols; i += kZthreads) {
-    const int j = i / kZcols, cb = i - j * kZcols;
-    if (cb >= nc) continue;
-    const double pj = plev[j];
-    const double *col = zs + cb;
-    // interval (k, k + 1): p of k + 1 <= p_j <= p of k; four levels read at
-    // a time (past the top the last level again, which brackets nothing new)
-    int k = -1;
-    double hi = col[0];
-    for (int l = 0; l + 1 < L && k < 0; l += 4) {
-      double v[4];
+  for (int j0 = 0; j0 < np; j0 += kZlev) {
+    const int nj = min(kZlev, np - j0);
+    for (int i = threadIdx.x; i < kZlev * kZcols; i += kZthreads) below[i] = L;
+    if (threadIdx.x < nj) pl[threadIdx.x] = plev[j0 + threadIdx.x];
+    __syncthreads();
+    // interval (k, k + 1) of a column holds the pressure levels from p of
+    // k + 1 up to p of k (the levels ascend)
+    for (int i = threadIdx.x; i < nc * (L - 1); i += kZthreads) {
+      const int cb = i / (L - 1), k = i - cb * (L - 1);
+      const double hi = zs[k * kZpitch + cb], lo = zs[(k + 1) * kZpitch + cb];
+      int j = 0;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = col[min(l + 1 + u, L - 1) * kZpitch];
-#pragma unroll
-      for (int u = 3; u >= 0; --u)
-        if (l + 1 + u < L && v[u] <= pj && pj <= (u ? v[u - 1] : hi)) k = l + u;
-      hi = v[3];
+      for (int h = kZlev / 2; h > 0; h >>= 1)
+        if (j + h <= nj && !(pl[j + h - 1] >= lo)) j += h;
+      if (j == nj - 1 && !(pl[j] >= lo)) j = nj;
+      for (; j < nj && pl[j] >= lo && pl[j] <= hi; ++j) atomicMin(&below[j * kZcols + cb], k);
     }
-    double *out = Z + (size_t)j * kZslot * N + pos0 + cb;
-    const double p0 = col[max(k, 0) * kZpitch], p1 = col[min(max(k, 0) + 1, L - 1) * kZpitch];
-    const double w = (pj - p1) / (p0 - p1);
-    const double *q0 = col + max(k, 0) * kZpitch, *q1 = q0 + (k < 0 ? 0 : kZpitch);
+    __syncthreads();
+    // whole wavefronts: four levels each (past the last one without a value)
+    for (int i = threadIdx.x; i < (nj + 3) / 4 * 64; i += kZthreads) {
+      const int jj = min(i / kZcols, nj - 1), cb = i % kZcols;
+      const bool in = i / kZcols < nj && cb < nc;
+      const double pj = pl[jj];
+      const double *col = zs + min(cb, nc - 1);
+      const int b = below[jj * kZcols + min(cb, nc - 1)], k = b < L ? b : -1;
+      const bool has = in && k >= 0;
+      const double p0 = col[max(k, 0) * kZpitch], p1 = col[min(max(k, 0) + 1, L - 1) * kZpitch];
+      const double w = (pj - p1) / (p0 - p1);
+      const double *q0 = col + max(k, 0) * kZpitch, *q1 = q0 + (k < 0 ? 0 : kZpitch);
+      double x[kZq];   // u, v, T, theta
 #pragma unroll
-    for (int q = 1; q <= kZq; ++q) {
-      const double up = q1[q * plane];
-      out[(size_t)(q - 1) * N] = k < 0 ? 0.0 : up + w * (q0[q * plane] - up);
+      for (int q = 1; q <= kZq; ++q) {
+        const double up = q1[q * plane];
+        x[q - 1] = has ? up + w * (q0[q * plane] - up) : 0.0;
+      }
+      const double A0 = in ? area[pos0 + cb] : 0.0, A = has ? A0 : 0.0;
+      double m[2 + kZq] = {A, A0, A * x[0], A * x[1], A * x[2], A * x[3]};
+      lane16_sums<2 + kZq>(m);
+      const double iA = m[0] == 0.0 ? 0.0 : 1.0 / m[0];
+      const double mu = m[2] * iA, mv = m[3] * iA, mT = m[4] * iA;   // as k_zreduce forms them
+      const double du = x[0] - mu, dv = x[1] - mv, dT = x[2] - mT;
+      double co[5] = {A * du * dv, A * dv * dT, A * du, A * dv, A * dT};
+      lane16_sums<5>(co);
+      if (cb < kZrec && i / kZcols < nj) {
+        double v = m[0];
+#pragma unroll
+        for (int q = 1; q < kZrec; ++q)
+          if (cb == q) v = q < 6 ? m[q < 6 ? q : 0] : co[q < 6 ? 0 : q - 6];
+        P[((size_t)(j0 + jj) * gridDim.x + blockIdx.x) * kZrec + cb] = v;
+      }
     }
-    out[(size_t)kZq * N] = k < 0 ? 0.0 : 1.0;
+    __syncthreads();   // the table is free
   }
 }
 
@@ -127,65 +183,72 @@ __device__ __forceinline__ void block_sums(double v[NV], double (*sm)[NV]) {
   for (int k = 0; k < NV; ++k) v[k] = ((sm[0][k] + sm[1][k]) + sm[2][k]) + sm[3][k];
 }
 
-// Band b, pressure level j < np (one workgroup each): area-weighted means of the
-// band's columns that have a value (thread t takes positions t, t + 256, ... of
-// the band's list), then the eddy products; added to the time sums
-// S[b][j][0..6] = u, v, T, theta, [u'v'], [v'T'], valid fraction and to the
-// snapshot count S[b][j][7].  j = np: the area-weighted mean of the
-// first-layer w over all of the band's columns, then each column's deviation
-// from it added to the time sum Wsum[column].
-// Bound by latency: two passes over a band of ~1000 columns (the second from
-// L2); g6 L32, 20 levels and 36 bands: 42 -> 14 us (before,
-// one barrier tree per sum over 800-byte strides, and the map in a kernel of its own).
-__global__ __launch_bounds__(kZthreads) void k_zreduce(const double *Z, const double *Zw, int np, int N,
-                                                       const int32_t *off, const int32_t *cols, const double *area,
-                                                       double *S, double *Wsum) {
-  __shared__ double sm[kZthreads / 64][6];
-  const int b = blockIdx.x, j = blockIdx.y;
-  const int a0 = off[b], a1 = off[b + 1];
-  if (j == np) {
-    double s[6] = {0, 0, 0, 0, 0, 0};
+// A wavefront per band and pressure level: area-weighted means of the band's
+// columns that have a value, then the eddy products, from the band's tiles
+// toff[b] .. toff[b + 1] - 1 (lane t takes tiles t, t + 64, ...); added to the
+// time sums S[b][j][0..6] = u, v, T, theta, [u'v'], [v'T'], valid fraction and
+// to the snapshot count S[b][j][7].  The last workgroup of a band: the
+// area-weighted mean of the first-layer w over all of its columns, then each
+// column's deviation from it added to the time sum Wsum[column].
+// Bound by latency; g6 L32, 20 levels, 36 bands: 14 us from every column's
+// values, 8.5 from the records.
+__global__ __launch_bounds__(kZthreads) void k_zreduce(const double *P, const double *Zw, int np, int n_tiles,
+                                                       const int32_t *toff, const int32_t *off, const int32_t *cols,
+                                                       const double *area, double *S, double *Wsum) {
+  __shared__ double sm[kZthreads / 64][2];
+  const int b = blockIdx.x, a0 = off[b], a1 = off[b + 1];
+  if (blockIdx.y == gridDim.y - 1) {
+    double s[2] = {0, 0};
     for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) {
       s[0] += area[i];
       s[1] += area[i] * Zw[i];
     }
-    block_sums<6>(s, sm);
+    block_sums<2>(s, sm);
     if (s[0] == 0.0) return;   // empty band, uniform across the workgroup
     const double mw = s[1] / s[0];
     for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) Wsum[cols[i]] += Zw[i] - mw;
     return;
   }
-  const double *z = Z + (size_t)j * kZslot * N;
+  const int j = blockIdx.y * (kZthreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (j >= np) return;
+  const int t0 = toff[b], t1 = toff[b + 1];
+  const double *rec = P + (size_t)j * n_tiles * kZrec;
   double s[6] = {0, 0, 0, 0, 0, 0};   // A, band area, u, v, T, theta
-  for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) {
-    const double A0 = area[i], A = A0 * z[(size_t)kZq * N + i];
-    s[0] += A;
-    s[1] += A0;
-    s[2] += A * z[i];
-    s[3] += A * z[(size_t)N + i];
-    s[4] += A * z[(size_t)2 * N + i];
-    s[5] += A * z[(size_t)3 * N + i];
-  }
-  block_sums<6>(s, sm);
+  for (int t = t0 + lane; t < t1; t += 64)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) s[k] += rec[(size_t)t * kZrec + k];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) s[k] += __shfl_xor(s[k], o, 64);
   const double sA = s[0];
-  if (sA == 0.0) return;   // uniform across the workgroup
+  if (sA == 0.0) return;   // uniform across the wavefront
   const double mu = s[2] / sA, mv = s[3] / sA, mT = s[4] / sA, mth = s[5] / sA, frac = sA / s[1];
-  double e[6] = {0, 0, 0, 0, 0, 0};
-  for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) {
-    const double A = area[i] * z[(size_t)kZq * N + i];
-    const double dv = z[(size_t)N + i] - mv;
-    e[0] += A * (z[i] - mu) * dv;
-    e[1] += A * dv * (z[(size_t)2 * N + i] - mT);
+  double e0 = 0.0, e1 = 0.0;
+  for (int t = t0 + lane; t < t1; t += 64) {
+    const double *r = rec + (size_t)t * kZrec;
+    const double iA = r[0] == 0.0 ? 0.0 : 1.0 / r[0];
+    // co-moments about the band's means: the tile's own, and the area times
+    // the deviations of its means, which are the rounded means the tile used
+    // and what its values leave over them
+    const double tu = r[2] * iA, tv = r[3] * iA, tT = r[4] * iA;
+    const double du = (tu - mu) + r[8] * iA, dv = (tv - mv) + r[9] * iA, dT = (tT - mT) + r[10] * iA;
+    e0 += r[6] + r[0] * (du * dv);
+    e1 += r[7] + r[0] * (dv * dT);
   }
-  block_sums<6>(e, sm);
-  if (threadIdx.x == 0) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    e0 += __shfl_xor(e0, o, 64);
+    e1 += __shfl_xor(e1, o, 64);
+  }
+  if (lane == 0) {
     double *o = S + ((size_t)b * np + j) * 8;
     o[0] += mu;
     o[1] += mv;
     o[2] += mT;
     o[3] += mth;
-    o[4] += e[0] / sA;
-    o[5] += e[1] / sA;
+    o[4] += e0 / sA;
+    o[5] += e1 / sA;
     o[6] += frac;
     o[7] += 1.0;
   }
@@ -247,8 +310,10 @@ struct thor_zonal {
   int nb = 0, np = 0;
   std::vector<double> plev_h;
   double radius = 0, gravity = 0;
-  double *plev = nullptr, *Z = nullptr, *S = nullptr, *area = nullptr, *Zw = nullptr, *Wsum = nullptr;
-  int32_t *off = nullptr, *cols = nullptr;
+  double *plev = nullptr, *P = nullptr, *S = nullptr, *area = nullptr, *Zw = nullptr, *Wsum = nullptr;
+  int32_t *off = nullptr, *cols = nullptr, *toff = nullptr;
+  int2 *tiles = nullptr;
+  int n_tiles = 0;
   int snapshots = 0;
 };
 
@@ -262,7 +327,10 @@ size_t zonal_layout(thor_zonal *z, size_t N, char *base) {
     return p;
   };
   z->plev = (double *)take(z->np * sizeof(double));
-  z->Z = (double *)take(N * z->np * kZslot * sizeof(double));
+  const size_t tiles = N / kZcols + z->nb;   // at most: one partly filled tile per band
+  z->P = (double *)take(tiles * z->np * kZrec * sizeof(double));
+  z->tiles = (int2 *)take(tiles * sizeof(int2));
+  z->toff = (int32_t *)take((z->nb + 1) * sizeof(int32_t));
   z->S = (double *)take((size_t)z->nb * z->np * 8 * sizeof(double));
   z->area = (double *)take(N * sizeof(double));
   z->off = (int32_t *)take((z->nb + 1) * sizeof(int32_t));
@@ -339,13 +407,22 @@ int thor_zonal_init(thor_state *s, const thor_grid *g, double radius, double gra
   for (int b = 0; b < n_bands; ++b) off[b + 1] += off[b];
   std::vector<int32_t> fill(off.begin(), off.end() - 1);
   for (size_t i = 0; i < N; ++i) cols[fill[band[i]]++] = (int32_t)i;
-  std::vector<double> area(N);   // in band order, as Z and Zw
+  std::vector<int32_t> toff(n_bands + 1, 0);
+  std::vector<int2> tiles;
+  for (int b = 0; b < n_bands; ++b) {
+    for (int i = off[b]; i < off[b + 1]; i += kZcols) tiles.push_back(make_int2(i, std::min(kZcols, off[b + 1] - i)));
+    toff[b + 1] = (int32_t)tiles.size();
+  }
+  z->n_tiles = (int)tiles.size();
+  std::vector<double> area(N);   // in band order, as Zw
   for (size_t i = 0; i < N; ++i) area[i] = g->g.area[cols[i]];
   hipStream_t st = s->stream;
   const size_t ns = (size_t)n_bands * n_plev * 8;
   bool ok = zok(hipMemcpyAsync(z->plev, plev, n_plev * sizeof(double), hipMemcpyHostToDevice, st), "copy plev") &&
             zok(hipMemcpyAsync(z->area, area.data(), N * sizeof(double), hipMemcpyHostToDevice, st), "copy area") &&
             zok(hipMemcpyAsync(z->off, off.data(), off.size() * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy off") &&
+            zok(hipMemcpyAsync(z->toff, toff.data(), toff.size() * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy toff") &&
+            zok(hipMemcpyAsync(z->tiles, tiles.data(), tiles.size() * sizeof(int2), hipMemcpyHostToDevice, st), "copy tiles") &&
             zok(hipMemcpyAsync(z->cols, cols.data(), N * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy cols");
   if (ok) {
     hipLaunchKernelGGL(k_zzero, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, st, z->S, ns);
@@ -361,16 +438,16 @@ int thor_zonal_accumulate(thor_zonal *z) {
   clear_error();
   if (!z) { set_error("thor_zonal_accumulate: NULL argument"); return THOR_EINVAL; }
   thor_state *s = z->s;
-  const dim3 g((unsigned)((s->c.N + kZcols - 1) / kZcols)), t(kZthreads);
+  const dim3 g((unsigned)z->n_tiles), t(kZthreads);
   const unsigned lds = (unsigned)(kZslot * s->c.L * kZpitch * sizeof(double));   // 43520 bytes at 64 levels
   if (s->precision == THOR_MIXED)
-    hipLaunchKernelGGL(k_zinterp<float>, g, t, lds, s->stream, s->f32[s->parity], s->c, z->cols, z->plev, z->np, z->Z,
-                       z->Zw);
+    hipLaunchKernelGGL(k_zinterp<float>, g, t, lds, s->stream, s->f32[s->parity], s->c, z->cols, z->tiles, z->area,
+                       z->plev, z->np, z->P, z->Zw);
   else
-    hipLaunchKernelGGL(k_zinterp<double>, g, t, lds, s->stream, s->f64[s->parity], s->c, z->cols, z->plev, z->np, z->Z,
-                       z->Zw);
-  hipLaunchKernelGGL(k_zreduce, dim3(z->nb, z->np + 1), t, 0, s->stream, z->Z, z->Zw, z->np, s->c.N, z->off, z->cols,
-                     z->area, z->S, z->Wsum);
+    hipLaunchKernelGGL(k_zinterp<double>, g, t, lds, s->stream, s->f64[s->parity], s->c, z->cols, z->tiles, z->area,
+                       z->plev, z->np, z->P, z->Zw);
+  hipLaunchKernelGGL(k_zreduce, dim3(z->nb, (z->np + 3) / 4 + 1), t, 0, s->stream, z->P, z->Zw, z->np, z->n_tiles,
+                     z->toff, z->off, z->cols, z->area, z->S, z->Wsum);
   if (!zok(hipGetLastError(), "zonal accumulate")) return THOR_EHIP;
   z->snapshots += 1;
   return THOR_OK;

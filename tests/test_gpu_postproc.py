@@ -100,3 +100,9 @@ def test_zonal_means_at_the_edges_of_the_work_split(n_lev, n_plev, n_bands):
     imp, _ = z.imprint()
     imp_ref = opp.imprint_map([opp.imprint_snapshot(model, ost, n_bands)])
     assert np.abs(imp - imp_ref).max() <= 1e-9 * max(np.abs(opp.first_layer_w(model, ost)).max(), 1e-300)
+
+
+def test_zonal_means_in_several_passes_over_the_levels():
+    """More pressure levels than the interpolation takes at a time (64), the
+    last pass with one."""
+    test_zonal_means_at_the_edges_of_the_work_split(9, 129, 5)
