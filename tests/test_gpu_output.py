@@ -22,7 +22,7 @@ def check_scalars(st):
 
 
 @pytest.mark.parametrize("precision", [0, 1])
-@pytest.mark.parametrize("glevel,n_lev", [(0, 1), (2, 7), (3, 33), (2, 64)])
+@pytest.mark.parametrize("glevel,n_lev", [(0, 1), (2, 7), (3, 33), (2, 64), (4, 31)])   # the last: copied in two halves
 def test_output_equals_the_fields(glevel, n_lev, precision):
     say(f"[output] g{glevel} L{n_lev} precision {precision}")
     st = lib_state(small_earth(glevel=glevel, n_lev=n_lev), precision)
