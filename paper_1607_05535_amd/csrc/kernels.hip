@@ -817,6 +817,40 @@ __device__ __forceinline__ void b_vert2(const Fields<H> &f, const Consts &c, con
   }
 }
 
+// Held-Suarez boundary-layer friction (Eq. im_eq_v with K_v of Eq. im_eq_fv)
+// of a lane's cells after the last phase V of a large step, sg = sigma of the
+// dynamics output.  Phase V on the gather mapping ends with it (it gathers
+// the tangent components, so nothing else reads the Cartesian momentum then):
+// as a kernel of its own, which phase V left sigma for, it took 6.8 us at g5
+// L37, and so 377 us a step against 370 here.
+template <typename H>
+__device__ __forceinline__ void friction_cells(const Fields<H> &f, const Consts &c, size_t idx, int nv,
+                                               const H sg[kHq]) {
+  H mx[kHq], my[kHq], mz[kHq];
+  ld4<true>(f.Mx + idx, kHq, mx);
+  ld4<true>(f.My + idx, kHq, my);
+  ld4<true>(f.Mz + idx, kHq, mz);
+#pragma unroll
+  for (int q = 0; q < kHq; ++q) {
+    const double sigma = (double)sg[q];
+    const double kv = c.hs_kf * fmax(0.0, (sigma - c.hs_sb) / (1.0 - c.hs_sb));
+    const double den = 1.0 + kv * c.dt;
+    mx[q] = (H)((double)mx[q] / den);
+    my[q] = (H)((double)my[q] / den);
+    mz[q] = (H)((double)mz[q] / den);
+  }
+  // levels from L up are left as they are
+  if (nv == kHq) {
+    st4<true>(f.Mx + idx, kHq, mx);
+    st4<true>(f.My + idx, kHq, my);
+    st4<true>(f.Mz + idx, kHq, mz);
+  } else {
+    st4<false>(f.Mx + idx, nv, mx);
+    st4<false>(f.My + idx, nv, my);
+    st4<false>(f.Mz + idx, nv, mz);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Phase V on the gather mapping: a lane owns kHq = 4 consecutive levels
 // lev0..lev0+3 of one column (hlpc = ceil(L / 4) lanes per column, hcpw
@@ -856,8 +890,8 @@ __device__ __forceinline__ VLane map_vlane(const Consts &c, int lb) {
 }
 
 //
-// Bound by the memory system: per cell 16 words in and 5 out from the
-// last-level cache, and 21 gathered rows.  The momentum is gathered as two
+// Bound by the memory system: per cell 12 words in and 5 out from the
+// last-level cache, and 18 gathered rows from L2.  The momentum is gathered as two
 // tangent components (3 rows per neighbour with theta_L, not 4; 136 bytes of
 // stencil per column, not 192), and the density is carried as its deviation
 // from rho[t] inside a stage, so that only the stage's last substep reads
@@ -1130,7 +1164,7 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
     }
     if (end) rho_new[q] += rt[q];
     rth_new[q] = rth_hat[q] - ap * thIp * Wp[q] + am * thI[q] * Wn[q];
-    p[q] = c.p_ref * powd(c.rd_p * rth_new[q], c.gamma);
+    p[q] = LAST && c.forcing == THOR_FORCING_NONE ? 0.0 : c.p_ref * powd(c.rd_p * rth_new[q], c.gamma);
   }
   double hs_sigma[kHq] = {0.0, 0.0, 0.0, 0.0};
   if (LAST && c.forcing != THOR_FORCING_NONE) {
@@ -1144,59 +1178,45 @@ __device__ __forceinline__ void b_vert4(const Fields<H> &f, const Consts &c, con
     }
   }
   if (!ln.store) return;
+  // p* and D are for the stage's next substep and the next stage's slow terms:
+  // a stage's last substep leaves no D, the large step's neither (g6 L32 FP64
+  // 35.2 -> 34.6 us a substep on average, g7 L48 230.5 -> 227.6)
   H psn[kHq], dn[kHq];
 #pragma unroll
   for (int q = 0; q < kHq; ++q) {
     psn[q] = (H)(p[q] - pt[q]);
-    const double D3 = (double)drho[q] + (gp[q + 1] * Wp[q] - gm[q + 1] * Wn[q]);
-    dn[q] = (H)(LAST && c.forcing == THOR_FORCING_HELD_SUAREZ ? hs_sigma[q] : D3);
+    dn[q] = (H)((double)drho[q] + (gp[q + 1] * Wp[q] - gm[q + 1] * Wn[q]));
   }
   if (ln.nv == kHq) {
     st4<true>(f.rho + idx, kHq, rho_new);
     st4<true>(f.rth + idx, kHq, rth_new);
     st4<true>(f.W + idx, kHq, Wn);
-    st4<true>(f.ps + idx, kHq, psn);
-    st4<true>(f.D + idx, kHq, dn);
+    if (!LAST) st4<true>(f.ps + idx, kHq, psn);
+    if (!end) st4<true>(f.D + idx, kHq, dn);
   } else {
     st4<false>(f.rho + idx, ln.nv, rho_new);
     st4<false>(f.rth + idx, ln.nv, rth_new);
     st4<false>(f.W + idx, ln.nv, Wn);
-    st4<false>(f.ps + idx, ln.nv, psn);
-    st4<false>(f.D + idx, ln.nv, dn);
+    if (!LAST) st4<false>(f.ps + idx, ln.nv, psn);
+    if (!end) st4<false>(f.D + idx, ln.nv, dn);
+  }
+  if (LAST && c.forcing == THOR_FORCING_HELD_SUAREZ) {
+    H sg[kHq];
+#pragma unroll
+    for (int q = 0; q < kHq; ++q) sg[q] = (H)hs_sigma[q];
+    friction_cells(f, c, idx, ln.nv, sg);
   }
 }
 
-// Held-Suarez boundary-layer friction (Eq. im_eq_v with K_v of Eq. im_eq_fv)
-// after the last phase V of a large step, with sigma of the dynamics output
-// left in D by that kernel.  Other forcings: nothing.
+// The friction after the other forms of phase V and after the energy fixer,
+// which leave sigma in D.  Other forcings: nothing.
 template <typename H>
 __device__ __forceinline__ void b_friction(const Fields<H> &f, const Consts &c, const HLane &ln) {
   if (!ln.store || c.forcing != THOR_FORCING_HELD_SUAREZ) return;
   const size_t idx = (size_t)ln.col * c.S + ln.lev0;
-  H sg[kHq], mx[kHq], my[kHq], mz[kHq];
+  H sg[kHq];
   ld4<true>(f.D + idx, kHq, sg);
-  ld4<true>(f.Mx + idx, kHq, mx);
-  ld4<true>(f.My + idx, kHq, my);
-  ld4<true>(f.Mz + idx, kHq, mz);
-#pragma unroll
-  for (int q = 0; q < kHq; ++q) {
-    const double sigma = (double)sg[q];
-    const double kv = c.hs_kf * fmax(0.0, (sigma - c.hs_sb) / (1.0 - c.hs_sb));
-    const double den = 1.0 + kv * c.dt;
-    mx[q] = (H)((double)mx[q] / den);
-    my[q] = (H)((double)my[q] / den);
-    mz[q] = (H)((double)mz[q] / den);
-  }
-  // levels from L up are left as they are
-  if (ln.nv == kHq) {
-    st4<true>(f.Mx + idx, kHq, mx);
-    st4<true>(f.My + idx, kHq, my);
-    st4<true>(f.Mz + idx, kHq, mz);
-  } else {
-    st4<false>(f.Mx + idx, ln.nv, mx);
-    st4<false>(f.My + idx, ln.nv, my);
-    st4<false>(f.Mz + idx, ln.nv, mz);
-  }
+  friction_cells(f, c, idx, ln.nv, sg);
 }
 
 // ---------------------------------------------------------------------------
@@ -2246,8 +2266,9 @@ void launch_vert(const Fields<H> &f, const Consts &c, int wpb, int div, bool fir
     dispatch_vert<H, false>(f, c, wpb, s, ev0, ev1, div, flags);
     return;
   }
-  // with the friction kernel, the family ends with it
-  const bool fr = c.forcing == THOR_FORCING_HELD_SUAREZ;
+  // the one- and two-level forms leave the friction to a kernel of its own;
+  // the family ends with it
+  const bool fr = c.forcing == THOR_FORCING_HELD_SUAREZ && c.vnl != 4 && c.vorder != 3 && !c.anelastic;
   dispatch_vert<H, true>(f, c, wpb, s, ev0, fr ? nullptr : ev1, div, flags);
   if (fr) dispatch(k_friction<H>, dim3(n_blocks_h(c, 4)), dim3(256), s, nullptr, ev1, f, c);
 }
@@ -2352,8 +2373,6 @@ void launch_batch(const Planet<H> *P, const int2 *tiles, int n_tiles, int wpb, i
       break;
     case BatchOp::VertLast:
       hipLaunchKernelGGL((kb_vert<H, true>), g, b, 0, s, P, tiles, parity, arg0, arg1);
-      // the friction of Held-Suarez members (a no-op for the others), same tiles
-      hipLaunchKernelGGL(kb_friction<H>, g, b, 0, s, P, tiles, parity);
       break;
   }
 }
