@@ -3,20 +3,19 @@
 // Paper: Mendonca et al. 2016 (arXiv:1607.05535), Sec. 2-5.
 //
 // Work mappings.  Column data is contiguous in memory ([col][lev]).
-//  * Gather kernels (acoustic phase M, the gather half of phase V, slow
-//    terms, per-large-step terms): a lane owns kHq = 4 consecutive levels of
-//    one column, ceil(L / 4) lanes per column.  A neighbour row is read with
-//    16-byte loads, per-column stencil weights are loaded once per 4 cells,
-//    and a vertical neighbour is a register or, across a lane boundary, one
+//  * Gather mapping (every kernel of the step by default): a lane owns
+//    kHq = 4 consecutive levels of one column, ceil(L / 4) lanes per column.
+//    A neighbour row is read with 16-byte loads, per-column stencil weights
+//    are loaded once per 4 cells or staged in LDS per wavefront, and a
+//    vertical neighbour is a register or, across a lane boundary, one
 //    cross-lane shuffle.
-//  * Vertical solve (phase V): a wavefront covers cpw = floor(64 / L) whole
-//    columns with lane = (col - first col) * L + lev, so the implicit system
-//    of a column is solved in registers by cyclic reduction across its lanes
-//    (ceil(log2 L) shuffle rounds), an exact direct solver of the same
-//    tridiagonal the Thomas algorithm solves.  Its horizontal divergences
-//    are gathered with the same mapping: staging them through LDS from the
-//    gather mapping leaves 4x fewer wavefronts, each solving 4 column groups
-//    in turn, and measured slower.
+//  * Column mapping (the other forms of phase V): a wavefront covers
+//    cpw = floor(64 / L) whole columns with lane = (col - first col) * L +
+//    lev, and the implicit system of a column is solved in registers by
+//    cyclic reduction across its lanes (ceil(log2 L) shuffle rounds).
+//  Both solve the tridiagonal of the Thomas algorithm directly.  The
+//  horizontal momentum of a step is held as two components along the
+//  column's own east and north; the folded coefficients come in that basis.
 //
 // Horizontal stencils use folded coefficients built on the host:
 //   div F = (1/r) sum_{j=0..6} c_j . F_j                   (Eqs. flx_div, int_grid, div_gauss)
@@ -53,6 +52,10 @@
 #ifndef LARGE1_OCC_F
 #define LARGE1_OCC_F 2
 #endif
+// Minimum wavefronts per SIMD of phase V on the gather mapping and the
+// neighbours whose rows it loads together.  All six together are 18 rows of
+// 2 KiB in flight per wavefront, past the 32 KiB of L1 for the compute unit:
+// 70 us against 35 at g6 L32 FP64; its own rows before the neighbours' 39 us.
 #ifndef VERT4_OCC
 #define VERT4_OCC 2
 #endif
