@@ -33,6 +33,7 @@ struct Fields {
   const H *lc;            // [N][kLc] Laplacian neighbour weights (6)
   const H *rhat;          // [N][3]
   const H *frame;         // [N][kFr] local east e, north n and rhat of the column (9)
+  const double *frame64;  // [N][6] e and n of the positions as the mixed form holds them, in FP64 (mixed form only)
   const H *dv;            // [N][kDv] divergence coefficients of (Ma, Mb): c_j . (e, n) of column j (14)
   const H *gt;            // [N][kGt] gradient coefficients in the column's own basis (6 x 2)
   const int32_t *ddi;     // [N][18] two-ring columns
@@ -127,29 +128,19 @@ __device__ __forceinline__ void row4(const float *p, float v[kHq]) {
   v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
 }
 
-// Local east and north of a column in FP64.  The FP64 state reads them from
-// its table; a mixed state's table is FP32, so what leaves it as FP64 or is
-// rounded once (diagnostics, zonal means, network inputs, corrections) forms
-// them from rhat: no angle is needed (at a pole the longitude counts as 0).
+// Local east and north of a column in FP64.  A mixed state's table is FP32;
+// what leaves it as FP64 or is rounded once (diagnostics, zonal means, network
+// inputs, corrections) and the change of basis at the ends of a large step
+// take them from a table of their own.
 template <typename H>
 __device__ __forceinline__ void tangent64(const Fields<H> &f, int col, double e[3], double n[3]) {
-  if (sizeof(H) == sizeof(double)) {
-    const H *fr = f.frame + (size_t)col * kFr;
-    for (int k = 0; k < 3; ++k) {
-      e[k] = fr[k];
-      n[k] = fr[3 + k];
-    }
-    return;
+  const double *t = sizeof(H) == sizeof(double) ? reinterpret_cast<const double *>(f.frame) + (size_t)col * kFr
+                                                : f.frame64 + (size_t)col * 6;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    e[k] = t[k];
+    n[k] = t[3 + k];
   }
-  const H *rh = f.rhat + (size_t)col * 3;
-  const double x = rh[0], y = rh[1], z = fmin(1.0, fmax(-1.0, (double)rh[2])), h = sqrt(x * x + y * y);
-  const double cl = h < 1e-12 ? 1.0 : x / h, sl = h < 1e-12 ? 0.0 : y / h;
-  e[0] = -sl;
-  e[1] = cl;
-  e[2] = 0.0;
-  n[0] = -z * cl;
-  n[1] = -z * sl;
-  n[2] = sqrt((1.0 - z) * (1.0 + z));
 }
 
 struct Consts {

@@ -370,18 +370,23 @@ __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, 
       ddb[q] *= s;
     }
   }
-  const H *fr = f.frame + (size_t)col * kFr;
   const H dt = (H)dtau;
   H ma[kHq], mb[kHq], sa[kHq], sb[kHq];
   if (FIRST) {
+    // the change of basis, here and at the end of the large step, is in FP64:
+    // an FP32 e and n are no unit vectors, and the momentum of the mixed form
+    // would grow or decay by up to 6e-8 every step (u after a day at g7 4.3e-7
+    // off the FP64 form, 2.0e-7 so)
+    double e[3], n[3];
+    tangent64(f, col, e, n);
     H mx[kHq], my[kHq], mz[kHq];
     ld4<VEC>(f.Mx_t + idx, nv, mx);
     ld4<VEC>(f.My_t + idx, nv, my);
     ld4<VEC>(f.Mz_t + idx, nv, mz);
 #pragma unroll
     for (int q = 0; q < kHq; ++q) {
-      ma[q] = mx[q] * fr[0] + my[q] * fr[1] + mz[q] * fr[2];
-      mb[q] = mx[q] * fr[3] + my[q] * fr[4] + mz[q] * fr[5];
+      ma[q] = (H)((double)mx[q] * e[0] + (double)my[q] * e[1] + (double)mz[q] * e[2]);
+      mb[q] = (H)((double)mx[q] * n[0] + (double)my[q] * n[1] + (double)mz[q] * n[2]);
     }
   } else {
     ld4<VEC>(f.Ma + idx, nv, ma);
@@ -398,12 +403,16 @@ __device__ __forceinline__ void hmom_cells(const Fields<H> &f, const Consts &c, 
   st4<VEC>(f.Ma + idx, nv, ma);
   st4<VEC>(f.Mb + idx, nv, mb);
   if (last) {
+    // (not to be hoisted over the sums above: the mixed form then spills)
+    if (sizeof(H) == 4) __builtin_amdgcn_sched_barrier(0);
+    double e[3], n[3];
+    tangent64(f, col, e, n);
     H mx[kHq], my[kHq], mz[kHq];
 #pragma unroll
     for (int q = 0; q < kHq; ++q) {
-      mx[q] = ma[q] * fr[0] + mb[q] * fr[3];
-      my[q] = ma[q] * fr[1] + mb[q] * fr[4];
-      mz[q] = ma[q] * fr[2] + mb[q] * fr[5];
+      mx[q] = (H)((double)ma[q] * e[0] + (double)mb[q] * n[0]);
+      my[q] = (H)((double)ma[q] * e[1] + (double)mb[q] * n[1]);
+      mz[q] = (H)((double)ma[q] * e[2] + (double)mb[q] * n[2]);
     }
     st4<VEC>(f.Mx + idx, nv, mx);
     st4<VEC>(f.My + idx, nv, my);

@@ -70,3 +70,25 @@ def test_mixed_four_levels_per_lane_matches_one_level():
         assert err[k] < 1e-7, (k, err[k])
     for k in ("u", "v", "w"):
         assert err[k] < 1e-5, (k, err[k])
+
+
+def test_changing_the_basis_of_the_momentum_leaves_it_alone():
+    """Steps so short that nothing moves: the horizontal momentum of a mixed
+    state then changes by its roundings alone, two a step (into the tangent
+    components and back), which add up like a random walk, at most 4 standard
+    deviations of 2^-24 here; a basis of length 1 + 6e-8 would scale it by
+    10^-4 over these 4000 steps."""
+    w = small_earth(glevel=2, n_lev=4)
+    w.dt, w.diff_D, w.div_damp = 1e-7, 0.0, False
+    st = lib_state(w, 1)
+    blob = st.export()[0]
+    NL = st.n_col * st.n_lev
+    rng = np.random.default_rng(9)
+    blob[4 + NL:4 + 4 * NL] = rng.standard_normal(3 * NL)
+    st.load(blob)
+    st.step(1, 6)          # leaves the tangent part
+    m0 = st.export()[0][4 + NL:4 + 4 * NL]
+    n = 4000
+    st.step(n, 6)
+    m1 = st.export()[0][4 + NL:4 + 4 * NL]
+    assert np.abs(m1 - m0).max() <= 4 * np.sqrt(2 * n) * 2.0 ** -24 * np.abs(m0).max()
