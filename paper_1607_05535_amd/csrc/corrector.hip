@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256) void k_fields(Fields<H> f, Consts c, float *ou
   W[kHq] = lev0 + kHq < L ? f.W_t[idx + kHq] : 0.0;
   if (lev0 == 0) W[0] = 0.0;
   double e[3], n[3];
-  tangent64(f, col, e, n);
+  wind64(f, col, e, n);
   float o[kF][kHq];
 #pragma unroll
   for (int q = 0; q < kHq; ++q) {
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(256) void k_apply(Fields<H> f, Consts c, const floa
   if (k == 0 && applied) applied[ln.col] = ok ? 1 : 0;
   if (!ok) return;
   double e[3], n[3];
-  tangent64(f, ln.col, e, n);
+  wind64(f, ln.col, e, n);
   const double r = rho1 / rho;
   f.Mx_t[idx] = (H)(r * (double)f.Mx_t[idx] + rho1 * (du * e[0] + dv * n[0]));
   f.My_t[idx] = (H)(r * (double)f.My_t[idx] + rho1 * (du * e[1] + dv * n[1]));

@@ -33,7 +33,8 @@ struct Fields {
   const H *lc;            // [N][kLc] Laplacian neighbour weights (6)
   const H *rhat;          // [N][3]
   const H *frame;         // [N][kFr] local east e, north n and rhat of the column (9)
-  const double *frame64;  // [N][6] e and n of the positions as the mixed form holds them, in FP64 (mixed form only)
+  const double *frame64;  // [N][6] e and n of the column in FP64 (mixed form only)
+  const double *wind64;   // [N][6] the same of the position as the mixed form holds it (mixed form only)
   const H *dv;            // [N][kDv] divergence coefficients of (Ma, Mb): c_j . (e, n) of column j (14)
   const H *gt;            // [N][kGt] gradient coefficients in the column's own basis (6 x 2)
   const int32_t *ddi;     // [N][18] two-ring columns
@@ -128,19 +129,32 @@ __device__ __forceinline__ void row4(const float *p, float v[kHq]) {
   v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
 }
 
-// Local east and north of a column in FP64.  A mixed state's table is FP32;
-// what leaves it as FP64 or is rounded once (diagnostics, zonal means, network
-// inputs, corrections) and the change of basis at the ends of a large step
-// take them from a table of their own.
+// Local east and north of a column in FP64 (a mixed state's `frame` is FP32):
+// tangent64 for the change of basis at the ends of a large step, of the column
+// itself, as the coefficients of the step are; wind64 for what reads the winds
+// of a state or corrects them (diagnostics, zonal means, network inputs,
+// corrections), in the mixed form of the FP32 position.  The rounding of a
+// position's z moves that north out of the column's tangent plane by up to
+// 3e-8 / cos(lat), 9.7e-7 at g6, which a component along it feels in second
+// order, but a momentum built from it in first: the step's own basis leaves M
+// within FP32 rounding (4.4e-8 |M| at g6) of the plane.
 template <typename H>
-__device__ __forceinline__ void tangent64(const Fields<H> &f, int col, double e[3], double n[3]) {
+__device__ __forceinline__ void basis64(const Fields<H> &f, const double *mixed, int col, double e[3], double n[3]) {
   const double *t = sizeof(H) == sizeof(double) ? reinterpret_cast<const double *>(f.frame) + (size_t)col * kFr
-                                                : f.frame64 + (size_t)col * 6;
+                                                : mixed + (size_t)col * 6;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     e[k] = t[k];
     n[k] = t[3 + k];
   }
+}
+template <typename H>
+__device__ __forceinline__ void tangent64(const Fields<H> &f, int col, double e[3], double n[3]) {
+  basis64(f, f.frame64, col, e, n);
+}
+template <typename H>
+__device__ __forceinline__ void wind64(const Fields<H> &f, int col, double e[3], double n[3]) {
+  basis64(f, f.wind64, col, e, n);
 }
 
 struct Consts {

@@ -1856,7 +1856,7 @@ __device__ __forceinline__ void b_diag(const Fields<H> &f, const Consts &c, cons
     out = field == THOR_F_P ? p : p / (rho * c.Rd);
   } else if (field == THOR_F_U || field == THOR_F_V) {
     double east[3], north[3];
-    tangent64(f, col, east, north);
+    wind64(f, col, east, north);
     const double *e = field == THOR_F_U ? east : north;
     const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
     out = e[0] * vx + e[1] * vy + e[2] * vz;
@@ -1949,7 +1949,7 @@ __global__ __launch_bounds__(256) void k_extremes(Fields<H> f, Consts c, double 
     const double rho = f.rho_t[idx];
     const double W = lev == 0 ? 0.0 : f.W_t[idx], W1 = (int)lev == c.L - 1 ? 0.0 : f.W_t[idx + 1];
     double east[3], north[3];
-    tangent64(f, (int)col, east, north);
+    wind64(f, (int)col, east, north);
     const double vx = (double)f.Mx_t[idx] / rho, vy = (double)f.My_t[idx] / rho, vz = (double)f.Mz_t[idx] / rho;
     const double u = east[0] * vx + east[1] * vy + east[2] * vz;
     const double v = north[0] * vx + north[1] * vy + north[2] * vz;

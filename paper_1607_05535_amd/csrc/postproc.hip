@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kZthreads) void k_zinterp(Fields<H> f, Consts c, co
     const double rho = f.rho_t[idx], rth = f.rth_t[idx];
     const double p = c.p_ref * powd(c.Rd * rth / c.p_ref, c.gamma);
     double e[3], n[3];
-    tangent64(f, col, e, n);
+    wind64(f, col, e, n);
     const double ir = rcpd(rho);
     const double vx = quot((double)f.Mx_t[idx], rho, ir), vy = quot((double)f.My_t[idx], rho, ir),
                  vz = quot((double)f.Mz_t[idx], rho, ir);

@@ -64,6 +64,7 @@ void carve(Carver &cv, Fields<H> &f, size_t N, size_t L, bool anelastic) {
   f.rhat = cv.take<H>(N * 3);
   f.frame = cv.take<H>(N * kFr);
   f.frame64 = sizeof(H) == sizeof(double) ? nullptr : cv.take<double>(N * 6);
+  f.wind64 = sizeof(H) == sizeof(double) ? nullptr : cv.take<double>(N * 6);
   f.dv = cv.take<H>(N * kDv);
   f.gt = cv.take<H>(N * kGt);
   f.ddi = cv.take<int32_t>(N * kRing2);
@@ -252,19 +253,20 @@ int upload(thor_state *s, const Grid &G, const thor_planet *pl, const thor_verti
   const HostArray<H> dc(G.div_coef, 21, kDc), lc(G.lap_coef, 6, kLc), frame(G.frame), dv(G.div_t), gt(G.grad_t),
       ddw(G.dd_t);
   std::vector<H> rh(N * 3);
-  std::vector<double> basis(f.frame64 ? N * 6 : 0);
+  std::vector<double> basis(f.frame64 ? N * 6 : 0), wind(f.wind64 ? N * 6 : 0);
   std::vector<double> teq(N);
   for (size_t i = 0; i < N; ++i) {
     const Vec3 p = G.pos[i];
     rh[3 * i] = (H)p.x;
     rh[3 * i + 1] = (H)p.y;
     rh[3 * i + 2] = (H)p.z;
-    if (f.frame64) {
+    if (f.frame64) std::copy(&G.frame[12 * i], &G.frame[12 * i] + 6, &basis[6 * i]);
+    if (f.wind64) {
       // of the rounded position (at a pole the longitude counts as 0)
       const double x = rh[3 * i], y = rh[3 * i + 1], z = std::fmin(1.0, std::fmax(-1.0, (double)rh[3 * i + 2]));
       const double h = std::sqrt(x * x + y * y), cl = h < 1e-12 ? 1.0 : x / h, sl = h < 1e-12 ? 0.0 : y / h;
       const double b[6] = {-sl, cl, 0.0, -z * cl, -z * sl, std::sqrt((1.0 - z) * (1.0 + z))};
-      std::copy(b, b + 6, &basis[6 * i]);
+      std::copy(b, b + 6, &wind[6 * i]);
     }
     double lam = std::sqrt(p.x * p.x + p.y * p.y) < 1e-12 ? 0.0 : std::atan2(p.y, p.x);
     double phi = std::asin(std::fmin(1.0, std::fmax(-1.0, p.z)));
@@ -309,6 +311,7 @@ int upload(thor_state *s, const Grid &G, const thor_planet *pl, const thor_verti
             hip_ok(hipMemcpyAsync((void *)f.rhat, rh.data(), rh.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy rhat") &&
             hip_ok(hipMemcpyAsync((void *)f.frame, frame.data(), frame.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy frame") &&
             (!f.frame64 || hip_ok(hipMemcpyAsync((void *)f.frame64, basis.data(), basis.size() * sizeof(double), hipMemcpyHostToDevice, st), "copy basis")) &&
+            (!f.wind64 || hip_ok(hipMemcpyAsync((void *)f.wind64, wind.data(), wind.size() * sizeof(double), hipMemcpyHostToDevice, st), "copy wind basis")) &&
             hip_ok(hipMemcpyAsync((void *)f.dv, dv.data(), dv.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy dv") &&
             hip_ok(hipMemcpyAsync((void *)f.gt, gt.data(), gt.size() * sizeof(H), hipMemcpyHostToDevice, st), "copy gt") &&
             hip_ok(hipMemcpyAsync((void *)f.ddi, G.dd_own.data(), G.dd_own.size() * sizeof(int32_t), hipMemcpyHostToDevice, st), "copy ddi") &&

@@ -92,3 +92,22 @@ def test_changing_the_basis_of_the_momentum_leaves_it_alone():
     st.step(n, 6)
     m1 = st.export()[0][4 + NL:4 + 4 * NL]
     assert np.abs(m1 - m0).max() <= 4 * np.sqrt(2 * n) * 2.0 ** -24 * np.abs(m0).max()
+
+
+def test_stored_momentum_is_tangent():
+    """The horizontal momentum that a step of the mixed form leaves lies in the
+    column's tangent plane: what is off is the FP32 rounding of its three
+    components, 2^-24 of |M| along the column's direction at most, next to the
+    poles (where an east and north built from rounded positions tilt) as
+    elsewhere."""
+    w = small_earth(glevel=5, n_lev=2)
+    w.dt, w.diff_D, w.div_damp = 1e-7, 0.0, False   # too short for the momentum to move
+    st = lib_state(w, 1)
+    blob = st.export()[0]
+    NL = st.n_col * st.n_lev
+    blob[4 + NL:4 + 4 * NL] = np.random.default_rng(3).standard_normal(3 * NL)
+    st.load(blob)
+    st.step(1, 6)
+    m = st.export()[0][4 + NL:4 + 4 * NL].reshape(3, st.n_col, st.n_lev)
+    radial = np.einsum("kil,ik->il", m, st.grid.export()[1])
+    assert np.all(np.abs(radial) <= (2.0 ** -24 + 1e-14) * np.sqrt((m ** 2).sum(0)))
