@@ -187,7 +187,7 @@ __device__ __forceinline__ void gemm_tile(const __bf16 *__restrict__ A, int lda,
     step(i + 1, std::integral_constant<int, 1>());
   }
   if (i < nt) step(i, std::integral_constant<int, 0>());
-  float sq = 0.f;   // this lane's squared errors
+  double sq = 0.0;   // this lane's squared errors, rounded once per tile
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -207,7 +207,7 @@ __device__ __forceinline__ void gemm_tile(const __bf16 *__restrict__ A, int lda,
           float g;
           if (EPI == EPI_LOSS) {
             const float d = z - ref;
-            sq += d * d;
+            sq += (double)d * d;
             g = 2.f * d / epi.scale;
           } else {
             g = z * gelu_grad_f(ref);
@@ -219,11 +219,11 @@ __device__ __forceinline__ void gemm_tile(const __bf16 *__restrict__ A, int lda,
     }
   if (EPI == EPI_LOSS) {
     // (the operand tiles are free: every wavefront passed the last barrier)
-    float *sm = reinterpret_cast<float *>(As[0]);
+    double *sm = reinterpret_cast<double *>(As[0]);
     for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
     if (lane == 0) sm[w] = sq;
     __syncthreads();
-    if (threadIdx.x == 0) epi.loss[(size_t)tn * ((M + kTile - 1) / kTile) + tm] = ((sm[0] + sm[1]) + sm[2]) + sm[3];
+    if (threadIdx.x == 0) epi.loss[(size_t)tn * ((M + kTile - 1) / kTile) + tm] = (float)(((sm[0] + sm[1]) + sm[2]) + sm[3]);
   }
 }
 
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(64 * kFW) void k_mlp_train4(TrainNet net, const __b
   clear();
   fused_layer<false, kFH, FI, R>(fw, use3, hid[0], acc, ring);
   weights(net.Wt[3], N3, tile);
-  float sq = 0.f;
+  double sq = 0.0;   // squared errors, rounded once per workgroup
 #pragma unroll
   for (int j = 0; j < kFT; ++j) {
     if (!use3[j]) continue;
@@ -689,20 +689,20 @@ __global__ __launch_bounds__(64 * kFW) void k_mlp_train4(TrainNet net, const __b
         const size_t o = (m0 + row) * N3 + col;
         const float y = acc[i][j][q] + bb;
         const float d = y - T[o];
-        sq += d * d;
+        sq += (double)d * d;
         const float g = 2.f * d / scale;
         net.dZ[3][o] = g;
         hid[1][row * kHRow + col] = (__bf16)g;
       }
   }
   for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
-  float *sums = reinterpret_cast<float *>(xs);   // the input tile is free
+  double *sums = reinterpret_cast<double *>(xs);   // the input tile is free
   if (lane == 0) sums[w] = sq;
   __syncthreads();
   if (threadIdx.x == 0) {
-    float s = 0.f;
+    double s = 0.0;
     for (int i = 0; i < kFW; ++i) s += sums[i];
-    loss[blockIdx.x] = s;
+    loss[blockIdx.x] = (float)s;
   }
   store_rows<R>(hid[1], net.dZb[3] + m0 * N3, N3);
 #pragma unroll

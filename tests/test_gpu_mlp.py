@@ -191,3 +191,22 @@ def test_fused_training_equals_layer_by_layer(w_in, w_out, B):
         assert abs(a[k] - b[k]) <= 64 * 2.0 ** -24 * a[k]
     for k in (2, 3, 4):
         assert np.array_equal(a[k], b[k])
+
+
+@pytest.mark.parametrize("widths,B", [([32, 32], 32), ([64, 96, 160], 160), ([64, 256, 256, 256, 256], 64),
+                                      ([64, 256, 256, 256, 160], 96), ([64, 256, 256, 256, 256], 4128)])
+@pytest.mark.parametrize("c", [3667 / 2048, 2049 / 2048])
+def test_loss_adds_squares_without_losing_digits(widths, B, c):
+    """Zero parameters and equal targets: every squared error is the same
+    24-bit number, whose FP32 sums one after the other all round the same way
+    (3.7 and 2 units over the 16 and 8 squares of a lane).  A partial sum may
+    round once: 2^-24."""
+    import torch
+    from paper_1607_05535_amd import thor
+    net = thor.MLP(widths, B)
+    net.set_params(np.zeros(net.n_params, np.float32))
+    x = torch.zeros(B, widths[0], dtype=torch.bfloat16, device="cuda:0")
+    t = torch.full((B, widths[-1]), c, device="cuda:0")
+    for fused in (True, False):
+        net.set_fused(fused)
+        assert abs(net.loss_grad(x, t, want_grad=False)[0] / c ** 2 - 1) <= 2.0 ** -24
