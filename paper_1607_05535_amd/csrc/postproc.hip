@@ -327,7 +327,7 @@ size_t zonal_layout(thor_zonal *z, size_t N, char *base) {
     return p;
   };
   z->plev = (double *)take(z->np * sizeof(double));
-  const size_t tiles = N / kZcols + z->nb;   // at most: one partly filled tile per band
+  const size_t tiles = std::min(N, N / kZcols + z->nb);   // at most: one partly filled tile per band, none empty
   z->P = (double *)take(tiles * z->np * kZrec * sizeof(double));
   z->tiles = (int2 *)take(tiles * sizeof(int2));
   z->toff = (int32_t *)take((z->nb + 1) * sizeof(int32_t));

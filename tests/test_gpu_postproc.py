@@ -106,3 +106,19 @@ def test_zonal_means_in_several_passes_over_the_levels():
     """More pressure levels than the interpolation takes at a time (64), the
     last pass with one."""
     test_zonal_means_at_the_edges_of_the_work_split(9, 129, 5)
+
+
+def test_many_bands_on_a_small_grid():
+    """More bands than columns: a record per column at most (88 bytes per
+    pressure level, beside 64 of sums per band and level), and the same means."""
+    import ctypes
+    from paper_1607_05535_amd import thor
+    w = workloads.small_gas_giant(glevel=2, n_lev=12)
+    st = thor.State(thor.Grid(2), *thor.structs_from_workload(w))
+    N, nb, plev = st.n_col, 4095, np.linspace(1e3, 1e7, 1024)
+    n = ctypes.c_size_t()
+    assert thor.lib().thor_zonal_bytes(st.handle, nb, plev.ctypes.data, plev.size, ctypes.byref(n)) == 0
+    arrays = 8 * plev.size + N * (88 * plev.size + 8) + 4 * (nb + 1) + 64 * nb * plev.size + N * 8 + 4 * (nb + 1) + \
+        4 * N + 16 * N
+    assert n.value <= arrays + 10 * 256
+    test_zonal_means_at_the_edges_of_the_work_split(9, 3, nb)
