@@ -197,6 +197,7 @@ __global__ __launch_bounds__(kZthreads) void k_zreduce(const double *P, const do
                                                        const double *area, double *S, double *Wsum) {
   __shared__ double sm[kZthreads / 64][2];
   const int b = blockIdx.x, a0 = off[b], a1 = off[b + 1];
+  if (a0 == a1) return;   // empty band (a snapshot of 4096 bands over 162 columns: 36 -> 12.5 us)
   if (blockIdx.y == gridDim.y - 1) {
     double s[2] = {0, 0};
     for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) {
@@ -204,7 +205,6 @@ __global__ __launch_bounds__(kZthreads) void k_zreduce(const double *P, const do
       s[1] += area[i] * Zw[i];
     }
     block_sums<2>(s, sm);
-    if (s[0] == 0.0) return;   // empty band, uniform across the workgroup
     const double mw = s[1] / s[0];
     for (int i = a0 + threadIdx.x; i < a1; i += kZthreads) Wsum[cols[i]] += Zw[i] - mw;
     return;
