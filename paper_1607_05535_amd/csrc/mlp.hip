@@ -39,6 +39,14 @@ constexpr int kRow = kStepK + 8;   // LDS row of a staged tile (bf16), padded
 constexpr int kMaxSplit = 8;       // batch chunks of the weight gradient
 constexpr int kBiasSplit = 32;     // batch chunks of the bias gradient
 constexpr int kMaxLayers = 16;
+// Bytes of split-K partial sums that layers share a gradient launch within
+// (the corrector's four take 15 MB).  Larger networks go through it in groups,
+// their partial sums in the same place one group after another, so that 16
+// layers of 4096 x 4096 need 0.5 GiB for them and not 8.  A group of this size
+// has 2048 product tiles per batch chunk, eight per compute unit; with 64 MiB
+// an Adam step of three 1024 x 1024 layers on 32 rows, then two groups, took
+// 102 us against 95 in one.
+constexpr size_t kSplitBytes = (size_t)256 << 20;
 
 enum Epilogue { EPI_STORE = 0, EPI_GELU = 1, EPI_GELU_ONLY = 2, EPI_LOSS = 3, EPI_ACT_GRAD = 4 };
 
@@ -250,7 +258,8 @@ __device__ __forceinline__ void colsum_tile(const float *X, int B, int N, int ro
   if (g == 0 && n < N) part[(size_t)chunk * N + n] = ((sm[0][c] + sm[1][c]) + sm[2][c]) + sm[3][c];
 }
 
-// Weight and bias gradients of every layer in one launch (they only need the
+// Weight and bias gradients of every layer of a group (kSplitBytes; all layers
+// of the corrector's networks) in one launch (they only need the
 // pre-activation gradients and the activations, which all exist by then, and
 // one layer's 16-72 tiles fill few compute units).  dW[N][K] = dZ^T H_prev,
 // both operands read with the batch as outer index, in S batch chunks of
@@ -312,15 +321,15 @@ struct UpdateLayer {
 struct UpdateNet {
   UpdateLayer l[kMaxLayers];
   int nl, S;
+  size_t p0, p1;   // the group's range of the packed parameters
 };
 struct Adam {
   float lr, b1, b2, eps, c1, c2;
 };
 template <bool ADAM>
-__global__ __launch_bounds__(256) void k_update(UpdateNet net, size_t n, float *p, float *m, float *v, float *grad,
-                                                Adam a) {
-  const size_t i = (blockIdx.x * (size_t)blockDim.x + threadIdx.x) * kUpd;
-  if (i >= n) return;
+__global__ __launch_bounds__(256) void k_update(UpdateNet net, float *p, float *m, float *v, float *grad, Adam a) {
+  const size_t i = net.p0 + (blockIdx.x * (size_t)blockDim.x + threadIdx.x) * kUpd;
+  if (i >= net.p1) return;
   int l = 0;
   while (l + 1 < net.nl && i >= net.l[l + 1].woff) ++l;
   const UpdateLayer &L = net.l[l];
@@ -788,7 +797,8 @@ struct thor_mlp {
   std::vector<__bf16 *> H;       // hidden activations, [B][w_{l+1}]
   std::vector<float *> dZ;       // gradients of the pre-activations
   std::vector<__bf16 *> dZb;
-  std::vector<float *> split;    // partial sums of the weight gradient, [kMaxSplit][w_{l+1}][w_l]
+  std::vector<int> group;        // first layer of each gradient launch, and the number of layers
+  std::vector<float *> split;    // partial sums of the weight gradient, [kMaxSplit][w_{l+1}][w_l], shared by the groups
   std::vector<float *> bsum;     // and of the bias gradient, [kBiasSplit][w_{l+1}]
   float *partial = nullptr;      // loss partial sums, one per output tile or workgroup of the fused pass
   int adam_t = 0;
@@ -834,6 +844,20 @@ size_t mlp_layout(thor_mlp *M, char *base) {
   M->dZb.assign(nl, nullptr);
   M->split.assign(nl, nullptr);
   M->bsum.assign(nl, nullptr);
+  M->group.clear();
+  std::vector<size_t> at(nl);   // of a layer's partial sums in the shared area
+  size_t used = 0, most = 0;
+  for (int l = 0; l < nl; ++l) {
+    const size_t bytes = a256((size_t)kMaxSplit * M->w[l] * M->w[l + 1] * 4);
+    if (l == 0 || used + bytes > kSplitBytes) {
+      M->group.push_back(l);
+      used = 0;
+    }
+    at[l] = used;
+    used += bytes;
+    most = std::max(most, used);
+  }
+  M->group.push_back(nl);
   for (int l = 0; l < nl; ++l) {
     const size_t wsz = (size_t)M->w[l] * M->w[l + 1];
     M->Wb[l] = (__bf16 *)take(wsz * 2);
@@ -845,9 +869,11 @@ size_t mlp_layout(thor_mlp *M, char *base) {
     }
     M->dZ[l] = (float *)take((size_t)B * M->w[l + 1] * 4);
     M->dZb[l] = (__bf16 *)take((size_t)B * M->w[l + 1] * 2);
-    M->split[l] = (float *)take(kMaxSplit * wsz * 4);
     M->bsum[l] = (float *)take((size_t)kBiasSplit * M->w[l + 1] * 4);
   }
+  char *const split = take(most);
+  if (base)
+    for (int l = 0; l < nl; ++l) M->split[l] = (float *)(split + at[l]);
   M->partial = (float *)take(std::max(tiles * ((M->w[nl] + kTile - 1) / kTile), ((size_t)B + 15) / 16) * 4);
   return off;
 }
@@ -984,40 +1010,39 @@ int passes_fused(thor_mlp *M, const __bf16 *X, const float *T, int B) {
   return wg;
 }
 
-struct Parts {
-  int grad, loss;   // batch chunks of a weight gradient; partial sums of the loss
-};
-
-// Forward and backward pass of the mean-squared loss, up to the partial sums
-// of the gradients (M->split, M->bsum) and of the loss (M->partial).
-Parts loss_and_grad(thor_mlp *M, const __bf16 *X, const float *T, int B) {
-  const int nl = M->nl;
-  hipStream_t s = M->stream;
-  const int n_loss = fused_shape(M) && M->fused ? passes_fused(M, X, T, B) : passes_by_layer(M, X, T, B);
+// Gradients of every parameter from the passes' results, group by group: into
+// M->g, or (ADAM) into an Adam step.
+template <bool ADAM>
+void gradients(thor_mlp *M, const __bf16 *X, int B, const Adam &a) {
   const int splits = grad_splits(B);
   const int chunk = ((B + splits - 1) / splits + kStepK - 1) / kStepK * kStepK, S = (B + chunk - 1) / chunk;
-  GradNet g{};
-  g.nl = nl;
-  g.S = S;
-  int sums = 0;
-  for (int l = 0; l < nl; ++l) {
-    const int K = M->w[l], N = M->w[l + 1], tn = (K + kTile - 1) / kTile;
-    g.l[l] = GradLayer{M->dZb[l], l ? M->H[l - 1] : X, M->dZ[l], M->split[l], M->bsum[l], N, K, tn, g.tiles, sums};
-    g.tiles += (N + kTile - 1) / kTile * tn;
-    sums += (N + 63) / 64 * kBiasSplit;
+  for (size_t k = 0; k + 1 < M->group.size(); ++k) {
+    const int l0 = M->group[k], l1 = M->group[k + 1];
+    GradNet g{};
+    UpdateNet u{};
+    g.nl = u.nl = l1 - l0;
+    g.S = u.S = S;
+    u.p0 = M->woff[l0];
+    u.p1 = l1 < M->nl ? M->woff[l1] : M->n_params;
+    int sums = 0;
+    for (int l = l0; l < l1; ++l) {
+      const int K = M->w[l], N = M->w[l + 1], tn = (K + kTile - 1) / kTile;
+      g.l[l - l0] = GradLayer{M->dZb[l], l ? M->H[l - 1] : X, M->dZ[l], M->split[l], M->bsum[l], N, K, tn, g.tiles, sums};
+      u.l[l - l0] = UpdateLayer{M->split[l], M->bsum[l], M->Wb[l], M->Wf[l], M->Wt[l], M->woff[l], N, K};
+      g.tiles += (N + kTile - 1) / kTile * tn;
+      sums += (N + 63) / 64 * kBiasSplit;
+    }
+    hipLaunchKernelGGL(k_grad, dim3(g.tiles * S + sums), dim3(256), 0, M->stream, g, B, chunk,
+                       (B + kBiasSplit - 1) / kBiasSplit);
+    hipLaunchKernelGGL(k_update<ADAM>, dim3(nb((u.p1 - u.p0) / kUpd)), dim3(256), 0, M->stream, u, M->p, M->m, M->v,
+                       M->g, a);
   }
-  hipLaunchKernelGGL(k_grad, dim3(g.tiles * S + sums), dim3(256), 0, s, g, B, chunk,
-                     (B + kBiasSplit - 1) / kBiasSplit);
-  return Parts{S, n_loss};
 }
 
-UpdateNet update_net(thor_mlp *M, int S) {
-  UpdateNet u{};
-  u.nl = M->nl;
-  u.S = S;
-  for (int l = 0; l < M->nl; ++l)
-    u.l[l] = UpdateLayer{M->split[l], M->bsum[l], M->Wb[l], M->Wf[l], M->Wt[l], M->woff[l], M->w[l + 1], M->w[l]};
-  return u;
+// Forward and backward pass of the mean-squared loss; the number of its
+// partial sums.
+int passes(thor_mlp *M, const __bf16 *X, const float *T, int B) {
+  return fused_shape(M) && M->fused ? passes_fused(M, X, T, B) : passes_by_layer(M, X, T, B);
 }
 
 // SplitMix64 stream and Box-Muller normals for the initial weights.
@@ -1125,10 +1150,8 @@ int thor_mlp_loss_grad(thor_mlp *m, const void *x_bf16, const float *t, int B, d
   if (!m || !x_bf16 || !t) { set_error("thor_mlp_loss_grad: NULL argument"); return THOR_EINVAL; }
   if (B < 1 || B > m->max_batch || B % 32) { set_error("thor_mlp_loss_grad: batch must be a multiple of 32 within max_batch"); return THOR_EINVAL; }
   if (((uintptr_t)x_bf16 & 15) != 0) { set_error("thor_mlp_loss_grad: inputs must be 16-byte aligned"); return THOR_EINVAL; }
-  const Parts parts = loss_and_grad(m, (const __bf16 *)x_bf16, t, B);
-  hipLaunchKernelGGL(k_update<false>, dim3(nb(m->n_params / kUpd)), dim3(256), 0, m->stream, update_net(m, parts.grad),
-                     m->n_params, (float *)nullptr, (float *)nullptr, (float *)nullptr, m->g, Adam{});
-  const size_t np = parts.loss;
+  const size_t np = passes(m, (const __bf16 *)x_bf16, t, B);
+  gradients<false>(m, (const __bf16 *)x_bf16, B, Adam{});
   std::vector<float> part(np);
   if (!mlp_ok(hipMemcpyAsync(part.data(), m->partial, np * 4, hipMemcpyDeviceToHost, m->stream), "copy loss"))
     return THOR_EHIP;
@@ -1146,12 +1169,11 @@ int thor_mlp_train_step(thor_mlp *m, const void *x_bf16, const float *t, int B, 
   if (!m || !x_bf16 || !t) { set_error("thor_mlp_train_step: NULL argument"); return THOR_EINVAL; }
   if (B < 1 || B > m->max_batch || B % 32 || !(lr > 0)) { set_error("thor_mlp_train_step: batch must be a multiple of 32 within max_batch, lr > 0"); return THOR_EINVAL; }
   if (((uintptr_t)x_bf16 & 15) != 0) { set_error("thor_mlp_train_step: inputs must be 16-byte aligned"); return THOR_EINVAL; }
-  const Parts parts = loss_and_grad(m, (const __bf16 *)x_bf16, t, B);
+  passes(m, (const __bf16 *)x_bf16, t, B);
   m->adam_t += 1;
   const float b1 = 0.9f, b2 = 0.999f;
   const float c1 = 1.f - std::pow(b1, (float)m->adam_t), c2 = 1.f - std::pow(b2, (float)m->adam_t);
-  hipLaunchKernelGGL(k_update<true>, dim3(nb(m->n_params / kUpd)), dim3(256), 0, m->stream, update_net(m, parts.grad),
-                     m->n_params, m->p, m->m, m->v, (float *)nullptr, Adam{lr, b1, b2, 1e-8f, c1, c2});
+  gradients<true>(m, (const __bf16 *)x_bf16, B, Adam{lr, b1, b2, 1e-8f, c1, c2});
   return mlp_ok(hipGetLastError(), "train step") ? THOR_OK : THOR_EHIP;
 }
 

@@ -247,3 +247,18 @@ def test_restriction_map_is_nearest_point():
     assert len(np.unique(m)) == cg.n
     ties = np.sum(m != np.argmax(dots, axis=1))
     assert ties < 0.01 * fg.n
+
+
+@pytest.mark.parametrize("widths,n_max", [([4096] * 17, 1), ([2048, 4096, 512, 32], 1), ([1120, 256, 256, 256, 160], 4)])
+def test_network_memory_holds_one_gradient_launch(widths, n_max):
+    """thor_mlp_bytes: 20 bytes per parameter (FP32 parameters, gradients, two
+    moments, two BF16 copies; 2 more for the transposed copies of the
+    corrector's shape), 12 per row and layer width, 32 x 4 per bias, and the
+    weight gradients' 8 partial sums of the layers that share a launch: the
+    corrector's four, else one layer at a time, not of the whole network."""
+    thor = _thor()
+    B = 64
+    sizes = [a * b for a, b in zip(widths[:-1], widths[1:])]
+    bound = 22 * (sum(sizes) + sum(widths)) + (12 * B + 128) * sum(widths) + 8 * B * widths[-1]
+    bound += 32 * sum(sorted(sizes)[-n_max:]) + 256 * (10 * len(widths) + 6)
+    assert thor.thor_mlp_bytes(widths, B) <= bound

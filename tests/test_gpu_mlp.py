@@ -210,3 +210,10 @@ def test_loss_adds_squares_without_losing_digits(widths, B, c):
     for fused in (True, False):
         net.set_fused(fused)
         assert abs(net.loss_grad(x, t, want_grad=False)[0] / c ** 2 - 1) <= 2.0 ** -24
+
+
+@pytest.mark.parametrize("widths,B", [([2048, 4096, 512, 32], 64), ([32, 4096, 2304, 64], 1056)])
+def test_gradients_of_networks_that_share_their_partial_sums(widths, B):
+    """Layers whose partial sums pass 256 MiB together take several gradient
+    launches in turn: two of one and two layers, and three of one."""
+    test_gradients_and_adam_at_ragged_tiles(widths, B)
