@@ -217,3 +217,30 @@ def test_gradients_of_networks_that_share_their_partial_sums(widths, B):
     """Layers whose partial sums pass 256 MiB together take several gradient
     launches in turn: two of one and two layers, and three of one."""
     test_gradients_and_adam_at_ragged_tiles(widths, B)
+
+
+@pytest.mark.parametrize("K", [32, 64, 96, 128, 192, 224, 256, 288, 320, 384, 448])
+def test_products_of_few_tiles(K):
+    """One to seven 64-k tiles, whole and half ones: a layer of whole numbers
+    (exact in BF16 and in FP32 sums) over K inputs, and its weight gradient over
+    K rows from the gradient of the outputs as the kernels round it (its FP32
+    sum of K terms: K 2^-24 of their absolute sum)."""
+    import torch
+    from paper_1607_05535_amd import thor
+    say(f"[mlp] {K} inputs and rows")
+    rs = np.random.default_rng(K)
+    net = thor.MLP([K, 96], K)
+    net.set_params(rs.integers(-4, 5, net.n_params).astype(np.float32))
+    (W, b), = net.unpack(net.get_params())
+    x = rs.integers(-4, 5, (K, K)).astype(np.float32)
+    t = rs.integers(-4, 5, (K, 96)).astype(np.float32)
+    xd, td = torch.from_numpy(x).to("cuda:0").to(torch.bfloat16), torch.from_numpy(t).to("cuda:0")
+    y = torch.empty(K, 96, device="cuda:0")
+    net.forward(xd, y)
+    ref = x @ W.T + b
+    assert np.array_equal(y.cpu().numpy(), ref)
+    loss, g = net.loss_grad(xd, td)
+    d = torch.from_numpy(2 * (ref - t) / np.float32(K * 96)).to(torch.bfloat16).double().numpy()
+    (gW, _), = net.unpack(g)
+    assert np.all(np.abs(gW - d.T @ x) <= K * 2.0 ** -24 * (np.abs(d).T @ np.abs(x)))
+    assert abs(loss / np.mean((ref - t).astype(np.float64) ** 2) - 1) <= 2.0 ** -24
