@@ -11,13 +11,12 @@
 #include <map>
 #include <new>
 #include <string>
-#include <system_error>
-#include <thread>
 #include <vector>
 
 #include "internal.h"
 #include "kernels.h"
 #include "state.h"
+#include "two_threads.h"
 
 namespace thor {
 
@@ -440,21 +439,13 @@ bool copy_out(thor_state *s, double *dst, const double *src, size_t n) {
     return e != hipSuccess ? e : w;
   };
   int dev = 0;
-  hipError_t second = hipGetDevice(&dev), first;
-  std::thread t;
-  if (second == hipSuccess) {
-    try {
-      t = std::thread([&] {
-        second = hipSetDevice(dev);
-        if (second == hipSuccess) second = move(n / 2, n, s->cap_stream);
-      });
-    } catch (const std::system_error &) {   // no thread to be had
-    }
-  }
-  const bool split = t.joinable();
-  first = move(0, n / 2, s->stream);
-  if (split) t.join();
-  else second = move(n / 2, n, s->stream);
+  if (!hip_ok(hipGetDevice(&dev), "copy state")) return false;
+  hipError_t first = hipSuccess, second = hipSuccess;
+  run_both([&] { first = move(0, n / 2, s->stream); },
+           [&] {
+             second = hipSetDevice(dev);
+             if (second == hipSuccess) second = move(n / 2, n, s->cap_stream);
+           });
   return hip_ok(first, "copy state") && hip_ok(second, "copy state");
 }
 
