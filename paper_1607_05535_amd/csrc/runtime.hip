@@ -421,16 +421,27 @@ double family_mean(thor_state *s, const char *name, int *count) {
   return n ? sum / n : 0.0;
 }
 
+// Whether the runtime knows this host memory (pinned or managed: it copies
+// there without a buffer of its own).
+bool known_memory(const void *p) {
+  const hipError_t before = hipPeekAtLastError();
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type != hipMemoryTypeUnregistered;
+  if (before == hipSuccess) (void)hipGetLastError();   // "no such pointer" is no error of the caller's
+  return false;
+}
+
 // n doubles of device memory, written on the state's stream, to the caller's
-// pageable memory.  The runtime fills a pinned buffer and copies it on from
-// the host, in turn (17 GB/s); from kSplitCopy on a second thread moves the
-// other half through the state's second stream, so that one half's transfer
+// memory.  For pageable memory the runtime fills a pinned buffer and copies it
+// on from the host, in turn (17 GB/s); from kSplitCopy on a second thread moves
+// the other half through the state's second stream, so that one half's transfer
 // runs beside the other's host copy.  Checkpoints of 0.5 / 2 / 3.9 / 5.9 / 24
 // / 252 MB take 68 / 144 / 258 / 385 / 1409 / 24400 us in one piece and 151 /
-// 171 / 199 / 276 / 846 / 13100 in two.
+// 171 / 199 / 276 / 846 / 13100 in two.  Pinned memory is filled at the link's
+// rate in one piece: a field of 5.2 / 10.5 MB takes 153 / 258 us, 180 / 285 in two.
 constexpr size_t kSplitCopy = (size_t)3 << 20;   // bytes
 bool copy_out(thor_state *s, double *dst, const double *src, size_t n) {
-  if (n * sizeof(double) < kSplitCopy)
+  if (n * sizeof(double) < kSplitCopy || known_memory(dst))
     return hip_ok(hipMemcpyAsync(dst, src, n * sizeof(double), hipMemcpyDeviceToHost, s->stream), "copy state");
   if (!hip_ok(hipStreamSynchronize(s->stream), "diag synchronize")) return false;
   auto move = [&](size_t i0, size_t i1, hipStream_t st) {

@@ -72,3 +72,23 @@ def test_winds_use_a_double_basis(precision):
     for name, basis in (("u", east), ("v", north)):
         got, want = st.field(name)[0], (m * basis).sum(0)
         assert np.abs(got - want).max() <= 1e-14 * np.abs(m).max(), name
+
+
+def test_pinned_memory_gets_the_same_bytes():
+    """A checkpoint and a field of more than 3 MiB into pinned memory (one
+    copy) and into pageable memory (two), and no error left behind by asking
+    which it is."""
+    import ctypes
+    import torch
+    from paper_1607_05535_amd import thor
+    st = lib_state(small_earth(glevel=5, n_lev=40))
+    st.step(1, 6)
+    for kind, field, n in ((thor.THOR_DIAG_STATE_EXPORT, 0, st.export()[0].size), (thor.THOR_DIAG_FIELD, 1, st.n_col * 40)):
+        out = [torch.zeros(n, dtype=torch.float64, pin_memory=pin) for pin in (False, True)]
+        for o in out:
+            assert thor.lib().thor_diag(st.handle, kind, field, ctypes.c_void_p(o.data_ptr()),
+                                        ctypes.c_size_t(8 * n)) == 0
+        assert out[0].abs().max() > 0 and torch.equal(out[0], out[1])
+    net = thor.MLP([32, 32], 32)   # reports the runtime's last error after its launches
+    x, y = torch.zeros(32, 32, dtype=torch.bfloat16, device="cuda:0"), torch.empty(32, 32, device="cuda:0")
+    net.forward(x, y)
