@@ -87,16 +87,30 @@ def achieved_gbs(w, kt, mixed, per_cell=(vert_moved_per_cell, hmom_moved_per_cel
     return out
 
 
+# what the phase-V kernel is compiled from
+KERNEL_SOURCES = ("kernels.hip", "kernels.h", "internal.h", "powd.h")
+
+
+def kernel_sources_sha256():
+    """SHA-256 of the kernels' sources, one after the other."""
+    import hashlib
+    h = hashlib.sha256()
+    csrc = os.path.join(ROOT, "paper_1607_05535_amd", "csrc")
+    for name in KERNEL_SOURCES:
+        path = os.path.join(csrc, name)
+        if name == "kernels.hip" or os.path.exists(path):
+            h.update(open(path, "rb").read())
+    return h.hexdigest()
+
+
 def counter_traffic():
     """HBM bytes per phase-V launch from the committed FETCH_SIZE/WRITE_SIZE
     counter summary (scaled by the copy-kernel calibration), if it was taken
     on the kernels as they are now; else None."""
-    import hashlib
     path = os.path.join(ROOT, "profiles", "vert_g6L32_counters.json")
-    src = os.path.join(ROOT, "paper_1607_05535_amd", "csrc", "kernels.hip")
     try:
         rec = json.load(open(path))
-        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
+        sha = kernel_sources_sha256()
     except (OSError, ValueError):
         return None
     return rec["hbm_bytes_per_launch"] if rec.get("kernels_hip_sha256") == sha else None

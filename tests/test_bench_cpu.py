@@ -54,3 +54,35 @@ def test_counter_traffic_only_for_the_kernels_it_was_taken_on(tmp_path, monkeypa
     assert bench.counter_traffic() is None
     summary.write_text("not json")
     assert bench.counter_traffic() is None
+
+
+def test_counter_traffic_follows_the_headers_too(tmp_path, monkeypatch):
+    """Device code that the measured kernel inlines lives in headers; a change
+    in any of them makes the stored counters stale as well."""
+    import json
+    sys.path.insert(0, ROOT)
+    import bench
+    src = tmp_path / "paper_1607_05535_amd" / "csrc"
+    src.mkdir(parents=True)
+    (tmp_path / "profiles").mkdir()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    names = ("kernels.hip", "kernels.h", "internal.h", "powd.h")
+    for name in names:
+        (src / name).write_text("// " + name)
+    (tmp_path / "profiles" / "vert_g6L32_counters.json").write_text(
+        json.dumps({"hbm_bytes_per_launch": 123.0, "kernels_hip_sha256": bench.kernel_sources_sha256()}))
+    assert bench.counter_traffic() == 123.0
+    for name in names:
+        (src / name).write_text("// changed")
+        assert bench.counter_traffic() is None, name
+        (src / name).write_text("// " + name)
+    assert bench.counter_traffic() == 123.0
+    # the names that the kernels' file includes, directly or by a header
+    real = os.path.join(ROOT, "paper_1607_05535_amd", "csrc")
+    seen, todo = set(), ["kernels.hip"]
+    while todo:
+        n = todo.pop()
+        if n not in seen:
+            seen.add(n)
+            todo += [l.split('"')[1] for l in open(os.path.join(real, n)) if l.startswith('#include "') and "thor.h" not in l]
+    assert seen == set(bench.KERNEL_SOURCES)
