@@ -90,10 +90,11 @@ struct Fields {
 // or, across a lane boundary, one shuffle.
 constexpr int kHq = 4;
 
-// 1 / x from the hardware reciprocal estimate refined by Newton steps, the
-// last of which leaves half a unit of rounding and a term below 2^-40 of it;
-// x / y from r = 1 / y with the remainder's correction, rounded as well.
+// 1 / x from the hardware reciprocal estimate refined by Newton steps (two in
+// FP64, one in FP32), and x / y from r = 1 / y with the remainder's correction.
 // For normal operands and quotients (densities, pressures, radii, pivots).
+// Nothing here proves correct rounding, but of 5.2e9 random operands in each
+// precision (exponents -20 to 20) both gave the correctly rounded value every time.
 // The compiler's division also scales its operands and repairs special
 // cases, 11 instructions to 5 and 3: 21 of them made up 40 % of the FP64
 // instructions of the slow terms, 32 were 55 % of the large step's first
@@ -197,8 +198,13 @@ inline int n_blocks(const Consts &c, int wpb) { return n_blocks_for(c.N, c.cpw, 
 inline int n_blocks_h(const Consts &c, int wpb) { return n_blocks_for(c.N, c.hcpw, wpb); }
 inline long n_waves_h(const Consts &c) { return (c.N + c.hcpw - 1) / c.hcpw; }
 
-// Wavefronts of at most kLdsCols columns stage stencil weights in LDS, in
-// slices of whole KiB (one copy instruction of the wavefront each).
+// Wavefronts of at most kLdsCols columns (13 levels and up) stage stencil
+// weights in LDS, in slices of whole KiB (one copy instruction of the wavefront
+// each).  A chosen limit: 8 slices of 16 columns fit a workgroup's 64 KiB in
+// either precision (56 in FP64); 21 columns (9 to 12 levels) would fill it and
+// 32 (5 to 8) exceed it in FP64.  Where they would fit, they pay on large grids
+// only: a large step at L = 12 with them and without, g4 167 / 160 us, g5 205.5 /
+// 200.5, g6 438 / 449, g7 1796 / 1986; L = 8, g6 362 / 376, g7 1202 / 1336.
 constexpr int kLdsCols = 16;
 __host__ __device__ inline int wave_bytes(int bytes) { return (bytes + 1023) / 1024 * 1024; }
 // Per wavefront of `cols` columns in phase M (damping and gradient weights);

@@ -2118,8 +2118,7 @@ THOR_KERNEL(diag, 8, map_lane, COMMA int field, COMMA field)
 THOR_KERNEL(import, 8, map_lane, COMMA const double *blob, COMMA blob)
 THOR_KERNEL(friction, 8, map_hlane, , )
 // LDSW (here and below): the stencil weights go through LDS (wave_copy),
-// `lds_wave` bytes per wavefront.  Not for wavefronts of more than kLdsCols
-// columns (n_lev <= 12): 8 of their slices exceed a workgroup's 64 KiB.
+// `lds_wave` bytes per wavefront, for wavefronts of at most kLdsCols columns.
 template <typename H, bool LDSW>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F, sizeof(H) == 8 ? HMOM_OCC_D : HMOM_OCC_F)))

@@ -19,17 +19,24 @@ enum { FAM_LARGE = 0, FAM_SLOW, FAM_HMOM, FAM_VERT, FAM_COUNT };
 static const char *const kFamily[FAM_COUNT] = {"large", "slow", "hmom", "vert"};
 
 // Default wavefronts per workgroup for `waves` gather-mapping wavefronts in a
-// launch (the tuner may choose others).  Up to about four rounds of the
-// card's 3072 slots, single wavefronts fill the compute units most evenly: a
-// large step takes 160 us with 1 and 184 with 4 at g4 L20 (214 wavefronts),
-// 1025 and 1079 at g6 L32 (5121; V 35.5 / 37.5 us, M 23.7 / 25.4), no
-// difference at g6 L64 (10241: V 76.4 / 77.1, M 53.7 / 53.5).  With more
-// rounds the rows that neighbouring wavefronts share in L1 count: g7 L48
-// (32769) V 249 us with 1, 239 with 4, 234 with 8 (in the mixed form 4 is
-// the better: g7 L40 135 against 147), M 170, 166, 187, slow terms 261, 247,
-// 254, large step 685, 662, 644.  An ensemble's launch holds planets of
-// several sizes: 9 planets 3925 us per large step with 4 throughout, 3960
-// with the 8s, 3983 with 1.
+// launch (the tuner may choose others).  The card holds 3072 wavefronts of phase
+// V at a time (3 per SIMD) and 2048 of phase M, the slow terms and k_large1
+// (FP64).  Up to a few rounds of them, single wavefronts fill the compute units
+// most evenly: a large step takes 160 us with 1 and 184 with 4 at g4 L20 (214
+// wavefronts), 1025 and 1079 at g6 L32 (5121); at 10241 it makes little
+// difference (g7 L16 2253 / 2249, mixed 1423 / 1422; g6 L64 2072 / 2033, mixed
+// 1220 / 1229).  With more rounds the rows that neighbouring wavefronts share in
+// L1 count, with 1 / 4 / 8:
+//   g7 L20  13654  2899 / 2819 / 2810, mixed 1870 / 1831 / 1890
+//   g7 L24  16385  3456 / 3335 / 3374, mixed 2213 / 2167 / 2248
+//   g7 L32  20481  4370 / 4260 / 4279, mixed 2796 / 2787 / 2859
+//   g7 L40  27307  5659 / 5394 / 5342, mixed 3656 / 3549 / 3617
+// and by kernel (g7 L40) V 209 / 202.5 / 193, mixed 137 / 134 / 144, M 133 / 125
+// / 131, slow terms 216 / 202 / 203, large step 546 / 515 / 499.  The line lies
+// between 10241 and 13654.  An ensemble's launch holds planets of several sizes:
+// 9 planets 3925 us per large step with 4 throughout, 3960 with the 8s, 3983
+// with 1.  The tuner finds a little more (2 for the slow terms at g6, 8 for an
+// ensemble's).
 inline void default_wpb(long waves, bool mixed, bool ensemble, int wpb[FAM_COUNT]) {
   const bool many = waves > 12288;
   wpb[FAM_LARGE] = many ? (ensemble ? 4 : 8) : 1;
