@@ -17,13 +17,13 @@
 
 namespace thor {
 
-// Horizontal-field storage/arithmetic type: double (FP64 path) or float
-// (mixed-precision form).  Vertical solve, reference state and prognostic
-// density / rho-theta / W stay double in both.
 // Values per column of the stencil records, padded so that a record is a
 // multiple of 16 bytes in either precision (they are copied in 16-byte pieces).
 constexpr int kDc = 24, kLc = 8, kFr = 12, kDv = 16, kGt = 12, kDw = 2 * kRing2;
 
+// H: horizontal-field storage/arithmetic type: double (FP64 path) or float
+// (mixed-precision form).  Vertical solve, reference state and prognostic
+// density / rho-theta / W stay double in both.
 template <typename H>
 struct Fields {
   // geometry (per column; a pentagon's missing neighbour, and a missing
