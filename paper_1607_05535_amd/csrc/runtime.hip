@@ -63,7 +63,6 @@ void carve(Carver &cv, Fields<H> &f, size_t N, size_t L, bool anelastic) {
   f.rhat = cv.take<H>(N * 3);
   f.frame = cv.take<H>(N * kFr);
   f.frame64 = sizeof(H) == sizeof(double) ? nullptr : cv.take<double>(N * 6);
-  f.wind64 = sizeof(H) == sizeof(double) ? nullptr : cv.take<double>(N * 6);
   f.dv = cv.take<H>(N * kDv);
   f.gt = cv.take<H>(N * kGt);
   f.ddi = cv.take<int32_t>(N * kRing2);
@@ -113,6 +112,7 @@ void carve(Carver &cv, Fields<H> &f, size_t N, size_t L, bool anelastic) {
   f.rref = anelastic ? cv.take<double>(row_stride(L)) : nullptr;
   f.fC = anelastic ? cv.take<H>(NL) : nullptr;
   f.fI = anelastic ? cv.take<double>(NL) : nullptr;
+  f.wind64 = sizeof(H) == sizeof(double) ? nullptr : cv.take<double>(N * 6);
 }
 
 template <typename H>
